@@ -13,9 +13,9 @@
 
 namespace cd {
 
-// Kepler solution at an interval endpoint.
+// Kepler solution at an interval endpoint (q = dE/dM there).
 struct EndPt {
-    double M, E, sE, cE;
+    double M, E, sE, cE, q;
 };
 
 // Bounds of object c (sinusoid constants os[i]) over the interval between the

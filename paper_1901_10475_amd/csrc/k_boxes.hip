@@ -20,8 +20,8 @@
 // sinusoid's extreme where the interval crosses it.
 //
 // One thread owns one object and a run of consecutive intervals, so each new
-// endpoint's Newton solve starts from the previous one (1-3 iterations) and
-// each endpoint is solved once.  With a uniform step the boxes are written
+// endpoint's solve starts from the previous one and each endpoint is solved
+// once, with one sincos.  With a uniform step the boxes are written
 // time-major (box k * n + i), so the lanes of a wave store consecutive boxes.
 #include <type_traits>
 
@@ -199,16 +199,16 @@ __device__ inline void object_steps(const ObjConst &c, const ObjSinus *os, uint3
     uint64_t ta = k0 * dt < T ? k0 * dt : T;
     EndPt A;
     A.M = c.m0 + c.n * ((double)ta * tick_s);
-    A.E = A.M + c.e * sin(A.M);
-    kepler(A.M, c.e, A.E, A.sE, A.cE);
+    A.E = kepler_start(A.M, c.e);
+    kepler(A.M, c.e, A.E, A.sE, A.cE, A.q);
     double pa[3];
     position(c, A.sE, A.cE, pa);
     for (uint64_t k = k0; k < k1; ++k) {
         uint64_t tb = (k + 1) * dt < T ? (k + 1) * dt : T;
         EndPt B;
         B.M = c.m0 + c.n * ((double)tb * tick_s);
-        B.E = A.E + (B.M - A.M) / (1.0 - c.e * A.cE);
-        kepler(B.M, c.e, B.E, B.sE, B.cE);
+        B.E = kepler_next(A.E, A.sE, A.q, c.e, B.M - A.M);
+        kepler(B.M, c.e, B.E, B.sE, B.cE, B.q);
         double pb[3];
         position(c, B.sE, B.cE, pb);
         double lo[3], hi[3];
@@ -359,8 +359,8 @@ __global__ void k_block_codes(const ObjConst *__restrict__ oc, uint32_t n, uint3
     uint64_t tb = k1 * dt < T ? k1 * dt : T;
     ObjConst c = oc[i];
     double M = c.m0 + c.n * (0.5 * (double)(ta + tb) * tick_s);
-    double E = M + c.e * sin(M), sE, cE;
-    kepler(M, c.e, E, sE, cE);
+    double E = kepler_start(M, c.e), sE, cE, q;
+    kepler(M, c.e, E, sE, cE, q);
     double p[3];
     position(c, sE, cE, p);
     double mn[3], inv[3];
@@ -372,72 +372,104 @@ __global__ void k_block_codes(const ObjConst *__restrict__ oc, uint32_t n, uint3
     ucode[(k0 * n + i) * stride] = morton30(p[0], p[1], p[2], mn, inv);
 }
 
-// Per-object steps, object-major output (box off_i + k).  One lane per box, so
-// consecutive lanes store consecutive boxes.  Each lane solves Kepler's
-// equation for the start of its interval; the end of the interval is the next
-// box's start, taken from the next lane by a shuffle (a second solve only for
-// the last box of a wave or of an object).
+// Per-object steps, object-major output (box off_i + k).  A wave owns 64
+// `rows` consecutive boxes and takes them in rows of 64, last row first: one
+// lane per box, so consecutive lanes store consecutive boxes.  Each lane
+// solves Kepler's equation for the start of its interval; the end is the next
+// box's start, taken from the next lane (lane 63: from lane 0 of the row taken
+// before), and a second solve runs only for the wave's last box and for the
+// last box of an object.  The object is found by binary search for the last
+// row and followed downwards from there.
+// Solve-bound with one sincos per box and store-bound after it.
 template <int PREC, int RULE>
 __global__ __launch_bounds__(256) void k_boxes_variable(const ObjConst *__restrict__ oc,
                                                         const ObjSinus *__restrict__ os,
                                                         const ObjSteps *__restrict__ st,
                                                         uint32_t n, uint32_t T, double tick_s,
-                                                        double half_thr, BoxOut out)
+                                                        double half_thr, uint32_t rows,
+                                                        BoxOut out)
 {
-    uint64_t b = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    bool active = b < out.cap;
+    const uint32_t lane = threadIdx.x & 63;
+    const uint64_t w0 = ((uint64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * 64 * rows;
+    if (w0 >= out.cap)
+        return;
+    uint64_t b = w0 + (uint64_t)(rows - 1) * 64 + lane;
     // object owning box b: last i with box_off[i] <= b
-    uint32_t lo = 0, hi = n;
-    while (hi - lo > 1) {
-        uint32_t mid = (lo + hi) >> 1;
+    uint32_t i = 0;
+    for (uint32_t hi = n; hi - i > 1;) {
+        uint32_t mid = (i + hi) >> 1;
         if (st[mid].box_off <= b)
-            lo = mid;
+            i = mid;
         else
             hi = mid;
     }
-    uint32_t i = lo;
     ObjSteps s = st[i];
-    uint64_t k = active ? b - s.box_off : 0;
-    active = active && k < s.K;
     ObjConst c = oc[i];
-    uint64_t ta = k * s.dt < T ? k * s.dt : T;
-    uint64_t tb = (k + 1) * s.dt < T ? (k + 1) * s.dt : T;
-    EndPt A;
-    A.M = c.m0 + c.n * ((double)ta * tick_s);
-    A.E = A.M + c.e * sin(A.M);
-    kepler(A.M, c.e, A.E, A.sE, A.cE);
-    double pa[3];
-    position(c, A.sE, A.cE, pa);
-    // the next lane holds the start of this box's end, if it is the same object
-    int lane = threadIdx.x & 63;
-    double nx = __shfl_down(pa[0], 1, 64), ny = __shfl_down(pa[1], 1, 64),
-           nz = __shfl_down(pa[2], 1, 64);
-    uint32_t ni = __shfl_down(i, 1, 64);
-    uint64_t nk = __shfl_down(k, 1, 64);
-    EndPt B;
-    B.M = c.m0 + c.n * ((double)tb * tick_s);
-    if (RULE != CD_BOX_SPEED) {
-        B.E = __shfl_down(A.E, 1, 64);
-        B.sE = __shfl_down(A.sE, 1, 64);
-        B.cE = __shfl_down(A.cE, 1, 64);
-    }
-    double pb[3];
-    if (lane < 63 && ni == i && nk == k + 1 && k + 1 < s.K) {
-        pb[0] = nx;
-        pb[1] = ny;
-        pb[2] = nz;
-    } else {
-        B.E = A.E + (B.M - A.M) / (1.0 - c.e * A.cE);
-        kepler(B.M, c.e, B.E, B.sE, B.cE);
-        position(c, B.sE, B.cE, pb);
-    }
-    if (!active)
-        return;
-    double blo[3], bhi[3];
-    box_bounds<RULE>(c, os, i, A, B, pa, pb, (double)(tb - ta) * tick_s, half_thr, blo, bhi);
-    uint32_t t1 = (k + 1 == s.K) ? (uint32_t)(T + 1) : (uint32_t)tb;
     const CodeFrame f(out);
-    store_box<PREC>(out, f, b, pa, pb, blo, bhi, (uint32_t)ta, t1, i, kNoCode);
+    EndPt A0{};                      // lane 0's start of the row taken before
+    double p0[3] = {0.0, 0.0, 0.0};
+    uint32_t i0 = kEnd;
+    uint64_t k0 = 0;
+    for (uint32_t row = rows; row-- > 0; b -= 64) {
+        if (s.box_off > b) {
+            do
+                s = st[--i];
+            while (s.box_off > b);
+            c = oc[i];
+        }
+        bool active = b < out.cap;
+        uint64_t k = active ? b - s.box_off : 0;
+        active = active && k < s.K;
+        uint64_t ta = k * s.dt < T ? k * s.dt : T;
+        uint64_t tb = (k + 1) * s.dt < T ? (k + 1) * s.dt : T;
+        EndPt A;
+        A.M = c.m0 + c.n * ((double)ta * tick_s);
+        A.E = kepler_start(A.M, c.e);
+        kepler(A.M, c.e, A.E, A.sE, A.cE, A.q);
+        double pa[3], pb[3];
+        position(c, A.sE, A.cE, pa);
+        uint32_t ni = __shfl_down(i, 1, 64);
+        uint64_t nk = __shfl_down(k, 1, 64);
+        EndPt B;
+        for (int d = 0; d < 3; ++d)
+            pb[d] = __shfl_down(pa[d], 1, 64);
+        if (RULE != CD_BOX_SPEED) {
+            B.E = __shfl_down(A.E, 1, 64);
+            B.sE = __shfl_down(A.sE, 1, 64);
+            B.cE = __shfl_down(A.cE, 1, 64);
+        }
+        if (lane == 63) {
+            ni = i0;
+            nk = k0;
+            for (int d = 0; d < 3; ++d)
+                pb[d] = p0[d];
+            B.E = A0.E;
+            B.sE = A0.sE;
+            B.cE = A0.cE;
+        }
+        // this row's lane 0, for the next row's lane 63
+        i0 = __shfl(active ? i : kEnd, 0, 64);
+        k0 = __shfl(k, 0, 64);
+        for (int d = 0; d < 3; ++d)
+            p0[d] = __shfl(pa[d], 0, 64);
+        if (RULE != CD_BOX_SPEED) {
+            A0.E = __shfl(A.E, 0, 64);
+            A0.sE = __shfl(A.sE, 0, 64);
+            A0.cE = __shfl(A.cE, 0, 64);
+        }
+        B.M = c.m0 + c.n * ((double)tb * tick_s);
+        if (!(ni == i && nk == k + 1 && k + 1 < s.K)) {
+            B.E = kepler_next(A.E, A.sE, A.q, c.e, B.M - A.M);
+            kepler(B.M, c.e, B.E, B.sE, B.cE, B.q);
+            position(c, B.sE, B.cE, pb);
+        }
+        if (!active)
+            continue;
+        double blo[3], bhi[3];
+        box_bounds<RULE>(c, os, i, A, B, pa, pb, (double)(tb - ta) * tick_s, half_thr, blo, bhi);
+        uint32_t t1 = (k + 1 == s.K) ? (uint32_t)(T + 1) : (uint32_t)tb;
+        store_box<PREC>(out, f, b, pa, pb, blo, bhi, (uint32_t)ta, t1, i, kNoCode);
+    }
 }
 
 // After the interval counts have been scanned into first-box offsets.
@@ -449,7 +481,7 @@ __global__ void k_steps_apply_offsets(ObjSteps *st, const uint32_t *box_off, uin
     st[i].box_off = box_off[i];
 }
 
-static inline unsigned blocks_for(uint64_t n, unsigned t) { return (unsigned)((n + t - 1) / t); }
+static inline unsigned blocks_for(uint64_t n, uint64_t t) { return (unsigned)((n + t - 1) / t); }
 
 // Calls go(precision tag, rule tag) with compile-time constants; the caller
 // has checked both values.
@@ -621,8 +653,11 @@ static void boxes_variable(hipStream_t s, const ObjConst *oc, const ObjSinus *os
                            const ObjSteps *st, uint32_t n, uint32_t T, double tick_s,
                            double half_thr, const BoxOut &out)
 {
-    k_boxes_variable<PREC, RULE><<<blocks_for(out.cap, 256), 256, 0, s>>>(oc, os, st, n, T,
-                                                                         tick_s, half_thr, out);
+    // rows of 64 boxes per wave: enough to spread the second solve and the
+    // object search, as long as the grid keeps a few thousand waves
+    const uint32_t rows = out.cap >= (1u << 21) ? 8u : out.cap >= (1u << 19) ? 2u : 1u;
+    k_boxes_variable<PREC, RULE><<<blocks_for(out.cap, 256 * (uint64_t)rows), 256, 0, s>>>(
+        oc, os, st, n, T, tick_s, half_thr, rows, out);
 }
 
 hipError_t launch_boxes_variable(const ObjConst *oc, const ObjSinus *os, const ObjSteps *st,

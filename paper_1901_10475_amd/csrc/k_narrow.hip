@@ -21,22 +21,17 @@ namespace cd {
 
 struct Walker {
     ObjConst c;
-    double E = 0.0, M = 0.0;
+    double E = 0.0, M = 0.0, sE = 0.0, q = 0.0;
     bool warm = false;
     __device__ void at(double t_s, double p[3])
     {
         double m = c.m0 + c.n * t_s;
-        if (warm && fabs(m - M) < 1.0) {   // short step: extrapolate from the last E
-            double sE, cE;
-            sincos(E, &sE, &cE);
-            E += (m - M) / (1.0 - c.e * cE);
-        } else {
-            E = m + c.e * sin(m);
-            warm = true;
-        }
+        // short step: extrapolate from the last solution
+        E = warm && fabs(m - M) < 0.25 ? kepler_next(E, sE, q, c.e, m - M) : kepler_start(m, c.e);
+        warm = true;
         M = m;
-        double sE, cE;
-        kepler(m, c.e, E, sE, cE);
+        double cE;
+        kepler(m, c.e, E, sE, cE, q);
         position(c, sE, cE, p);
     }
 };

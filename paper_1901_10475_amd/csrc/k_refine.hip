@@ -47,9 +47,27 @@ __global__ void k_refine_seed(const cd_pair *__restrict__ pairs, uint32_t count,
 __device__ inline void solve_at(const ObjConst &c, double t_s, EndPt &P, double p[3])
 {
     P.M = c.m0 + c.n * t_s;
-    P.E = P.M + c.e * sin(P.M);
-    kepler(P.M, c.e, P.E, P.sE, P.cE);
+    P.E = kepler_start(P.M, c.e);
+    kepler(P.M, c.e, P.E, P.sE, P.cE, P.q);
     position(c, P.sE, P.cE, p);
+}
+
+// The span's other end, t_s >= the time of A: the same point for a single
+// instant, a warm start for a short span.
+__device__ inline void solve_end(const ObjConst &c, double t_s, const EndPt &A, const double pa[3],
+                                 EndPt &B, double pb[3])
+{
+    const double M = c.m0 + c.n * t_s;
+    if (M == A.M) {
+        B = A;
+        for (int d = 0; d < 3; ++d)
+            pb[d] = pa[d];
+        return;
+    }
+    B.M = M;
+    B.E = M - A.M < 0.25 ? kepler_next(A.E, A.sE, A.q, c.e, M - A.M) : kepler_start(M, c.e);
+    kepler(M, c.e, B.E, B.sE, B.cE, B.q);
+    position(c, B.sE, B.cE, pb);
 }
 
 template <int RULE>
@@ -89,7 +107,7 @@ __global__ __launch_bounds__(256) void k_refine_level(
                     EndPt A, B;
                     double pa[3], pb[3];
                     solve_at(ci, ta, A, pa);
-                    solve_at(ci, tb, B, pb);
+                    solve_end(ci, tb, A, pa, B, pb);
                     box_bounds<RULE>(ci, os, pr.i, A, B, pa, pb, tb - ta, half_thr, lo_i, hi_i);
                 }
                 {
@@ -97,7 +115,7 @@ __global__ __launch_bounds__(256) void k_refine_level(
                     EndPt A, B;
                     double pa[3], pb[3];
                     solve_at(cj, ta, A, pa);
-                    solve_at(cj, tb, B, pb);
+                    solve_end(cj, tb, A, pa, B, pb);
                     box_bounds<RULE>(cj, os, pr.j, A, B, pa, pb, tb - ta, half_thr, lo_j, hi_j);
                 }
                 keep = true;
