@@ -153,7 +153,23 @@ struct CodeFrame {
 // (kNoCode: compute it).
 constexpr int64_t kNoCode = -1;
 
-template <int PREC>
+// NT: non-temporal stores.  Consecutive lanes write consecutive boxes, so each
+// store instruction fills whole cache lines of one array, and the boxes are
+// read again only by the tree build.  Measured both ways: the uniform-step
+// boxes (60.65 M, FP64) take 0.78 ms with them against 0.94, per-object FP32
+// boxes (88 M) 1.21 against 1.27 ms, but per-object FP64 boxes (79.7 M) 1.63
+// against 1.02 ms with ordinary stores, where the L2 gathers the wave's
+// successive 512-byte pieces of six arrays.
+template <bool NT, class T>
+__device__ inline void store_to(T v, T *p)
+{
+    if (NT)
+        __builtin_nontemporal_store(v, p);
+    else
+        *p = v;
+}
+
+template <int PREC, bool NT>
 __device__ inline void store_box(const BoxOut &o, const CodeFrame &f, uint64_t b,
                                  const double pa[3], const double pb[3], const double blo[3],
                                  const double bhi[3], uint32_t t0, uint32_t t1, uint32_t obj,
@@ -161,31 +177,25 @@ __device__ inline void store_box(const BoxOut &o, const CodeFrame &f, uint64_t b
 {
     if (b >= o.cap)
         return;
-
-    // Non-temporal stores: consecutive lanes write consecutive boxes, so each
-    // store instruction fills whole cache lines of one array, and the boxes
-    // are read again only by the tree build, long after they would have left
-    // the caches (0.94 -> 0.78 ms for the 60.65 M boxes of the tracked hour).
     if (o.code)
-        __builtin_nontemporal_store(
-            code != kNoCode ? (uint32_t)code
-                            : morton30(0.5 * (pa[0] + pb[0]), 0.5 * (pa[1] + pb[1]),
-                                       0.5 * (pa[2] + pb[2]), f.mn, f.inv),
-            &o.code[b]);
+        store_to<NT>(code != kNoCode ? (uint32_t)code
+                                     : morton30(0.5 * (pa[0] + pb[0]), 0.5 * (pa[1] + pb[1]),
+                                                0.5 * (pa[2] + pb[2]), f.mn, f.inv),
+                     &o.code[b]);
     for (int d = 0; d < 3; ++d) {
         double lo = blo[d];
         double hi = bhi[d];
         if (PREC == CD_FP64) {
-            __builtin_nontemporal_store(lo, &((double *)o.lo[d])[b]);
-            __builtin_nontemporal_store(hi, &((double *)o.hi[d])[b]);
+            store_to<NT>(lo, &((double *)o.lo[d])[b]);
+            store_to<NT>(hi, &((double *)o.hi[d])[b]);
         } else {
-            __builtin_nontemporal_store(__double2float_rd(lo), &((float *)o.lo[d])[b]);
-            __builtin_nontemporal_store(__double2float_ru(hi), &((float *)o.hi[d])[b]);
+            store_to<NT>(__double2float_rd(lo), &((float *)o.lo[d])[b]);
+            store_to<NT>(__double2float_ru(hi), &((float *)o.hi[d])[b]);
         }
     }
-    __builtin_nontemporal_store(t0, &o.t0[b]);
-    __builtin_nontemporal_store(t1, &o.t1[b]);
-    __builtin_nontemporal_store(obj, &o.obj[b]);
+    store_to<NT>(t0, &o.t0[b]);
+    store_to<NT>(t1, &o.t1[b]);
+    store_to<NT>(obj, &o.obj[b]);
 }
 
 // Intervals [k0, k1) of object i: each box is handed to sink(k, pa, pb, lo,
@@ -236,7 +246,7 @@ struct ArraySink {
                                const double lo[3], const double hi[3], uint32_t t0,
                                uint32_t t1) const
     {
-        store_box<PREC>(out, f, base + k * stride, pa, pb, lo, hi, t0, t1, obj, code);
+        store_box<PREC, true>(out, f, base + k * stride, pa, pb, lo, hi, t0, t1, obj, code);
     }
 };
 
@@ -380,7 +390,8 @@ __global__ void k_block_codes(const ObjConst *__restrict__ oc, uint32_t n, uint3
 // before), and a second solve runs only for the wave's last box and for the
 // last box of an object.  The object is found by binary search for the last
 // row and followed downwards from there.
-// Solve-bound with one sincos per box and store-bound after it.
+// Bound by its stores since the solve takes one sincos: 79.7 M FP64 boxes
+// 2.17 -> 1.02 ms (5.0 TB/s), 88 M FP32 boxes 2.66 -> 1.21 ms.
 template <int PREC, int RULE>
 __global__ __launch_bounds__(256) void k_boxes_variable(const ObjConst *__restrict__ oc,
                                                         const ObjSinus *__restrict__ os,
@@ -468,7 +479,7 @@ __global__ __launch_bounds__(256) void k_boxes_variable(const ObjConst *__restri
         double blo[3], bhi[3];
         box_bounds<RULE>(c, os, i, A, B, pa, pb, (double)(tb - ta) * tick_s, half_thr, blo, bhi);
         uint32_t t1 = (k + 1 == s.K) ? (uint32_t)(T + 1) : (uint32_t)tb;
-        store_box<PREC>(out, f, b, pa, pb, blo, bhi, (uint32_t)ta, t1, i, kNoCode);
+        store_box<PREC, PREC == CD_FP32>(out, f, b, pa, pb, blo, bhi, (uint32_t)ta, t1, i, kNoCode);
     }
 }
 

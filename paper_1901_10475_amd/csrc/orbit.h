@@ -44,11 +44,11 @@ __device__ inline double kepler_start(double M, double e)
     const double turn = 6.283185307179586476925286766559;
     const float m = (float)(M - turn * rint(M * 0.15915494309189533577));
     const float ef = (float)e;
-    float x = ef * __sinf(m) / (1.0f - ef * __cosf(m));
+    float x = ef * __sinf(m) * __builtin_amdgcn_rcpf(1.0f - ef * __cosf(m));
     x = fminf(fmaxf(x, -ef), ef);
 #pragma unroll
     for (int it = 0; it < 2; ++it) {
-        x -= (x - ef * __sinf(m + x)) / (1.0f - ef * __cosf(m + x));
+        x -= (x - ef * __sinf(m + x)) * __builtin_amdgcn_rcpf(1.0f - ef * __cosf(m + x));
         x = fminf(fmaxf(x, -ef), ef);
     }
     return M + (double)x;
