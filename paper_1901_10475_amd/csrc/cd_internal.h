@@ -547,7 +547,7 @@ size_t refit_list_slots(uint32_t N, uint32_t *base);
 hipError_t launch_karras_slabs(const uint32_t *codes, uint32_t N, uint32_t slab_size, uint2 *kids,
                                const LinkSink &links, uint32_t *parent, uint8_t *clev,
                                hipStream_t s);
-// Hierarchy and inner boxes in one bottom-up pass (k_agglo.hip) over FP64
+// Hierarchy and inner boxes bottom-up (k_agglo.hip) over FP64
 // leaf records already in place in key order (keys: slab j / slab_size above
 // code[j]): inner records, child pairs, leaf skip links (leaf_esc, one per
 // leaf), refit seeds; the leaves' slabs (t0 / slab_ticks) and the key order

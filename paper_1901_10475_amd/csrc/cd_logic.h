@@ -256,24 +256,32 @@ __host__ __device__ inline uint32_t slab_escape32(const SlabKeys32 &k, uint32_t 
 
 // ---- bottom-up construction of the same tree -----------------------------------
 //
-// A node covering leaves [f, l] is the left child of its parent when keys l
-// and l+1 share a longer prefix than keys f-1 and f (the parent is [f, l'],
-// split after leaf l), else the right child (parent [f', l], split after
-// f-1); with positions breaking equal keys the two prefixes always differ.
-// Its id in the numbering above: leaf N-1+f when f == l, else l for a left
-// child and f for a right child (the root, [0, N-1], is 0).
+// Every split between two neighbouring leaves belongs to exactly one inner
+// node.  With a(j) the length of the prefix that keys j and j + 1 share, the
+// node split after leaf g covers the leaves between the nearest splits with a
+// smaller a on either side: [p + 1, n], a(p) < a(g) > a(n) (a is -1 below leaf 0
+// and from leaf N - 1 on).  Its parent is the split of p and n with the larger
+// a, and it is that parent's left child when it is n.  Ids are those above: an
+// inner node's id is its last leaf when it is a left child, its first leaf
+// when it is a right child, and 0 for the root, so the children of the node
+// split after g sit at the positions g and g + 1 (as a leaf or as an inner
+// node with that id).  For keys in order no two competing prefixes are equal;
+// keys out of order (reported as an error) may tie, and a tie then goes to the
+// smaller position, so that the structure stays a tree for any input.
 
-// Common prefix of keys a (at position i) and b (at j), equal keys broken by
-// position: clz of the 64-bit XOR, or 96 + clz of the 32-bit position XOR
-// (i != j); written as selects, without branches.
-__host__ __device__ inline int key_prefix(uint64_t a, uint64_t b, uint32_t i, uint32_t j)
+// a(j) + 1 in seven bits: the common prefix of keys a (position i) and b (j),
+// equal keys continued by the positions' XOR (i != j): 1..64 for keys that
+// differ, 65..96 for equal ones; 0 stands for "no key".
+__host__ __device__ inline uint32_t prefix7(uint64_t a, uint64_t b, uint32_t i, uint32_t j)
 {
     uint64_t x = a ^ b;
     uint32_t h = (uint32_t)(x >> 32), l = (uint32_t)x, p = i ^ j;
-    int ch = h ? __builtin_clz(h) : 0, cl = l ? __builtin_clz(l) : 0;
-    int cp = p ? __builtin_clz(p) : 0;
-    return h ? ch : (l ? 32 + cl : 96 + cp);
+    uint32_t ch = h ? (uint32_t)__builtin_clz(h) : 0, cl = l ? (uint32_t)__builtin_clz(l) : 0;
+    uint32_t cp = p ? (uint32_t)__builtin_clz(p) : 0;
+    return 1u + (h ? ch : (l ? 32u + cl : 64u + cp));
 }
+constexpr uint32_t kPrefixTie = 65;   // smallest prefix7 of equal keys
+constexpr uint32_t kPrefixPad = 127;  // above every prefix7
 
 // key(j) = (j / ms) << 32 | code[j]: time slabs of ms leaves above 32-bit codes.
 struct CodeKeys {
@@ -283,89 +291,125 @@ struct CodeKeys {
     {
         return ((uint64_t)(j / ms) << 32) | code[j];
     }
-    __host__ __device__ int delta(uint32_t i, uint32_t j) const
+};
+
+// Bytes of X (each below 128) that are <= y or < y: the top bit of each byte.
+__host__ __device__ inline uint64_t bytes_le(uint64_t X, uint32_t y)
+{
+    return ((0x8080808080808080ull + 0x0101010101010101ull * y) - X) & 0x8080808080808080ull;
+}
+__host__ __device__ inline uint64_t bytes_lt(uint64_t X, uint32_t y)
+{
+    return ((0x7F7F7F7F7F7F7F7Full + 0x0101010101010101ull * y) - X) & 0x8080808080808080ull;
+}
+__host__ __device__ inline uint32_t byte_min(uint64_t X)
+{
+    uint32_t m = 255;
+    for (int k = 0; k < 8; ++k) {
+        const uint32_t v = (uint32_t)(X >> (8 * k)) & 0xFFu;
+        m = v < m ? v : m;
+    }
+    return m;
+}
+__host__ __device__ inline uint32_t top_byte(uint64_t hit) { return (63u - (uint32_t)__builtin_clzll(hit)) >> 3; }
+__host__ __device__ inline uint32_t low_byte(uint64_t hit) { return (uint32_t)__builtin_ctzll(hit) >> 3; }
+
+// Up to 1 024 byte values with the minima of every 8 and every 64 of them (as
+// bytes again), so that the nearest value below a bound is found in at most
+// three steps of 8-byte reads.  Unused places hold kPrefixPad.
+constexpr uint32_t kNone = 0xFFFFFFFFu;
+struct ByteMins {
+    const uint64_t *b;    // [128] the values
+    const uint64_t *m8;   // [16]  minima of the words of b
+    const uint64_t *m64;  // [2]   minima of the words of m8
+    __host__ __device__ uint32_t value(uint32_t g) const
     {
-        return j >= N ? -1 : key_prefix(key(i), key(j), i, j);
+        return ((const uint8_t *)b)[g];
+    }
+    // largest p < g with value(p) <= x, or kNone.  The three levels around g
+    // are read at once; at most two reads follow, downwards.
+    __host__ __device__ uint32_t left_le(uint32_t g, uint32_t x) const
+    {
+        uint32_t w = g >> 3, q = w >> 3, r = q >> 3;
+        const uint64_t W0 = b[w], W1 = m8[q], W2 = m64[0], W3 = m64[1];
+        uint64_t h0 = bytes_le(W0, x) & below(g), h1 = bytes_le(W1, x) & below(w);
+        if (!h0) {
+            if (!h1) {
+                uint64_t h2 = bytes_le(r ? W3 : W2, x) & below(q);
+                if (!h2 && r) {
+                    r = 0;
+                    h2 = bytes_le(W2, x);
+                }
+                if (!h2)
+                    return kNone;
+                q = 8 * r + top_byte(h2);
+                h1 = bytes_le(m8[q], x);
+            }
+            w = 8 * q + top_byte(h1);
+            h0 = bytes_le(b[w], x);
+        }
+        return 8 * w + top_byte(h0);
+    }
+    // smallest n > g with value(n) < x, or kNone
+    __host__ __device__ uint32_t right_lt(uint32_t g, uint32_t x) const
+    {
+        uint32_t w = g >> 3, q = w >> 3, r = q >> 3;
+        const uint64_t W0 = b[w], W1 = m8[q], W2 = m64[0], W3 = m64[1];
+        uint64_t h0 = bytes_lt(W0, x) & above(g), h1 = bytes_lt(W1, x) & above(w);
+        if (!h0) {
+            if (!h1) {
+                uint64_t h2 = bytes_lt(r ? W3 : W2, x) & above(q);
+                if (!h2 && r == 0) {
+                    r = 1;
+                    h2 = bytes_lt(W3, x);
+                }
+                if (!h2)
+                    return kNone;
+                q = 8 * r + low_byte(h2);
+                h1 = bytes_lt(m8[q], x);
+            }
+            w = 8 * q + low_byte(h1);
+            h0 = bytes_lt(b[w], x);
+        }
+        return 8 * w + low_byte(h0);
+    }
+    __host__ __device__ static uint64_t below(uint32_t g)   // bytes before byte g % 8
+    {
+        return (1ull << (8 * (g & 7))) - 1;
+    }
+    __host__ __device__ static uint64_t above(uint32_t g)   // bytes after byte g % 8
+    {
+        return (g & 7) == 7 ? 0ull : ~0ull << (8 * ((g & 7) + 1));
     }
 };
 
-// The same keys for the positions lo, lo + 1, ... held in a window sk (lo may
-// wrap below 0: such positions are outside [0, N) and never read).
-struct WindowKeys {
-    const uint64_t *sk;
-    uint32_t lo, N;
-    __host__ __device__ int delta(uint32_t i, uint32_t j) const
-    {
-        return j >= N ? -1 : key_prefix(sk[i - lo], sk[j - lo], i, j);
-    }
+// The node split after item g of a chunk of m items, from the chunk's byte
+// values b (value(k) the prefix after item k, k < m; value(m - 1) the one
+// at the chunk's right edge) and vL, the prefix at its left edge.  formed: all
+// of its items lie in the chunk.
+struct ChunkNode {
+    bool formed;
+    bool whole;       // the node covers the chunk
+    bool left;        // it is a left child (of split n; else of split p)
+    uint32_t p, n;    // it covers items p + 1 .. n; p == kNone: from item 0
 };
-
-// Adjacent prefixes a(j) = delta(j, j+1), -1 at j = N-1 and below 0, held
-// as a(j) + 1 in one byte each (at most 128) for the positions lo, lo + 1, ...
-// A node's parent side, its sibling's shape and the skip links need only these.
-struct AdjBytes {
-    const uint8_t *d;
-    uint32_t lo, N;
-    __host__ __device__ int at(uint32_t j) const { return j >= N - 1 ? -1 : (int)d[j - lo] - 1; }
-};
-
-// karras_escape from adjacent prefixes: node s = r + 1 extends right when
-// a(s) >= a(s - 1).
-template <class A>
-__host__ __device__ inline uint32_t escape_adj(const A &a, uint32_t N, uint32_t r)
+__host__ __device__ inline ChunkNode chunk_node(const ByteMins &B, uint32_t m, uint32_t g,
+                                                uint32_t vL)
 {
-    if (r >= N - 1)
-        return kEnd;
-    uint32_t s = r + 1;
-    if (s <= N - 2 && a.at(s) >= a.at(s - 1))
-        return s;
-    return N - 1 + s;
+    ChunkNode c;
+    const uint32_t x = B.value(g);
+    c.p = B.left_le(g, x);
+    c.n = B.right_lt(g, x);
+    c.formed = (c.p != kNone || vL <= x) && c.n != kNone && c.n < m;
+    c.whole = c.formed && c.p == kNone && c.n == m - 1;
+    c.left = c.formed && B.value(c.n) >= (c.p == kNone ? vL : B.value(c.p));
+    return c;
 }
-
-// Children of the inner node [f, l] split after leaf g.
-__host__ __device__ inline uint2 agglo_children(uint32_t N, uint32_t f, uint32_t l, uint32_t g)
+// The split that is the parent of single item k (kNone: the chunk's left edge;
+// m - 1: its right edge).
+__host__ __device__ inline uint32_t chunk_item_parent(const ByteMins &B, uint32_t k, uint32_t vL)
 {
-    return make_uint2(f == g ? N - 1 + g : g, l == g + 1 ? N - 1 + g + 1 : g + 1);
-}
-
-// Where node [f, l] (not the root) meets its sibling, from dl = a(f - 1) and
-// dr = a(l).
-struct AggloStep {
-    bool right;      // a left child: the parent extends right
-    int prefix;      // key bits the parent's leaves share
-    uint32_t id;     // the node's own id
-    uint32_t split;  // the parent's split: after leaf l (right) or f - 1
-};
-__host__ __device__ inline AggloStep agglo_step(int dl, int dr, uint32_t N, uint32_t f,
-                                                uint32_t l)
-{
-    AggloStep st;
-    st.right = dr > dl;
-    st.prefix = st.right ? dr : dl;
-    st.id = f == l ? N - 1 + f : (st.right ? l : f);
-    st.split = st.right ? l : f - 1;
-    return st;
-}
-
-// Whether the sibling is the single leaf next to the node (l + 1 or f - 1):
-// it is when that leaf's own parent is this node's parent.  Otherwise the
-// sibling is the inner node numbered by that same position (a right child is
-// numbered by its first leaf, a left child by its last).
-template <class A>
-__host__ __device__ inline bool agglo_sibling_is_leaf(const A &a, const AggloStep &st,
-                                                      uint32_t f, uint32_t l)
-{
-    return st.right ? st.prefix > a.at(l + 1) : st.prefix > a.at(f - 2);
-}
-
-// Does the parent of node [f, l] lie within leaves [b0, b1)?  (The node does.)
-template <class V>
-__host__ __device__ inline bool agglo_parent_within(const V &k, uint32_t N, const AggloStep &st,
-                                                    uint32_t f, uint32_t l, uint64_t b0,
-                                                    uint64_t b1)
-{
-    return st.right ? (b1 >= N || k.delta(l, (uint32_t)b1) < st.prefix)
-                    : (b0 == 0 || k.delta(f, (uint32_t)(b0 - 1)) < st.prefix);
+    return B.value(k) >= (k ? B.value(k - 1) : vL) ? k : k - 1;
 }
 
 } // namespace cd

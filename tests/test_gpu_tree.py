@@ -349,3 +349,59 @@ def test_per_object_step_tree(box_prec, tree_prec, horizon, disp_km, slab_ticks)
     assert (room >= 30, room >= 24) == {3000: (True, True), 200000: (False, True),
                                         1 << 22: (False, False)}[horizon], (N, room)
     check_tree(bp)
+
+
+def _prefix_after(key):
+    """Common prefix length of each leaf's key with the next leaf's; equal
+    keys go on with the positions' common prefix (64 + leading zeros)."""
+    def clz(x, bits):
+        n = np.full(len(x), bits, np.int64)
+        for b in range(bits):
+            n[(x >> np.uint64(b)) & np.uint64(1) != 0] = bits - 1 - b
+        return n
+    pos = np.arange(len(key), dtype=np.uint64)
+    x = key[:-1] ^ key[1:]
+    return np.where(x != 0, clz(x, 64), 64 + clz(pos[:-1] ^ pos[1:], 32))
+
+
+@pytest.mark.parametrize("prec,in_tree", [(cd.CD_FP64, True), (cd.CD_FP64, False),
+                                          (cd.CD_FP32, False)])
+@pytest.mark.parametrize("n,K", [(511, 9), (512, 9), (1023, 17), (1024, 8), (1025, 10),
+                                 (2049, 40)])
+def test_radix_tree_of_callers_codes(n, K, prec, in_tree):
+    """Codes that differ between the slabs of a block, runs of equal codes and
+    a slab of one code only, at slab sizes around the half and the full chunk
+    of the bottom-up pass (511 and less share chunks): the leaves keep their
+    positions and every node splits its leaves where their keys share the
+    shortest prefix, which makes it the binary radix tree."""
+    need_gpu()
+    say("radix tree of given codes, n", n, "K", K, "precision", prec, "in tree", in_tree)
+    bp = _uniform(n, K, 2, seed=n + 9, box_precision=prec, tree_precision=prec, in_tree=in_tree,
+                  build=False)
+    cd.cd_build_boxes(bp.el_soa, None, bp.params, bp.boxes, bp.ws_boxes)
+    assert bp.in_tree == in_tree and bp.boxes.desc.layout == cd.CD_LAYOUT_SORTED
+    N = n * K
+    code = bp.boxes.code[:N].cpu().numpy().view(np.uint32).reshape(K, n).copy()
+    rng = np.random.default_rng(n)
+    code[3] = np.sort(rng.integers(0, 1 << 30, n))        # a slab of its own
+    code[5] &= ~np.uint32(0xFFFFF)                        # runs of equal codes
+    code[6] = 12345                                       # one run
+    if K > 8:
+        code[8] = np.sort(rng.integers(0, 1 << 30, n) >> 12 << 12)   # and a block's first
+    bp.boxes.code[:N] = torch.from_numpy(code.ravel().view(np.int32)).to(bp.boxes.code)
+    cd.cd_build_tree(bp.boxes, bp.tree_precision, bp.tree, bp.ws_tree)
+    check_tree(bp)
+    t = _decode(bp.tree, N, prec)
+    kids = t["kids"]
+    first = kids[:, 1].copy()                             # first leaf right of each split
+    while np.any(first < N - 1):
+        inner = first < N - 1
+        first[inner] = kids[first[inner], 0]
+    key = (np.repeat(np.arange(K, dtype=np.uint64), n) << np.uint64(32)) | code.ravel()
+    delta = _prefix_after(key)[first - (N - 1) - 1]
+    for side in (0, 1):
+        child = kids[:, side]
+        inner = child < N - 1
+        assert np.all(delta[child[inner]] > delta[inner])
+    leaf_obj = t["link"][N - 1:]
+    assert np.array_equal(leaf_obj, bp.boxes.obj[:N].cpu().numpy().view(np.uint32))
