@@ -22,9 +22,9 @@
  *     thread-local launch shapes of the traversal (cd_set_tuning), read by
  *     the calling thread's later queries; the process-wide stage profiler
  *     (cd_profile_*, guarded by a mutex); and a process-wide hint, kept in an
- *     atomic, of how many node-pair levels the last drained synchronous query
- *     needed, which sets how many levels the next one launches before its
- *     first host check; and, per thread, the last synchronous query's level
+ *     atomic, of how many node-pair launches the last drained synchronous query
+ *     needed, which sets how many the next one makes before its
+ *     first host check; and, per thread, the last synchronous query's launch
  *     count (cd_last_query_levels) and raw record count (when that fitted the
  *     one-workgroup canonical list, the next query forms its list before the
  *     first host check, on the device's count).  None of them changes a
@@ -325,10 +325,10 @@ int cd_query_pairs(const cd_tree *tree, cd_pair *out, int64_t capacity, int64_t 
  *                         bound of what a repeat with more capacity needs);
  *   *status_dev (uint32): 0, or bit 1 = capacity exceeded (out incomplete),
  *                         bit 2 = tree inconsistent (as CD_E_INVALID above).
- * The node-pair traversal runs for the tuning's max_levels levels, each
- * level ending at once when the previous queue is empty; if its queue
- * overflows or is not drained by then, the per-leaf walk redoes the
- * traversal, decided on the device.  The canonical sort runs over all
+ * The node-pair traversal runs for the tuning's max_levels launches (one
+ * expands one level of many pairs, several levels of few), each ending at once
+ * when the previous queue is empty; if its queue overflows or is not drained by
+ * then, the per-leaf walk redoes the traversal, decided on the device.  The canonical sort runs over all
  * `capacity` slots (unused slots hold a filler record that sorts last), so
  * its cost follows the capacity, not the count.  Workspace as for
  * cd_query_pairs.  Returns CD_OK once everything is enqueued. */
@@ -367,12 +367,12 @@ typedef struct {
     uint32_t expand_threads;  /* lanes per node-pair workgroup: 64 .. 1024, a power of 2
                                  [256]; mode 2 always takes 1024 */
     uint32_t walk_threads;    /* lanes per per-leaf-walk workgroup: 64, 128 or 256 [256] */
-    uint32_t mode;            /* 0 = node pairs, one launch per level, per-leaf walk as
+    uint32_t mode;            /* 0 = node pairs, launch after launch, per-leaf walk as
                                  fallback; 1 = per-leaf walk only; 2 = node pairs, every
                                  level in one launch of a resident grid (levels separated
                                  by a device-wide wait bounded at 2 s, after which the
                                  per-leaf walk takes over), per-leaf walk as fallback [0] */
-    uint32_t max_levels;      /* node-pair levels of cd_query_pairs_async in mode 0,
+    uint32_t max_levels;      /* node-pair launches of cd_query_pairs_async in mode 0,
                                  1..400 [96] */
 } cd_tuning;
 
@@ -380,7 +380,7 @@ typedef struct {
  * change nothing. */
 int cd_set_tuning(const cd_tuning *t);
 int cd_get_tuning(cd_tuning *t);
-/* Node-pair levels the calling thread's last cd_query_pairs ran until its
+/* Node-pair launches the calling thread's last cd_query_pairs made until its
  * queue was empty (0 when that query used the per-leaf walk, or none ran):
  * on the same tree, a max_levels with which cd_query_pairs_async needs no
  * walk. */

@@ -165,18 +165,19 @@ cd_tuning tuning() { return g_tune; }
 constexpr int64_t kMaxBoxes = (1ll << 30) - 1;  // node ids of 2N - 1 nodes below 2^31
 constexpr size_t kTreeHeader = sizeof(TreeHeader);
 constexpr int kExpandBatch = 12;                 // levels launched between count checks
-constexpr int kExpandMaxLevels = 400;            // > 2 x the deepest possible tree
-// Query control block (32-bit words): [l] queue count after level l - 1
-// ([0] stays zero), then the per-leaf-walk flag, the level flags, the
-// one-launch traversal's arrival counter, a status copy (record count
-// low/high, tree error) at an 8-byte-aligned word, and the result of a small
-// canonical list formed before the host read the count.
-constexpr int kCtlWalk = kExpandMaxLevels + 1;
-constexpr int kCtlFlags = kExpandMaxLevels + 2;
-constexpr int kCtlBarrier = kExpandMaxLevels + 3;
-constexpr int kCtlStatus = kExpandMaxLevels + 4;
-constexpr int kCtlCanon = kCtlStatus + 3;   // small canonical list done: records + 1
-constexpr int kCtlWords = kCtlStatus + 4;
+// Query control block (32-bit words): the level flags, the per-leaf-walk flag,
+// the one-launch traversal's arrival counter, a status copy (record count
+// low/high, tree error, last queue with pairs) at an 8-byte-aligned word, the
+// result of a canonical list formed before the host read the count; then the
+// queue counts (that of the seeds' place stays zero).
+constexpr int kCtlFlags = 0;
+constexpr int kCtlWalk = 1;
+constexpr int kCtlBarrier = 2;
+constexpr int kCtlStatus = 4;
+constexpr int kCtlCanon = kCtlStatus + 4;   // canonical list done: records + 1
+constexpr int kCtlHead = kCtlCanon + 1;     // words the host reads
+constexpr int kCtlCounts = 16;
+constexpr int kCtlWords = kCtlCounts + (int)(kExpandSubs * kExpandSubStride);
 // Node-pair levels the last drained traversal needed: the next synchronous
 // query launches that many before its first count check.
 std::atomic<int> g_expand_levels{kExpandBatch};
@@ -326,8 +327,8 @@ struct QueryWS {
     uint32_t *flags, *pos;
     void *scan, *radix;
     uint2 *qa, *qb;
-    unsigned int *qcount, *qflags;
-    uint32_t qcap;
+    unsigned int *ctl, *qcount, *qflags;
+    uint32_t qcap;   // pairs of a queue, a multiple of kExpandSubs
 };
 // Radix passes of the canonical order (i, j, t_lo, t_hi), least significant
 // field first, over the bits each field can use.
@@ -356,8 +357,13 @@ DigitPlan record_plan(const cd_tree *tree)
 }
 
 // node pairs per traversal level: N covers every case seen short of boxes that
-// overlap nearly everything (those overflow into the per-leaf walk)
-uint32_t queue_cap(int64_t N) { return (uint32_t)(N > 65536 ? N : 65536); }
+// overlap nearly everything (those overflow into the per-leaf walk), less the
+// queue counts' room
+uint32_t queue_cap(int64_t N)
+{
+    const uint32_t cap = (uint32_t)(N > 65536 ? N : 65536) - kExpandSubs * kExpandSubStride / 4;
+    return cap / kExpandSubs * kExpandSubs;
+}
 size_t layout_query(void *base, size_t bytes, int64_t N, int64_t cap, QueryWS *w)
 {
     Carve c(base, bytes);
@@ -365,8 +371,9 @@ size_t layout_query(void *base, size_t bytes, int64_t N, int64_t cap, QueryWS *w
     w->qcap = queue_cap(N);
     w->qa = c.take<uint2>(w->qcap);
     w->qb = c.take<uint2>(w->qcap);
-    w->qcount = c.take<unsigned int>(kCtlWords);
-    w->qflags = w->qcount + kCtlFlags;
+    w->ctl = c.take<unsigned int>(kCtlWords);
+    w->qcount = w->ctl + kCtlCounts;
+    w->qflags = w->ctl + kCtlFlags;
     w->raw = c.take<Rec>(m);
     w->alt = c.take<Rec>(m);
     w->counter = c.take<unsigned long long>(1);
@@ -1010,26 +1017,23 @@ int cd_query_pairs(const cd_tree *tree, cd_pair *out, int64_t capacity, int64_t 
         g_last_levels = 0;
         if (N > 1 && tu.mode == 2) {
             // every level in one launch; the walk decided on the device
-            CD_HIP(launch_fill_u32(w.qcount, 0u, kCtlWords, s));
-            CD_HIP(launch_fill_u64(w.counter, 0ull, 1, s));
-            CD_HIP(launch_query_begin(hdr, w.qflags, s));
+            CD_HIP(launch_query_begin(hdr, w.ctl, kCtlWords, kCtlFlags, 0u, w.counter, s));
             CD_HIP(launch_expand_all(nodes, kids, tree->precision, (uint32_t)N, seeds,
                                      &hdr->nseeds, (uint32_t)seed_cap((uint64_t)N), w.qa, w.qb,
                                      w.qcount, w.qcap, kExpandMaxLevels, w.raw,
                                      (unsigned long long)capacity, w.counter, w.qflags,
-                                     w.qcount + kCtlBarrier, tu.expand_blocks, s));
-            CD_HIP(launch_query_decide(w.qcount, w.qflags, w.counter, w.qcount + kCtlWalk, s));
-            run_walk = w.qcount + kCtlWalk;
+                                     w.ctl + kCtlBarrier, tu.expand_blocks, s));
+            CD_HIP(launch_query_decide(w.qcount, 1, w.qflags, w.counter, w.ctl + kCtlWalk, s));
+            run_walk = w.ctl + kCtlWalk;
         } else if (N > 1 && tu.mode == 0) {
-            CD_HIP(launch_fill_u32(w.qcount, 0u, kCtlWords, s));
-            CD_HIP(launch_fill_u64(w.counter, 0ull, 1, s));
-            CD_HIP(launch_query_begin(hdr, w.qflags, s));
+            CD_HIP(launch_query_begin(hdr, w.ctl, kCtlWords, kCtlFlags, 0u, w.counter, s));
             const uint2 *in = seeds;
             const unsigned int *n_in = &hdr->nseeds;
             uint32_t in_cap = (uint32_t)seed_cap((uint64_t)N);
+            const uint32_t sub_cap = w.qcap / kExpandSubs;
             // the control block with the status copy behind it: a drained
             // traversal needs no second read
-            unsigned int ctl[kCtlWords];
+            unsigned int ctl[kCtlHead];
             int lev = 0;
             int batch = g_expand_levels.load(std::memory_order_relaxed);
             batch = batch < 1 ? 1 : (batch > kExpandMaxLevels ? kExpandMaxLevels : batch);
@@ -1053,14 +1057,16 @@ int cd_query_pairs(const cd_tree *tree, cd_pair *out, int64_t capacity, int64_t 
                 for (; lev < end; ++lev) {
                     uint2 *outq = (lev & 1) ? w.qb : w.qa;
                     CD_HIP(launch_expand(nodes, kids, tree->precision, (uint32_t)N, in, n_in,
-                                         in_cap, outq, w.qcount + lev + 1, w.qcap, w.raw,
-                                         (unsigned long long)capacity, w.counter, w.qflags, 1,
-                                         tu.expand_blocks, tu.expand_threads, s));
+                                         in_cap, outq, w.qcount + lev + 1, sub_cap, w.raw,
+                                         (unsigned long long)capacity, w.counter, w.qflags,
+                                         lev == 0, false, tu.expand_blocks,
+                                         tu.expand_threads, s));
                     in = outq;
                     n_in = w.qcount + lev + 1;
-                    in_cap = w.qcap;
+                    in_cap = sub_cap;
                 }
-                CD_HIP(launch_query_status(w.counter, err, w.qcount + kCtlStatus, s));
+                CD_HIP(launch_query_status(w.counter, err, w.qcount, (uint32_t)lev,
+                                           w.ctl + kCtlStatus, s));
                 if (try_canon) {
                     // the list, if the levels drained and the count fits
                     delete trav;
@@ -1069,15 +1075,15 @@ int cd_query_pairs(const cd_tree *tree, cd_pair *out, int64_t capacity, int64_t 
                     if (plan) {
                         const DevCount g{w.counter, w.qflags, err, (uint32_t)kSmallCanon, plan};
                         CD_HIP(launch_medium_canon(w.raw, w.alt, plan, w.flags, w.pos, w.scan,
-                                                   (Rec *)out, s, g, w.qcount + kCtlCanon, 1u));
+                                                   (Rec *)out, s, g, w.ctl + kCtlCanon, 1u));
                     } else {
                         CD_HIP(launch_small_canon_gated(w.raw, w.counter, w.qflags, err,
                                                         (uint32_t)capacity, (Rec *)out,
-                                                        w.qcount + kCtlCanon, s));
+                                                        w.ctl + kCtlCanon, s));
                     }
                     try_canon = false;
                 }
-                CD_HIP(hipMemcpyAsync(ctl, w.qcount, sizeof ctl, hipMemcpyDeviceToHost, s));
+                CD_HIP(hipMemcpyAsync(ctl, w.ctl, sizeof ctl, hipMemcpyDeviceToHost, s));
                 CD_HIP(hipStreamSynchronize(s));
                 qf = ctl[kCtlFlags];
                 if (qf)
@@ -1089,10 +1095,7 @@ int cd_query_pairs(const cd_tree *tree, cd_pair *out, int64_t capacity, int64_t 
             if (!walk) {
                 // levels needed: the last non-empty queue's reader and the one
                 // that found the queue empty
-                int last = 0;
-                for (int l = 1; l <= lev && l <= kExpandMaxLevels; ++l)
-                    if (ctl[l])
-                        last = l;
+                const int last = (int)ctl[kCtlStatus + 3];
                 g_expand_levels.store(last + 2, std::memory_order_relaxed);
                 g_last_levels = last + 1;
                 for (int k = 0; k < 3; ++k)
@@ -1114,8 +1117,8 @@ int cd_query_pairs(const cd_tree *tree, cd_pair *out, int64_t capacity, int64_t 
         }
     }
     if (!status_read) {
-        CD_HIP(launch_query_status(w.counter, err, w.qcount + kCtlStatus, s));
-        CD_HIP(hipMemcpyAsync(stw, w.qcount + kCtlStatus, sizeof stw, hipMemcpyDeviceToHost, s));
+        CD_HIP(launch_query_status(w.counter, err, w.qcount, 0, w.ctl + kCtlStatus, s));
+        CD_HIP(hipMemcpyAsync(stw, w.ctl + kCtlStatus, sizeof stw, hipMemcpyDeviceToHost, s));
         CD_HIP(hipStreamSynchronize(s));
     }
     unsigned long long cnt = (unsigned long long)stw[0] | ((unsigned long long)stw[1] << 32);
@@ -1189,38 +1192,37 @@ int cd_query_pairs_async(const cd_tree *tree, cd_pair *out, int64_t capacity,
         (const uint2 *)((const char *)tree->mem + tree_kids_offset((uint64_t)N, tree->precision));
     const cd_tuning tu = tuning();
     const uint32_t cap = (uint32_t)capacity;
-    unsigned int *walk = w.qcount + kCtlWalk;
-    CD_HIP(launch_fill_u64(w.counter, 0ull, 1, s));
+    unsigned int *walk = w.ctl + kCtlWalk;
     {
         Stage st("traverse", s);
-        CD_HIP(launch_fill_u32(w.qcount, 0u, kCtlWords, s));
-        CD_HIP(launch_fill_u32(w.qflags, tu.mode == 1 ? 4u : 0u, 1, s));
+        CD_HIP(launch_query_begin(hdr, w.ctl, kCtlWords, kCtlFlags, tu.mode == 1 ? 4u : 0u,
+                                  w.counter, s));
         if (N > 1 && tu.mode == 2) {
-            CD_HIP(launch_query_begin(hdr, w.qflags, s));
             CD_HIP(launch_expand_all(nodes, kids, tree->precision, (uint32_t)N, seeds,
                                      &hdr->nseeds, (uint32_t)seed_cap((uint64_t)N), w.qa, w.qb,
                                      w.qcount, w.qcap, kExpandMaxLevels, w.raw, cap, w.counter,
-                                     w.qflags, w.qcount + kCtlBarrier, tu.expand_blocks, s));
+                                     w.qflags, w.ctl + kCtlBarrier, tu.expand_blocks, s));
             // qcount[0] is never written: the flags alone decide
-            CD_HIP(launch_query_decide(w.qcount, w.qflags, w.counter, walk, s));
+            CD_HIP(launch_query_decide(w.qcount, 1, w.qflags, w.counter, walk, s));
             CD_HIP(launch_traverse(nodes, tree->precision, (uint32_t)N, tree->slab_ticks, w.raw,
                                    cap, w.counter, err, walk, tu.walk_threads, side_on, side, s));
         } else if (N > 1) {
-            CD_HIP(launch_query_begin(hdr, w.qflags, s));
             const uint2 *in = seeds;
             const unsigned int *n_in = &hdr->nseeds;
             uint32_t in_cap = (uint32_t)seed_cap((uint64_t)N);
+            const uint32_t sub_cap = w.qcap / kExpandSubs;
             uint32_t levels = tu.mode == 0 ? tu.max_levels : 0;
             for (uint32_t lev = 0; lev < levels; ++lev) {
                 uint2 *outq = (lev & 1) ? w.qb : w.qa;
                 CD_HIP(launch_expand(nodes, kids, tree->precision, (uint32_t)N, in, n_in, in_cap,
-                                     outq, w.qcount + lev + 1, w.qcap, w.raw, cap, w.counter,
-                                     w.qflags, 1, tu.expand_blocks, tu.expand_threads, s));
+                                     outq, w.qcount + lev + 1, sub_cap, w.raw, cap, w.counter,
+                                     w.qflags, lev == 0, lev + 1 == levels, tu.expand_blocks,
+                                     tu.expand_threads, s));
                 in = outq;
                 n_in = w.qcount + lev + 1;
-                in_cap = w.qcap;
+                in_cap = sub_cap;
             }
-            CD_HIP(launch_query_decide(n_in, w.qflags, w.counter, walk, s));
+            CD_HIP(launch_query_decide(n_in, levels ? kExpandSubs : 1, w.qflags, w.counter, walk, s));
             CD_HIP(launch_traverse(nodes, tree->precision, (uint32_t)N, tree->slab_ticks, w.raw,
                                    cap, w.counter, err, walk, tu.walk_threads, side_on, side, s));
         }

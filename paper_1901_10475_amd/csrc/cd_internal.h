@@ -597,18 +597,27 @@ hipError_t launch_traverse(const void *tree, int precision, uint32_t N, uint32_t
                            Rec *out, unsigned long long capacity, unsigned long long *counter,
                            unsigned int *err, const unsigned int *run_if, uint32_t threads,
                            const unsigned int *side_on, const uint32_t *side, hipStream_t s);
-// One breadth-first level of the node-pair self-traversal: every pair in
-// `in` (count *n_in, at most in_cap) is expanded into the overlapping pairs of
-// its children; pairs of two leaves are emitted as records, the others queued
-// in `outq` (count *n_out, capacity out_cap; bit 0 of *flags on overflow,
-// bit 1 on a bad node, bit 3 when *n_in is 0).  gated: return at once if any
-// flag is set.
+// A queue of node pairs is kExpandSubs lists of sub_cap places; the count of
+// list q of the queue that launch l - 1 fills is word q kExpandSubStride + l of
+// the queue counts (1 792 bytes apart: not one memory channel's).
+constexpr int kExpandMaxLevels = 400;            // > 2 x the deepest possible tree
+constexpr uint32_t kExpandSubs = 8, kExpandSubStride = 448;
+static_assert(kExpandSubStride > kExpandMaxLevels, "a count for every launch");
+// One launch of the node-pair self-traversal: every pair in `in` (a queue with
+// counts at n_in, in_cap places a list) is expanded into the overlapping pairs
+// of its children, and, of few pairs, those in turn; pairs of two leaves are
+// emitted as records, pairs left over queued in `outq` (counts at n_out, sub_cap
+// places a list; bit 0 of *flags on overflow, bit 1 on a bad node, bit 3 when
+// `in` is empty).  Returns at once if any flag is set.  first: `in` is the
+// seeds, one list of *n_in (at most in_cap).  last: no launch follows, so
+// nothing is left that the waves can hold (how the pairs fall to them, and so
+// the launches a traversal takes, may differ a little between runs).
 hipError_t launch_expand(const void *tree, const uint2 *kids, int precision, uint32_t N,
                          const uint2 *in, const unsigned int *n_in, uint32_t in_cap, uint2 *outq,
-                         unsigned int *n_out, uint32_t out_cap, Rec *out,
+                         unsigned int *n_out, uint32_t sub_cap, Rec *out,
                          unsigned long long capacity, unsigned long long *counter,
-                         unsigned int *flags, int gated, uint32_t blocks, uint32_t threads,
-                         hipStream_t s);
+                         unsigned int *flags, bool first, bool last, uint32_t blocks,
+                         uint32_t threads, hipStream_t s);
 // Every level in one launch of a resident grid (at most `blocks` workgroups of
 // 1 024 lanes), levels separated by a device-wide wait on *bar (zero before
 // the launch).  Level l reads the seeds (l = 0) or the queue written by level
@@ -629,12 +638,19 @@ constexpr int kCounterWords = 6;
 hipError_t counters_reset(uint32_t *visits, uint32_t nobj, hipStream_t s);
 hipError_t counters_read(unsigned long long *out, hipStream_t s);
 #endif
-// out[0..2] = low and high words of *counter, *tree_err
+// out[0..3] = low and high words of *counter, *tree_err, the last of the queues
+// 1 .. levels (counts in qcount) that held pairs.
 hipError_t launch_query_status(const unsigned long long *counter, const unsigned int *tree_err,
-                               unsigned int *out, hipStream_t s);
-hipError_t launch_query_begin(const TreeHeader *hdr, unsigned int *qflags, hipStream_t s);
-hipError_t launch_query_decide(const unsigned int *last_count, const unsigned int *qflags,
-                               unsigned long long *counter, unsigned int *walk, hipStream_t s);
+                               const unsigned int *qcount, uint32_t levels, unsigned int *out,
+                               hipStream_t s);
+// ctl[0 .. words) = 0 but for the flags, *counter = 0.
+hipError_t launch_query_begin(const TreeHeader *hdr, unsigned int *ctl, uint32_t words,
+                              uint32_t flags_at, unsigned int init, unsigned long long *counter,
+                              hipStream_t s);
+// lists: those of the last queue (1 for the seeds).
+hipError_t launch_query_decide(const unsigned int *last_count, uint32_t lists,
+                               const unsigned int *qflags, unsigned long long *counter,
+                               unsigned int *walk, hipStream_t s);
 hipError_t launch_pad_records(Rec *raw, const unsigned long long *counter, uint32_t cap,
                               hipStream_t s);
 hipError_t launch_query_finish(const unsigned long long *counter, const unsigned int *tree_err,

@@ -233,242 +233,391 @@ hipError_t launch_traverse(const void *tree, int precision, uint32_t N, uint32_t
 // overlapping pair of leaves lies under exactly one such pair (the children of
 // its lowest common ancestor), and expanding an overlapping node pair into the
 // overlapping pairs of their children reaches each of those leaf pairs exactly
-// once.  One launch per level: a lane takes one queued pair, loads the
-// children's boxes, tests the (up to) four child pairs, emits leaf pairs as
-// records and queues the rest; both appends are aggregated per wave with a
-// ballot and one atomic.
+// once.  A lane takes one pair, loads the children's boxes, tests the (up to)
+// four child pairs, emits leaf pairs as records and keeps the rest to expand.
 
-// Side s of a pair: a leaf stays itself, an inner node is replaced by its two
-// children (kids of the tree).  Loads the boxes of the resulting nodes, and
-// the leaves' object ids unless LINKS is false (FP32: the ids sit in the
-// link array, a second cache line, and are then read only for leaf pairs
-// whose boxes overlap).
-template <int TP, bool LINKS = true>
-__device__ inline bool load_side(const void *tree, const uint2 *kids, uint32_t N, uint32_t x,
-                                 uint32_t ids[2], typename Q<TP>::F lo[2][3],
-                                 typename Q<TP>::F hi[2][3], uint32_t t0[2], uint32_t t1[2],
-                                 uint32_t lk[2], uint32_t &cnt)
+// Lanes below this one in a ballot.
+__device__ inline uint32_t lanes_before(uint64_t all)
 {
-    const uint32_t nodes = 2 * N - 1;
-    uint32_t e;
-    if (x >= nodes)
-        return false;
-    if (x >= N - 1) {
-        ids[0] = x;
-        if (LINKS || TP == CD_FP64) {
-            Q<TP>::load(tree, N, x, lo[0], hi[0], t0[0], t1[0], lk[0], e);
-        } else {
-            Q<TP>::load_box(tree, N, x, lo[0], hi[0], t0[0], t1[0]);
-            lk[0] = 0;
-        }
-        cnt = 1;
-        return true;
-    }
-    uint2 kk = kids[x];
-    if (kk.x >= nodes || kk.y >= nodes)
-        return false;
-    ids[0] = kk.x;
-    ids[1] = kk.y;
-    if (TP == CD_FP64) {   // the links share the record's cache line
-        Q<TP>::load(tree, N, kk.x, lo[0], hi[0], t0[0], t1[0], lk[0], e);
-        Q<TP>::load(tree, N, kk.y, lo[1], hi[1], t0[1], t1[1], lk[1], e);
-        cnt = 2;
-        return true;
-    }
-    // FP32: an inner child's link (a second cache line) is never used, its
-    // children come from kids, so only a leaf child pays for the object id
-    lk[0] = lk[1] = 0;
-    if (LINKS && kk.x >= N - 1)
-        Q<TP>::load(tree, N, kk.x, lo[0], hi[0], t0[0], t1[0], lk[0], e);
-    else
-        Q<TP>::load_box(tree, N, kk.x, lo[0], hi[0], t0[0], t1[0]);
-    if (LINKS && kk.y >= N - 1)
-        Q<TP>::load(tree, N, kk.y, lo[1], hi[1], t0[1], t1[1], lk[1], e);
-    else
-        Q<TP>::load_box(tree, N, kk.y, lo[1], hi[1], t0[1], t1[1]);
-    cnt = 2;
-    return true;
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(all >> 32),
+                                     __builtin_amdgcn_mbcnt_lo((uint32_t)all, 0u));
 }
 
-// One level over the n pairs of `in`, by every workgroup of the grid in turn
-// (block-uniform loop: the block scan needs every thread).  COH: the queue
-// entries are written and read as device-scope atomics, each coherent across
-// the XCDs' separate L2 caches by itself, for a reader in the same launch.
-template <int TP, bool COH = false>
-__device__ inline void expand_level(const void *__restrict__ tree, const uint2 *__restrict__ kids,
-                                    uint32_t N, const uint2 *__restrict__ in, uint32_t n,
-                                    uint2 *__restrict__ outq, unsigned int *n_out,
-                                    uint32_t out_cap, Rec *__restrict__ out,
-                                    unsigned long long capacity, unsigned long long *counter,
-                                    unsigned int *flags, uint32_t *wsum, unsigned int &qbase,
-                                    unsigned long long &rbase)
+// A node in a queue, by its two children instead of its id, so that expanding
+// it needs no look-up of its child pair (a cache line of its own): kind N + g
+// for a node split after leaf g, bit 0 of the kind set if its left child is
+// leaf g (else the inner node g), bit 1 if its right child is leaf g + 1 (else
+// the inner node g + 1); 4 N + j for leaf j.  An FP64 record holds what this
+// takes: link is the left child, and esc, the node that follows the subtree, is
+// a right child and so numbered by its first leaf, the one after the node's
+// last.  FP32 records keep their links in another array; their queues (and
+// those of trees of more than kCodedLeaves leaves) hold ids.
+constexpr uint32_t kCodedLeaves = 0xFFFFFFFFu / 5;
+
+__device__ inline uint32_t node_code(uint32_t N, uint32_t id, uint32_t link, uint32_t esc)
 {
+    const bool left = link >= N - 1;
+    const uint32_t g = link - (left ? N - 1 : 0u), j = esc - (esc >= N - 1 ? N - 1 : 0u),
+                   after = esc == kEnd ? N : j, kind = (left ? 1u : 0u) + (g + 2 == after ? 2u : 0u);
+    return id >= N - 1 ? 4 * N + (id - (N - 1)) : kind * N + g;
+}
+
+// The pairs of one wave, the lanes' (ids, active) in, its child pairs out:
+// push bit 2 ia + ic for a pair to expand, hit for a record.  IN: the pairs
+// come as ids (else codes); OUT: node holds ids (else codes).
+template <int TP, bool IN, bool OUT>
+struct PairTest {
     using F = typename Q<TP>::F;
+    uint32_t node[2][2], t0[2][2], t1[2][2], lk[2][2];
+    uint32_t push, hit;
+
+    // Side s: a leaf stays itself (twice), an inner node is its two children.
+    __device__ void run(const void *__restrict__ tree, const uint2 *__restrict__ kids,
+                        uint32_t N, uint2 pr, bool active, unsigned int *flags)
+    {
+        static_assert(OUT || TP == CD_FP64, "codes come from FP64 records");
 #ifdef CD_COUNTERS
-    constexpr bool kLinks = true;   // the node-visit counts need every leaf's object
+        constexpr bool kLinks = true;   // the node-visit counts need every leaf's object
 #else
-    constexpr bool kLinks = TP == CD_FP64;   // FP32: object ids only for overlapping leaf pairs
+        constexpr bool kLinks = TP == CD_FP64;   // FP32: object ids only for overlapping leaf pairs
 #endif
-    for (uint32_t base = blockIdx.x * blockDim.x; base < n; base += gridDim.x * blockDim.x) {
-        uint32_t k = base + threadIdx.x;
-        bool active = k < n;
-        uint32_t ids[2][2], cnt[2] = {0, 0};
+        const uint32_t nodes = 2 * N - 1;
+        uint32_t x[2] = {pr.x, pr.y}, ids[2][2];
         F lo[2][2][3], hi[2][2][3];
-        uint32_t t0[2][2], t1[2][2], lk[2][2];
-        if (active) {
-            uint2 pr;
-            if (COH) {
-                unsigned long long v =
-                    __hip_atomic_load(reinterpret_cast<const unsigned long long *>(in + k),
-                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                pr = make_uint2((uint32_t)v, (uint32_t)(v >> 32));
-            } else {
-                pr = in[k];
+        bool one[2], ok = true;
+        if (IN) {
+            uint2 kk[2];
+            for (int side = 0; side < 2; ++side) {   // both reads asked for together
+                ok &= x[side] < nodes;
+                one[side] = x[side] >= N - 1;
+                kk[side] = kids[one[side] ? 0u : x[side]];
             }
-            bool ok = load_side<TP, kLinks>(tree, kids, N, pr.x, ids[0], lo[0], hi[0], t0[0],
-                                            t1[0], lk[0], cnt[0]) &&
-                      load_side<TP, kLinks>(tree, kids, N, pr.y, ids[1], lo[1], hi[1], t0[1],
-                                            t1[1], lk[1], cnt[1]);
-            if (!ok) {
-                atomicOr(flags, 2u);
-                active = false;
+            for (int side = 0; side < 2; ++side) {
+                ids[side][0] = one[side] ? x[side] : kk[side].x;
+                ids[side][1] = one[side] ? x[side] : kk[side].y;
+            }
+        } else {
+            for (int side = 0; side < 2; ++side) {
+                one[side] = x[side] >= 4 * N;
+                const uint32_t r = x[side] >= 2 * N ? 1u : 0u, y = x[side] - 2 * N * r,
+                               l = y >= N ? 1u : 0u, g = y - N * l;
+                ids[side][0] = one[side] ? x[side] - 4 * N + (N - 1) : g + (l ? N - 1 : 0u);
+                ids[side][1] = one[side] ? ids[side][0] : g + 1 + (r ? N - 1 : 0u);
             }
         }
-        uint32_t push_mask = 0, hit_mask = 0;
+        for (int side = 0; side < 2; ++side)
+            ok &= (ids[side][0] < nodes) & (ids[side][1] < nodes);
+        if (active && !ok)
+            atomicOr(flags, 2u);
+        active &= ok;
+        uint32_t esc[2][2];
+        for (int side = 0; side < 2; ++side)
+            for (int c = 0; c < 2; ++c) {
+                ids[side][c] = active ? ids[side][c] : 0u;
+                if (kLinks)
+                    Q<TP>::load(tree, N, ids[side][c], lo[side][c], hi[side][c], t0[side][c],
+                                t1[side][c], lk[side][c], esc[side][c]);
+                else
+                    Q<TP>::load_box(tree, N, ids[side][c], lo[side][c], hi[side][c],
+                                    t0[side][c], t1[side][c]);
+            }
+        if (!OUT)   // the four records are asked for before any is waited for
+            asm volatile("" : "+v"(esc[0][0]), "+v"(esc[0][1]), "+v"(esc[1][0]), "+v"(esc[1][1]));
+        for (int side = 0; side < 2; ++side)
+            for (int c = 0; c < 2; ++c)
+                node[side][c] = OUT ? ids[side][c]
+                                    : node_code(N, ids[side][c], lk[side][c], esc[side][c]);
+        const uint32_t first_leaf = OUT ? N - 1 : 4 * N;
+        push = hit = 0;
         for (int ia = 0; ia < 2; ++ia)
             for (int ic = 0; ic < 2; ++ic) {
-                bool ov = active && ia < (int)cnt[0] && ic < (int)cnt[1] &&
-                          time_overlap(t0[0][ia], t1[0][ia], t0[1][ic], t1[1][ic]) &&
-                          space_overlap(lo[0][ia], hi[0][ia], lo[1][ic], hi[1][ic]);
-                bool leaves = ov && ids[0][ia] >= N - 1 && ids[1][ic] >= N - 1;
-                int bit = ia * 2 + ic;
+                // every comparison made, no branches
+                const bool t = (t0[0][ia] < t1[1][ic]) & (t0[1][ic] < t1[0][ia]);
+                bool ov = active & !(ia & (int)one[0]) & !(ic & (int)one[1]) & t;
+                for (int d = 0; d < 3; ++d)
+                    ov &= (lo[0][ia][d] <= hi[1][ic][d]) & (lo[1][ic][d] <= hi[0][ia][d]);
+                const bool leaves =
+                    ov & (node[0][ia] >= first_leaf) & (node[1][ic] >= first_leaf);
+                const uint32_t bit = 1u << (ia * 2 + ic);
                 if (!kLinks && leaves) {
                     const uint2 *links = (const uint2 *)((const Box32 *)tree + (2 * (size_t)N - 1));
-                    lk[0][ia] = links[ids[0][ia]].x;
-                    lk[1][ic] = links[ids[1][ic]].x;
+                    lk[0][ia] = links[node[0][ia]].x;
+                    lk[1][ic] = links[node[1][ic]].x;
                 }
-                if (leaves && lk[0][ia] != lk[1][ic])
-                    hit_mask |= 1u << bit;
-                if (ov && !leaves)
-                    push_mask |= 1u << bit;
+                hit |= (leaves & (lk[0][ia] != lk[1][ic])) ? bit : 0u;
+                push |= (ov & !leaves) ? bit : 0u;
             }
 #ifdef CD_COUNTERS
-        {
-            uint32_t c_tests = 0, c_ll = 0, c_li = 0;
-            for (int ia = 0; ia < 2; ++ia)
-                for (int ic = 0; ic < 2; ++ic) {
-                    if (!(active && ia < (int)cnt[0] && ic < (int)cnt[1]))
-                        continue;
-                    const bool la = ids[0][ia] >= N - 1, lc = ids[1][ic] >= N - 1;
-                    ++c_tests;
-                    c_ll += (la && lc) ? 1u : 0u;
-                    c_li += (la != lc) ? 1u : 0u;
-                    if (la)
-                        ctr_visit(lk[0][ia]);
-                    if (lc)
-                        ctr_visit(lk[1][ic]);
-                }
-            ctr_wave_add(0, c_tests);
-            ctr_wave_add(1, c_ll);
-            ctr_wave_add(2, c_li);
-            ctr_wave_add(3, (uint32_t)__popc(hit_mask));
-            ctr_wave_add(4, active ? 1u : 0u);
-        }
+        uint32_t c_tests = 0, c_ll = 0, c_li = 0;
+        for (int ia = 0; ia < 2; ++ia)
+            for (int ic = 0; ic < 2; ++ic) {
+                if (!active || (ia && one[0]) || (ic && one[1]))
+                    continue;
+                const bool la = node[0][ia] >= first_leaf, lc = node[1][ic] >= first_leaf;
+                ++c_tests;
+                c_ll += (la && lc) ? 1u : 0u;
+                c_li += (la != lc) ? 1u : 0u;
+                if (la)
+                    ctr_visit(lk[0][ia]);
+                if (lc)
+                    ctr_visit(lk[1][ic]);
+            }
+        ctr_wave_add(0, c_tests);
+        ctr_wave_add(1, c_ll);
+        ctr_wave_add(2, c_li);
+        ctr_wave_add(3, (uint32_t)__popc(hit));
+        ctr_wave_add(4, active ? 1u : 0u);
 #endif
-        // one scan packs both counts: pushes in the low 16 bits, hits above
-        uint32_t mine = (uint32_t)__popc(push_mask) | ((uint32_t)__popc(hit_mask) << 16);
-        uint32_t total;
-        uint32_t pre = block_exclusive_scan(mine, wsum, &total);
-        if (threadIdx.x == 0) {
-            qbase = (total & 0xFFFFu) ? atomicAdd(n_out, total & 0xFFFFu) : 0u;
-            rbase = (total >> 16) ? atomicAdd(counter, (unsigned long long)(total >> 16)) : 0ull;
-        }
-        __syncthreads();
-        uint32_t q = qbase + (pre & 0xFFFFu);
-        unsigned long long r = rbase + (pre >> 16);
-        for (int bit = 0; bit < 4; ++bit) {
-            int ia = bit >> 1, ic = bit & 1;
-            if (push_mask & (1u << bit)) {
-                if (q < out_cap)
-                {
-                    if (COH)
-                        __hip_atomic_store(reinterpret_cast<unsigned long long *>(outq + q),
-                                           (unsigned long long)ids[0][ia] |
-                                               ((unsigned long long)ids[1][ic] << 32),
-                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    else
-                        outq[q] = make_uint2(ids[0][ia], ids[1][ic]);
-                }
-                else
-                    atomicOr(flags, 1u);
-                ++q;
-            }
-            if (hit_mask & (1u << bit)) {
-                if (r < capacity) {
-                    uint32_t oa = lk[0][ia], oc = lk[1][ic];
-                    Rec rec;
-                    rec.i = oa < oc ? oa : oc;
-                    rec.j = oa < oc ? oc : oa;
-                    rec.tlo = t0[0][ia] > t0[1][ic] ? t0[0][ia] : t0[1][ic];
-                    rec.thi = t1[0][ia] < t1[1][ic] ? t1[0][ia] : t1[1][ic];
-                    out[r] = rec;
-                }
-                ++r;
-            }
-        }
-        __syncthreads();
     }
-}
 
-template <int TP>
-__global__ __launch_bounds__(1024) void k_expand(const void *__restrict__ tree,
+    __device__ uint2 pair(int bit) const { return make_uint2(node[0][bit >> 1], node[1][bit & 1]); }
+
+    __device__ Rec record(int bit) const
+    {
+        const bool a = (bit & 2) != 0, c = (bit & 1) != 0;
+        const uint32_t oa = a ? lk[0][1] : lk[0][0], oc = c ? lk[1][1] : lk[1][0];
+        const uint32_t a0 = a ? t0[0][1] : t0[0][0], c0 = c ? t0[1][1] : t0[1][0];
+        const uint32_t a1 = a ? t1[0][1] : t1[0][0], c1 = c ? t1[1][1] : t1[1][0];
+        Rec rec;
+        rec.i = oa < oc ? oa : oc;
+        rec.j = oa < oc ? oc : oa;
+        rec.tlo = a0 > c0 ? a0 : c0;
+        rec.thi = a1 < c1 ? a1 : c1;
+        return rec;
+    }
+};
+
+// What a wave holds in LDS: pairs (an expansion of 64 adds up to 256) and
+// records.
+constexpr uint32_t kExpandStack = 576, kExpandRecs = 64;
+constexpr size_t kExpandLds = kExpandStack * sizeof(uint2) + kExpandRecs * sizeof(Rec);
+// Pairs above which a wave sends what it holds to the queue; in deep launches
+// all but 64, and sooner: a wave with that many is far behind the others.
+constexpr uint32_t kExpandKeep = kExpandStack - 256, kExpandKeepDeep = 128;
+// A launch over at most this many pairs goes deep; expansions a wave then makes
+// after its input has run out before it hands what is left to the next launch,
+// which deals it out again.  Measured on 3.2 M pairs over 60.65 M leaves and on
+// 17.5 M over 79.7 M (which first shrink to 175 K a level and then grow to
+// 845 K): 65 536 pairs 291 and 902 us, 131 072 279 and 903, 262 144 222 and
+// 873, 524 288 249 and 1 022; without a limit of expansions 221 and 1 175.
+constexpr uint32_t kExpandDeep = 262144, kExpandTail = 16, kExpandTailLast = 65536;
+
+// One launch over the pairs of `in`, each wave by itself until its workgroup's
+// last appends.
+//
+// Many pairs: one level.  A wave takes strips of 64 pairs and collects their
+// child pairs and records in LDS.  Breadth first the pairs of a strip share
+// nodes, and every level is dealt to the waves anew: depth first from the
+// start, with each wave's stack in LDS, took 2.3 ms where the levels took 1.4
+// (17.5 M pairs over 79.7 M leaves).
+//
+// Few pairs: a launch per level costs more than its work (about 8 us).  Here a
+// wave goes on with its own stack, 64 pairs at a time.
+//
+// Appends: atomics on one address go through the memory side one after another
+// (12 ns each measured: one per wave made every level of 8 192 waves 100 us),
+// so a wave appends some 350 pairs at a time, a workgroup makes one last append
+// of each kind, and a queue is kExpandSubs lists whose counts lie apart, taken
+// in turn.
+//
+// Bound: many pairs by random 64-byte records, four per pair (6.5 pairs per ns:
+// 2 TB/s of 64-byte pieces, each in a 128-byte line of its own half the time);
+// few by the two dependent reads of an expansion (about 2 us).  Against one
+// launch per level with queues of ids: 4 240 seeds over 75 000 leaves 85 -> 37
+// us, 495 K over 60.65 M 478 -> 300, 1.6 M over 79.7 M 1 395 -> 1 080; FP32,
+// 77 K over 11.1 M 195 -> 77, 4 M over 79.7 M 3 222 -> 2 930.
+template <int TP, bool IN, bool OUT>
+__global__ __launch_bounds__(1024)
+__attribute__((amdgpu_waves_per_eu(TP == CD_FP64 ? 5 : 7))) void k_expand(const void *__restrict__ tree,
                                                 const uint2 *__restrict__ kids, uint32_t N,
                                                 const uint2 *__restrict__ in,
                                                 const unsigned int *n_in, uint32_t in_cap,
                                                 uint2 *__restrict__ outq, unsigned int *n_out,
-                                                uint32_t out_cap, Rec *__restrict__ out,
+                                                uint32_t sub_cap, Rec *__restrict__ out,
                                                 unsigned long long capacity,
                                                 unsigned long long *counter, unsigned int *flags,
-                                                int gated)
+                                                int first, int last)
 {
-    __shared__ uint32_t wsum[64];
-    __shared__ unsigned int qbase;
+    extern __shared__ uint4 held[];
+    __shared__ uint32_t stop, npair[16], nrec[16], qbase;
     __shared__ unsigned long long rbase;
-    // gated: a set flag (queue overflow, bad node, the traversal handed to the
-    // per-leaf walk, or an earlier level found its queue empty) ends the
+    // a set flag (queue overflow, bad node, the traversal handed to the
+    // per-leaf walk, or an earlier launch found its queue empty) ends the
     // node-pair levels
-    if (gated && *flags)
+    if (threadIdx.x == 0)
+        stop = *flags;
+    // the seeds are one list, a queue is kExpandSubs of them: pair k of all is
+    // pair k - start[q] of the last list q that starts at or before it
+    uint32_t start[kExpandSubs], n = 0;
+#pragma unroll
+    for (int q = 0; q < kExpandSubs; ++q) {
+        start[q] = n;
+        const uint32_t c = first ? (q ? 0u : *n_in) : n_in[q * kExpandSubStride];
+        n += c < in_cap ? c : in_cap;
+    }
+    __syncthreads();
+    if (stop)
         return;
-    uint32_t n = *n_in;
-    n = n < in_cap ? n : in_cap;
     if (n == 0) {
         // every pair has been expanded: flag 8 tells the host (and the gate)
         if (blockIdx.x == 0 && threadIdx.x == 0)
             atomicOr(flags, 8u);
         return;
     }
-    expand_level<TP>(tree, kids, N, in, n, outq, n_out, out_cap, out, capacity, counter, flags,
-                     wsum, qbase, rbase);
+    const bool deep = IN == OUT && !first && (last || n <= kExpandDeep);
+    const uint32_t lane = threadIdx.x & 63u, wv = threadIdx.x >> 6, per = blockDim.x >> 6;
+    Rec *const recs = reinterpret_cast<Rec *>(held) + wv * kExpandRecs;
+    uint2 *const st = reinterpret_cast<uint2 *>(reinterpret_cast<Rec *>(held) + per * kExpandRecs) +
+                      wv * kExpandStack;
+    // input in strips of `take` pairs, dealt to the waves in turn; a short
+    // input in short strips, so that more waves share its latency
+    const uint32_t waves = gridDim.x * per, share = (n + waves - 1) / waves;
+    const uint32_t take = !deep || share > 64 ? 64u : share < 16 ? 16u : share;
+    uint64_t strip = (uint64_t)(blockIdx.x * per + wv) * take;
+    uint32_t done = 0;        // pairs taken of the strip
+    uint32_t cnt = 0, rc = 0, left = last ? kExpandTailLast : kExpandTail;
+    const uint32_t keep = !deep || last ? kExpandKeep : kExpandKeepDeep;
+    uint32_t sub = (blockIdx.x * per + wv) % kExpandSubs;   // list of the wave's next append
+    auto queue = [&](uint32_t from, uint32_t list, uint32_t q) {   // the pairs held from `from` on
+        uint2 *const to = outq + (size_t)list * sub_cap;
+        for (uint32_t k = from + lane; k < cnt; k += 64) {
+            if (q + (k - from) < sub_cap)
+                to[q + (k - from)] = st[k];
+            else
+                atomicOr(flags, 1u);
+        }
+        cnt = from;
+    };
+    auto records = [&](unsigned long long r) {   // those held
+        if (lane < rc && r + lane < capacity)
+            out[r + lane] = recs[lane];
+        rc = 0;
+    };
+    for (;;) {
+        const uint32_t m = !deep ? 0u : cnt < 64 ? cnt : 64u;   // from the wave's own pairs
+        uint32_t f = 0;                                         // from the input
+        if (strip < n) {
+            const uint32_t rest = (uint32_t)(n - strip < take ? n - strip : take) - done;
+            f = rest < 64 - m ? rest : 64 - m;
+        } else {
+            if (!deep || cnt == 0 || left == 0)
+                break;
+            --left;
+        }
+        cnt -= m;
+        uint2 pr = make_uint2(0, 0);
+        if (lane < m)
+            pr = st[cnt + lane];
+        else if (lane < m + f) {
+            const uint32_t k = (uint32_t)strip + done + (lane - m);
+            size_t at = k;
+#pragma unroll
+            for (uint32_t q = 1; q < kExpandSubs; ++q)
+                at = k >= start[q] ? k - start[q] + (size_t)q * in_cap : at;
+            pr = in[at];
+        }
+        asm volatile("" ::: "memory");
+        if (strip < n) {
+            done += f;
+            if (done == take || strip + done == n) {
+                strip += (uint64_t)waves * take;
+                done = 0;
+            }
+        }
+        PairTest<TP, IN, OUT> P;
+        P.run(tree, kids, N, pr, lane < m + f, flags);
+        // records, one a lane at a time
+        for (;;) {
+            const uint64_t some = __ballot(P.hit != 0);
+            if (some == 0)
+                break;
+            const uint32_t total = (uint32_t)__popcll(some);
+            if (rc + total > kExpandRecs) {   // those held, at once
+                uint32_t r0 = 0, r1 = 0;
+                if (lane == 0) {
+                    const unsigned long long r = atomicAdd(
+                        counter, (unsigned long long)__builtin_amdgcn_readfirstlane(rc));
+                    r0 = (uint32_t)r;
+                    r1 = (uint32_t)(r >> 32);
+                }
+                records(((unsigned long long)__builtin_amdgcn_readfirstlane(r1) << 32) |
+                        __builtin_amdgcn_readfirstlane(r0));
+            }
+            if (P.hit != 0) {
+                recs[rc + lanes_before(some)] = P.record(__ffs(P.hit) - 1);
+                P.hit &= P.hit - 1;
+            }
+            rc += total;
+        }
+        // a lane's child pairs side by side: they share children, and so records
+        uint32_t at = cnt;
+#pragma unroll
+        for (int bit = 0; bit < 4; ++bit) {
+            const uint64_t all = __ballot((P.push & (1u << bit)) != 0);
+            at += lanes_before(all);
+            cnt += (uint32_t)__popcll(all);
+        }
+#pragma unroll
+        for (int bit = 0; bit < 4; ++bit)
+            if (P.push & (1u << bit))
+                st[at++] = P.pair(bit);
+        asm volatile("" ::: "memory");
+        if (cnt > keep) {
+            const uint32_t from = deep ? 64u : 0u;
+            uint32_t q = 0;
+            if (lane == 0)
+                q = atomicAdd(n_out + sub * kExpandSubStride,
+                              __builtin_amdgcn_readfirstlane(cnt - from));
+            queue(from, sub, __builtin_amdgcn_readfirstlane(q));
+            sub = (sub + 1) % kExpandSubs;
+        }
+    }
+    if (lane == 0) {
+        npair[wv] = cnt;
+        nrec[wv] = rc;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t p = 0, r = 0;
+        for (uint32_t k = 0; k < per; ++k) {
+            p += npair[k];
+            r += nrec[k];
+        }
+        qbase = p ? atomicAdd(n_out + blockIdx.x % kExpandSubs * kExpandSubStride, p) : 0u;
+        rbase = r ? atomicAdd(counter, (unsigned long long)r) : 0ull;
+    }
+    __syncthreads();
+    uint32_t q = qbase;
+    unsigned long long r = rbase;
+    for (uint32_t k = 0; k < wv; ++k) {
+        q += npair[k];
+        r += nrec[k];
+    }
+    queue(0, blockIdx.x % kExpandSubs, q);
+    records(r);
 }
 
 hipError_t launch_expand(const void *tree, const uint2 *kids, int precision, uint32_t N,
                          const uint2 *in, const unsigned int *n_in, uint32_t in_cap, uint2 *outq,
-                         unsigned int *n_out, uint32_t out_cap, Rec *out,
+                         unsigned int *n_out, uint32_t sub_cap, Rec *out,
                          unsigned long long capacity, unsigned long long *counter,
-                         unsigned int *flags, int gated, uint32_t blocks, uint32_t threads,
-                         hipStream_t s)
+                         unsigned int *flags, bool first, bool last, uint32_t blocks,
+                         uint32_t threads, hipStream_t s)
 {
     if (N <= 1)
         return hipSuccess;
-    if (precision == CD_FP64)
-        k_expand<CD_FP64><<<blocks, threads, 0, s>>>(tree, kids, N, in, n_in, in_cap, outq, n_out,
-                                                     out_cap, out, capacity, counter, flags,
-                                                     gated);
-    else
-        k_expand<CD_FP32><<<blocks, threads, 0, s>>>(tree, kids, N, in, n_in, in_cap, outq, n_out,
-                                                     out_cap, out, capacity, counter, flags,
-                                                     gated);
-    return hipGetLastError();
+    const size_t lds = threads / 64 * kExpandLds;
+    auto run = [&](auto kernel) {
+        kernel<<<blocks, threads, lds, s>>>(tree, kids, N, in, n_in, in_cap, outq, n_out, sub_cap,
+                                            out, capacity, counter, flags, first ? 1 : 0, last ? 1 : 0);
+        return hipGetLastError();
+    };
+    if (precision == CD_FP32)
+        return run(k_expand<CD_FP32, true, true>);
+    if (N > kCodedLeaves)
+        return run(k_expand<CD_FP64, true, true>);
+    // the seeds are ids, every later queue codes
+    return first ? run(k_expand<CD_FP64, true, false>) : run(k_expand<CD_FP64, false, false>);
 }
 
 // ---- every level in one launch ----------------------------------------------------------------
@@ -495,6 +644,63 @@ constexpr long long kGridWaitTicks = 200000000ll;   // 2 s
 __device__ inline unsigned int load_dev(const unsigned int *p)
 {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// One level over the n pairs of `in`, by every workgroup of the grid in turn
+// (block-uniform loop: the block scan needs every thread).  The queue entries
+// are written and read as device-scope atomics, each coherent across the XCDs'
+// separate L2 caches by itself, for a reader in the same launch.
+template <int TP>
+__device__ inline void expand_level(const void *__restrict__ tree, const uint2 *__restrict__ kids,
+                                    uint32_t N, const uint2 *__restrict__ in, uint32_t n,
+                                    uint2 *__restrict__ outq, unsigned int *n_out,
+                                    uint32_t out_cap, Rec *__restrict__ out,
+                                    unsigned long long capacity, unsigned long long *counter,
+                                    unsigned int *flags, uint32_t *wsum, unsigned int &qbase,
+                                    unsigned long long &rbase)
+{
+    for (uint32_t base = blockIdx.x * blockDim.x; base < n; base += gridDim.x * blockDim.x) {
+        const uint32_t k = base + threadIdx.x;
+        uint2 pr = make_uint2(0, 0);
+        if (k < n) {
+            const unsigned long long v =
+                __hip_atomic_load(reinterpret_cast<const unsigned long long *>(in + k),
+                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            pr = make_uint2((uint32_t)v, (uint32_t)(v >> 32));
+        }
+        PairTest<TP, true, true> P;
+        P.run(tree, kids, N, pr, k < n, flags);
+        // one scan packs both counts: pushes in the low 16 bits, hits above
+        uint32_t mine = (uint32_t)__popc(P.push) | ((uint32_t)__popc(P.hit) << 16);
+        uint32_t total;
+        uint32_t pre = block_exclusive_scan(mine, wsum, &total);
+        if (threadIdx.x == 0) {
+            qbase = (total & 0xFFFFu) ? atomicAdd(n_out, total & 0xFFFFu) : 0u;
+            rbase = (total >> 16) ? atomicAdd(counter, (unsigned long long)(total >> 16)) : 0ull;
+        }
+        __syncthreads();
+        uint32_t q = qbase + (pre & 0xFFFFu);
+        unsigned long long r = rbase + (pre >> 16);
+#pragma unroll
+        for (int bit = 0; bit < 4; ++bit) {
+            if (P.push & (1u << bit)) {
+                if (q < out_cap)
+                    __hip_atomic_store(reinterpret_cast<unsigned long long *>(outq + q),
+                                       (unsigned long long)P.pair(bit).x |
+                                           ((unsigned long long)P.pair(bit).y << 32),
+                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                else
+                    atomicOr(flags, 1u);
+                ++q;
+            }
+            if (P.hit & (1u << bit)) {
+                if (r < capacity)
+                    out[r] = P.record(bit);
+                ++r;
+            }
+        }
+        __syncthreads();
+    }
 }
 
 template <int TP>
@@ -525,7 +731,7 @@ __global__ __launch_bounds__(1024) void k_expand_all(const void *__restrict__ tr
             return;
         }
         uint2 *outq = (lev & 1) ? qb : qa;
-        expand_level<TP, true>(tree, kids, N, in, n, outq, qcount + lev + 1, qcap, out,
+        expand_level<TP>(tree, kids, N, in, n, outq, qcount + lev + 1, qcap, out,
                                capacity, counter, flags, wsum, qbase, rbase);
         // every wave's queue stores and count updates have completed (each
         // is coherent by itself) before its workgroup arrives
@@ -610,21 +816,31 @@ hipError_t launch_expand_all(const void *tree, const uint2 *kids, int precision,
 
 // ---- device-side control of the query (no host reads) -----------------------------------------
 
-// Before the node-pair levels: a build error or lost seeds hand the whole
-// traversal to the per-leaf walk.
-__global__ void k_query_begin(const TreeHeader *hdr, unsigned int *qflags)
+// Before the node-pair levels: the control words, the flags (init, or the whole
+// traversal handed to the per-leaf walk after a build error or lost seeds) and
+// the record count.
+__global__ __launch_bounds__(1024) void k_query_begin(const TreeHeader *hdr, unsigned int *ctl,
+                                                      uint32_t words, uint32_t flags_at,
+                                                      unsigned int init,
+                                                      unsigned long long *counter)
 {
-    if (hdr->err || hdr->seed_overflow)
-        atomicOr(qflags, 4u);
+    const unsigned int f = init | (hdr->err || hdr->seed_overflow ? 4u : 0u);
+    for (uint32_t k = threadIdx.x; k < words; k += blockDim.x)
+        ctl[k] = k == flags_at ? f : 0u;
+    if (threadIdx.x == 0)
+        *counter = 0ull;
 }
 
 // After the last level: the per-leaf walk runs (from a cleared counter) if
 // an overflow, bad-node or handover flag is set (bits 1, 2, 4; bit 8 only
-// marks a drained queue) or the last queue is not empty.
-__global__ void k_query_decide(const unsigned int *last_count, const unsigned int *qflags,
-                               unsigned long long *counter, unsigned int *walk)
+// marks a drained queue) or one of the last queue's `lists` lists is not empty.
+__global__ void k_query_decide(const unsigned int *last_count, uint32_t lists,
+                               const unsigned int *qflags, unsigned long long *counter,
+                               unsigned int *walk)
 {
-    unsigned int w = ((*qflags & 7u) != 0 || *last_count != 0) ? 1u : 0u;
+    unsigned int w = (*qflags & 7u) != 0 ? 1u : 0u;
+    for (uint32_t q = 0; q < lists; ++q)
+        w |= last_count[q * kExpandSubStride] != 0 ? 1u : 0u;
     if (w)
         *counter = 0ull;
     *walk = w;
@@ -665,33 +881,55 @@ __global__ void k_query_finish(const unsigned long long *counter, const unsigned
     *status_out = st;
 }
 
-// The record count and the tree's error word side by side, for one read.
-__global__ void k_query_status(const unsigned long long *counter, const unsigned int *tree_err,
-                               unsigned int *out)
+// Side by side, for one read: the record count, the tree's error word and the
+// last of the queues 1 .. levels that held pairs (0: none did).
+__global__ __launch_bounds__(512) void k_query_status(const unsigned long long *counter,
+                                                      const unsigned int *tree_err,
+                                                      const unsigned int *qcount, uint32_t levels,
+                                                      unsigned int *out)
 {
-    unsigned long long c = *counter;
-    out[0] = (unsigned int)c;
-    out[1] = (unsigned int)(c >> 32);
-    out[2] = *tree_err;
+    __shared__ unsigned int last;
+    if (threadIdx.x == 0)
+        last = 0;
+    __syncthreads();
+    const uint32_t l = threadIdx.x + 1;
+    unsigned int any = 0;
+    for (uint32_t q = 0; q < kExpandSubs && l <= levels; ++q)
+        any |= qcount[q * kExpandSubStride + l];
+    if (any)
+        atomicMax(&last, l);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const unsigned long long c = *counter;
+        out[0] = (unsigned int)c;
+        out[1] = (unsigned int)(c >> 32);
+        out[2] = *tree_err;
+        out[3] = last;
+    }
 }
 
 hipError_t launch_query_status(const unsigned long long *counter, const unsigned int *tree_err,
-                               unsigned int *out, hipStream_t s)
+                               const unsigned int *qcount, uint32_t levels, unsigned int *out,
+                               hipStream_t s)
 {
-    k_query_status<<<1, 1, 0, s>>>(counter, tree_err, out);
+    static_assert(kExpandMaxLevels <= 512, "one lane per level");
+    k_query_status<<<1, 512, 0, s>>>(counter, tree_err, qcount, levels, out);
     return hipGetLastError();
 }
 
-hipError_t launch_query_begin(const TreeHeader *hdr, unsigned int *qflags, hipStream_t s)
+hipError_t launch_query_begin(const TreeHeader *hdr, unsigned int *ctl, uint32_t words,
+                              uint32_t flags_at, unsigned int init, unsigned long long *counter,
+                              hipStream_t s)
 {
-    k_query_begin<<<1, 1, 0, s>>>(hdr, qflags);
+    k_query_begin<<<1, 1024, 0, s>>>(hdr, ctl, words, flags_at, init, counter);
     return hipGetLastError();
 }
 
-hipError_t launch_query_decide(const unsigned int *last_count, const unsigned int *qflags,
-                               unsigned long long *counter, unsigned int *walk, hipStream_t s)
+hipError_t launch_query_decide(const unsigned int *last_count, uint32_t lists,
+                               const unsigned int *qflags, unsigned long long *counter,
+                               unsigned int *walk, hipStream_t s)
 {
-    k_query_decide<<<1, 1, 0, s>>>(last_count, qflags, counter, walk);
+    k_query_decide<<<1, 1, 0, s>>>(last_count, lists, qflags, counter, walk);
     return hipGetLastError();
 }
 

@@ -243,3 +243,34 @@ def test_slab_tuner_keeps_the_record_list(tmp_path):
                                      path=path)
     assert hit and again == best
     say("slab tuned", best)
+
+
+@pytest.mark.parametrize("prec", [cd.CD_FP64, cd.CD_FP32])
+@pytest.mark.parametrize("n,K,km", [(2, 1, 5000.0), (300, 7, 3000.0), (1500, 40, 800.0)])
+def test_node_pair_launches_of_dense_boxes(n, K, km, prec):
+    """Boxes inflated until most pairs of a slab's neighbours overlap, on few
+    waves: their stacks are cut, their records fill the buffers, launches hand
+    pairs on, and the last launch of the device-count query runs what is left.
+    The list equals the per-leaf walk's in every shape."""
+    need_gpu()
+    say("dense boxes, n", n, "K", K, "km", km, "precision", prec)
+    rng = np.random.default_rng(n)
+    el = cd.soa(catalog.leo_mix(rng, n))
+    p = cd.params_struct(1.0, catalog.MU_EARTH, km, 2 * K - 1, 2)
+    bp = cd.BroadPhase(n, p, box_precision=prec, tree_precision=prec, capacity=1 << 22)
+    bp.build(el)
+    cd.cd_set_tuning({"mode": 1})
+    try:
+        ref = bp.query().cpu().numpy()
+        say("  records", len(ref))
+        for tun in (None, {"expand_blocks": 64, "expand_threads": 64},
+                    {"expand_blocks": 64, "expand_threads": 1024}):
+            cd.cd_set_tuning(tun)
+            assert np.array_equal(bp.query().cpu().numpy(), ref), tun
+    finally:
+        cd.cd_set_tuning(None)
+    cap = max(len(ref), 1)
+    for tun in ({"max_levels": 2, "expand_blocks": 64, "expand_threads": 64},
+                {"max_levels": 3}, {"max_levels": 40, "expand_blocks": 64, "expand_threads": 64}):
+        got, c, s = _async(bp, cap, tun)
+        assert s == 0 and np.array_equal(got, ref), tun
