@@ -1077,9 +1077,13 @@ int cd_query_pairs(const cd_tree *tree, cd_pair *out, int64_t capacity, int64_t 
                         CD_HIP(launch_medium_canon(w.raw, w.alt, plan, w.flags, w.pos, w.scan,
                                                    (Rec *)out, s, g, w.ctl + kCtlCanon, 1u));
                     } else {
-                        CD_HIP(launch_small_canon_gated(w.raw, w.counter, w.qflags, err,
-                                                        (uint32_t)capacity, (Rec *)out,
-                                                        w.ctl + kCtlCanon, s));
+                        const uint32_t limit = (uint32_t)(capacity < kSmallCanon ? capacity
+                                                                                 : kSmallCanon);
+                        if (limit) {
+                            const SmallCount g{w.counter, w.qflags, err, limit};
+                            CD_HIP(launch_small_canon(w.raw, limit, w.alt, (Rec *)out,
+                                                      w.ctl + kCtlCanon, s, g, 1u));
+                        }
                     }
                     try_canon = false;
                 }
@@ -1141,7 +1145,7 @@ int cd_query_pairs(const cd_tree *tree, cd_pair *out, int64_t capacity, int64_t 
     {
         Stage st("canon", s);
         if (count <= (uint32_t)kSmallCanon) {
-            CD_HIP(launch_small_canon(w.raw, count, (Rec *)out, w.pos + count, s));
+            CD_HIP(launch_small_canon(w.raw, count, w.alt, (Rec *)out, w.pos + count, s));
         } else if (count <= (uint32_t)kMediumCanon) {
             CD_HIP(launch_medium_canon(w.raw, w.alt, count, w.flags, w.pos, w.scan, (Rec *)out,
                                        s));
@@ -1229,9 +1233,12 @@ int cd_query_pairs_async(const cd_tree *tree, cd_pair *out, int64_t capacity,
     }
     {
         Stage st("canon", s);
-        CD_HIP(launch_pad_records(w.raw, w.counter, cap, s));
-        if (cap <= (uint32_t)kSmallCanon) {
-            CD_HIP(launch_small_canon(w.raw, cap, (Rec *)out, w.pos + cap, s));
+        const bool padded = cap > (uint32_t)kSmallCanon;
+        if (padded)
+            CD_HIP(launch_pad_records(w.raw, w.counter, cap, s));
+        if (!padded) {
+            const SmallCount g{w.counter, nullptr, nullptr, cap};
+            CD_HIP(launch_small_canon(w.raw, cap, w.alt, (Rec *)out, w.pos + cap, s, g));
         } else if (cap <= (uint32_t)kMediumCanon) {
             CD_HIP(launch_medium_canon(w.raw, w.alt, cap, w.flags, w.pos, w.scan, (Rec *)out,
                                        s));
@@ -1241,7 +1248,8 @@ int cd_query_pairs_async(const cd_tree *tree, cd_pair *out, int64_t capacity,
             CD_HIP(radix_sort16(SORT_REC, w.raw, w.alt, cap, plan, w.radix, &res, s));
             CD_HIP(launch_unique((const Rec *)res, cap, w.flags, w.pos, w.scan, (Rec *)out, s));
         }
-        CD_HIP(launch_query_finish(w.counter, err, w.pos + cap, cap, count_dev, status_dev, s));
+        CD_HIP(launch_query_finish(w.counter, err, w.pos + cap, cap, padded, count_dev,
+                                   status_dev, s));
     }
     return debug_sync((hipStream_t)stream, "cd_query_pairs_async", nullptr, status_dev);
 }
@@ -1496,7 +1504,7 @@ int cd_refine_records(const cd_elements *el, const cd_params *p, uint32_t delta_
     {
         Stage st("refine_canon", s);
         if (nleaf <= (uint32_t)kSmallCanon) {
-            CD_HIP(launch_small_canon(w.raw, nleaf, (Rec *)out, w.pos + nleaf, s));
+            CD_HIP(launch_small_canon(w.raw, nleaf, w.alt, (Rec *)out, w.pos + nleaf, s));
         } else if (nleaf <= (uint32_t)kMediumCanon) {
             CD_HIP(launch_medium_canon(w.raw, w.alt, nleaf, w.flags, w.pos, w.scan, (Rec *)out,
                                        s));
@@ -1679,7 +1687,7 @@ int cd_canonical_records(const cd_pair *in, int64_t count, uint32_t horizon_tick
     layout_records(ws, ws_bytes, count, &w);
     uint32_t m = (uint32_t)count;
     if (m <= (uint32_t)kSmallCanon) {
-        CD_HIP(launch_small_canon((const Rec *)in, m, (Rec *)out, w.pos + m, s));
+        CD_HIP(launch_small_canon((const Rec *)in, m, w.alt, (Rec *)out, w.pos + m, s));
     } else if (m <= (uint32_t)kMediumCanon) {
         CD_HIP(hipMemcpyAsync(w.raw, in, (size_t)m * sizeof(Rec), hipMemcpyDeviceToDevice, s));
         CD_HIP(launch_medium_canon(w.raw, w.alt, m, w.flags, w.pos, w.scan, (Rec *)out, s));

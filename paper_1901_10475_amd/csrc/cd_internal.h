@@ -654,8 +654,9 @@ hipError_t launch_query_decide(const unsigned int *last_count, uint32_t lists,
 hipError_t launch_pad_records(Rec *raw, const unsigned long long *counter, uint32_t cap,
                               hipStream_t s);
 hipError_t launch_query_finish(const unsigned long long *counter, const unsigned int *tree_err,
-                               const uint32_t *uniq, uint32_t cap, unsigned long long *count_out,
-                               unsigned int *status_out, hipStream_t s);
+                               const uint32_t *uniq, uint32_t cap, bool padded,
+                               unsigned long long *count_out, unsigned int *status_out,
+                               hipStream_t s);
 // bulk interval refinement (items {record, first instant, last instant, 0})
 hipError_t launch_refine_seed(const cd_pair *pairs, uint32_t count, uint32_t start, uint32_t T,
                               uint32_t delta, uint4 *items, hipStream_t s);
@@ -685,23 +686,38 @@ hipError_t launch_gather_elements(const cd_elements &el, const uint32_t *ids, ui
                                   double *out, hipStream_t s);
 hipError_t launch_remap_records(const cd_pair *in, uint32_t count, const uint32_t *ids,
                                 uint32_t nids, cd_pair *out, hipStream_t s);
-// The canonical list of at most kSmallCanon records in one workgroup (LDS
-// radix sort + repeat removal); *total = records written.
+// A small list's record count where it is still on the device (counter set):
+// with qflags, valid if the node-pair levels drained (*qflags == 8), the tree
+// has no error bits and the count is at most limit (the kernels do nothing
+// otherwise); without, the first limit records.
 constexpr int kSmallCanon = 4096;
-hipError_t launch_small_canon(const Rec *in, uint32_t count, Rec *out, uint32_t *total,
-                              hipStream_t s);
-// The same with the count still on the device: runs only if the node-pair
-// levels drained (*qflags == 8), *tree_err == 0 and *counter <= min(capacity,
-// kSmallCanon); then *done = records written + 1 (else *done is untouched).
-hipError_t launch_small_canon_gated(const Rec *in, const unsigned long long *counter,
-                                    const unsigned int *qflags, const unsigned int *tree_err,
-                                    uint32_t capacity, Rec *out, unsigned int *done,
-                                    hipStream_t s);
-// kSmallCanon < count <= kMediumCanon: tiles sorted in LDS, merged pairwise,
-// then repeats removed (launch_unique; total at pos[count]).  a holds the
+struct SmallCount {
+    const unsigned long long *counter;
+    const unsigned int *qflags, *tree_err;
+    uint32_t limit;
+    __device__ bool get(uint32_t host, uint32_t &count) const
+    {
+        count = host;
+        if (!counter)
+            return true;
+        const unsigned long long c = *counter;
+        if (qflags && (*qflags != 8u || *tree_err != 0u || c > limit))
+            return false;
+        count = c < limit ? (uint32_t)c : limit;
+        return true;
+    }
+};
+// The canonical list of 1 .. kSmallCanon records (count, or g.limit == count of
+// them at most): sorted into tmp (count places), *total = records written to
+// out + bias.
+hipError_t launch_small_canon(const Rec *in, uint32_t count, Rec *tmp, Rec *out,
+                              unsigned int *total, hipStream_t s, const SmallCount &g = {},
+                              uint32_t bias = 0);
+// kSmallCanon < count <= kMediumCanon: short runs sorted, merged eight at a
+// time, then repeats removed (launch_unique; total at pos[count]).  a holds the
 // records and is overwritten; b is scratch of count records.  Up to 2^18
-// records six merge passes cost less than the radix path's ten digit passes
-// (three launches each): 69 589 records took 0.72 ms by radix.
+// records three merge passes cost less than the radix path's ten digit passes
+// (three launches each): 180 K records take 0.15 ms, 69 589 took 0.72 by radix.
 constexpr int kMediumCanon = 1 << 18;
 // A record count read on the device when the kernels run, for lists
 // enqueued before the host knows it: valid when the node-pair levels drained

@@ -862,9 +862,10 @@ __global__ void k_pad_records(Rec *raw, const unsigned long long *counter, uint3
 
 // Result words: count (records written, or records found when they exceed the
 // capacity) and status bits (1 capacity exceeded, 2 tree inconsistent).
+// padded: the list was formed over all cap slots, the unused ones one filler.
 __global__ void k_query_finish(const unsigned long long *counter, const unsigned int *tree_err,
-                               const uint32_t *uniq, uint32_t cap, unsigned long long *count_out,
-                               unsigned int *status_out)
+                               const uint32_t *uniq, uint32_t cap, int padded,
+                               unsigned long long *count_out, unsigned int *status_out)
 {
     unsigned long long c = *counter;
     unsigned int st = 0;
@@ -876,7 +877,7 @@ __global__ void k_query_finish(const unsigned long long *counter, const unsigned
     if (c > cap)
         n = c;
     else if (c > 0)
-        n = (unsigned long long)*uniq - (c < cap ? 1ull : 0ull);
+        n = (unsigned long long)*uniq - (padded && c < cap ? 1ull : 0ull);
     *count_out = n;
     *status_out = st;
 }
@@ -943,26 +944,13 @@ hipError_t launch_pad_records(Rec *raw, const unsigned long long *counter, uint3
 }
 
 hipError_t launch_query_finish(const unsigned long long *counter, const unsigned int *tree_err,
-                               const uint32_t *uniq, uint32_t cap, unsigned long long *count_out,
-                               unsigned int *status_out, hipStream_t s)
+                               const uint32_t *uniq, uint32_t cap, bool padded,
+                               unsigned long long *count_out, unsigned int *status_out,
+                               hipStream_t s)
 {
-    k_query_finish<<<1, 1, 0, s>>>(counter, tree_err, uniq, cap, count_out, status_out);
+    k_query_finish<<<1, 1, 0, s>>>(counter, tree_err, uniq, cap, padded ? 1 : 0, count_out,
+                                   status_out);
     return hipGetLastError();
-}
-
-// Small lists (count <= kSmallCanon) in one workgroup: a stable LSD radix
-// sort on the full (i, j, t_lo, t_hi) order, then repeat flags, one block
-// scan and the scatter.  The order and the count equal the radix path's; one
-// launch instead of a pass triple per digit.
-__device__ inline bool rec_less(const Rec &a, const Rec &b)
-{
-    if (a.i != b.i)
-        return a.i < b.i;
-    if (a.j != b.j)
-        return a.j < b.j;
-    if (a.tlo != b.tlo)
-        return a.tlo < b.tlo;
-    return a.thi < b.thi;
 }
 
 __device__ inline bool rec_eq(const Rec &a, const Rec &b)
@@ -972,196 +960,115 @@ __device__ inline bool rec_eq(const Rec &a, const Rec &b)
 
 constexpr int kRecPer = kSmallCanon / 1024;   // records per lane of a 1 024-lane workgroup
 
-struct RecSortLds {
-    Rec xch[kSmallCanon];
-    uint32_t cnt[16 * 257];   // per (wave, digit), rows of 257 words
-    uint32_t wsum[33];
-    unsigned int fmax[4];     // largest value of each field
-};
-
-__device__ inline uint32_t rec_field(const Rec &r, uint32_t f)
+// A record as two words in canonical order.
+__device__ inline ulonglong2 rec_key(const Rec &r)
 {
-    return f == 0 ? r.thi : f == 1 ? r.tlo : f == 2 ? r.j : r.i;
+    return make_ulonglong2((unsigned long long)r.i << 32 | r.j,
+                           (unsigned long long)r.tlo << 32 | r.thi);
 }
 
-// Stable LSD radix sort of the m <= kSmallCanon records a 1 024-lane
-// workgroup holds kRecPer per lane (item q of lane `lane` in wave w at place
-// w * 64 * kRecPer + q * 64 + lane).  Fields from the least significant
-// (t_hi) to the most (i), 8-bit digits, each field only over the bits its
-// largest value in this list uses.  A digit's rank: the lanes holding it
-// found by ballots, a per-(wave, digit) counter, a digit-major scan of the
-// counters.  On return the sorted records are S.xch[0 .. m).
-__device__ inline void lds_radix_rec(Rec (&x)[kRecPer], uint32_t m, RecSortLds &S)
+// Short runs of records are sorted by brute force over the chip: a record's
+// place is the number of records of its run before it (equal ones in input
+// order).  kRankPer records per workgroup, each compared by kRankSlices lanes
+// with the run's records in turn, a tile of them in LDS at a time; the lanes of
+// a wave read 128 consecutive bytes (no bank conflicts).  A list of up to
+// kSmallCanon records is one run, and one workgroup then drops its repeats.
+// Bound: latency (the 10 M comparisons of 3 258 records take 3 us of 12).
+// Against one workgroup's LDS radix sort, 8 to 10 digit passes of 4 to 6 us
+// each: a few hundred records 41 -> 7 us, 3 258 66 -> 19, both with the repeats.
+constexpr uint32_t kRankThreads = 256, kRankPer = 8, kRankSlices = kRankThreads / kRankPer,
+                   kRankTile = 1024;
+
+// Run blockIdx.y: the records [y width, (y + 1) width) of the list.
+template <class Count>
+__global__ __launch_bounds__(kRankThreads) void k_rank_runs(const Rec *__restrict__ list,
+                                                            uint32_t host, Count g,
+                                                            uint32_t width,
+                                                            Rec *__restrict__ runs)
 {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const uint32_t p0 = (uint32_t)w * 64 * kRecPer + lane;
-    const uint64_t lt = lanemask_lt();
-    if (threadIdx.x < 4)
-        S.fmax[threadIdx.x] = 0;
-    __syncthreads();
-    {
-        uint32_t mx[4] = {0, 0, 0, 0};
-#pragma unroll
-        for (int q = 0; q < kRecPer; ++q)
-            if (p0 + q * 64 < m)
-                for (uint32_t f = 0; f < 4; ++f)
-                    mx[f] = max(mx[f], rec_field(x[q], f));
-        for (uint32_t f = 0; f < 4; ++f) {
-            for (int o = 32; o >= 1; o >>= 1)
-                mx[f] = max(mx[f], (uint32_t)__shfl_xor(mx[f], o, 64));
-            if (lane == 0)
-                atomicMax(&S.fmax[f], mx[f]);
-        }
-    }
-    __syncthreads();
-    bool moved = false;   // S.xch holds the current order
-    for (uint32_t f = 0; f < 4; ++f) {
-        const uint32_t fm = S.fmax[f];
-        for (uint32_t shift = 0; shift < 32 && (fm >> shift) != 0; shift += 8) {
-            for (int k = threadIdx.x; k < 16 * 257; k += blockDim.x)
-                S.cnt[k] = 0;
-            __syncthreads();
-            uint32_t rk[kRecPer], dg[kRecPer];
-#pragma unroll
-            for (int q = 0; q < kRecPer; ++q) {
-                const bool valid = p0 + q * 64 < m;
-                const uint32_t d = valid ? (rec_field(x[q], f) >> shift) & 0xFFu : 0u;
-                const uint64_t peers = match_digit(d, __ballot(valid));
-                const uint32_t c = valid ? S.cnt[w * 257 + d] : 0u;
-                const uint32_t mine = (uint32_t)__popcll(peers & lt);
-                if (valid && mine == 0)
-                    S.cnt[w * 257 + d] = c + (uint32_t)__popcll(peers);
-                rk[q] = c + mine;
-                dg[q] = d;
-            }
-            __syncthreads();
-            {   // exclusive scan of the 4 096 counters in (digit, wave) order
-                uint32_t v[4], sum = 0;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const uint32_t o = threadIdx.x * 4 + k;
-                    v[k] = S.cnt[(o % 16) * 257 + o / 16];
-                    sum += v[k];
-                }
-                uint32_t total;
-                uint32_t run = block_exclusive_scan(sum, S.wsum, &total);
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const uint32_t o = threadIdx.x * 4 + k;
-                    S.cnt[(o % 16) * 257 + o / 16] = run;
-                    run += v[k];
-                }
-            }
-            __syncthreads();
-#pragma unroll
-            for (int q = 0; q < kRecPer; ++q)
-                if (p0 + q * 64 < m)
-                    S.xch[S.cnt[w * 257 + dg[q]] + rk[q]] = x[q];
-            __syncthreads();
-#pragma unroll
-            for (int q = 0; q < kRecPer; ++q)
-                if (p0 + q * 64 < m)
-                    x[q] = S.xch[p0 + q * 64];
-            moved = true;
-            __syncthreads();
-        }
-    }
-    if (!moved) {   // a single distinct record (or none): already in order
-#pragma unroll
-        for (int q = 0; q < kRecPer; ++q)
-            if (p0 + q * 64 < m)
-                S.xch[p0 + q * 64] = x[q];
+    __shared__ ulonglong2 tile[kRankTile];
+    __shared__ uint32_t before[kRankPer];
+    uint32_t m;
+    const uint32_t first = blockIdx.y * width + blockIdx.x * kRankPer;
+    if (!g.get(host, m) || first >= m)
+        return;   // (the whole workgroup)
+    const Rec *in = list + blockIdx.y * width;
+    Rec *const sorted = runs + blockIdx.y * width;
+    m -= blockIdx.y * width;
+    m = m < width ? m : width;
+    const uint32_t k = blockIdx.x * kRankPer + threadIdx.x % kRankPer;
+    const uint32_t slice = threadIdx.x / kRankPer;
+    const Rec me = in[k < m ? k : m - 1];
+    const ulonglong2 x = rec_key(me);
+    if (threadIdx.x < kRankPer)
+        before[threadIdx.x] = 0;
+    uint32_t rank = 0;
+    for (uint32_t base = 0; base < m; base += kRankTile) {
+        const uint32_t n = m - base < kRankTile ? m - base : kRankTile;
         __syncthreads();
+        for (uint32_t q = threadIdx.x; q < n; q += kRankThreads)
+            tile[q] = rec_key(in[base + q]);
+        __syncthreads();
+#pragma unroll 4
+        for (uint32_t q = slice; q < n; q += kRankSlices) {
+            const ulonglong2 y = tile[q];
+            const bool tie = (y.y < x.y) | ((y.y == x.y) & (base + q < k));
+            rank += (y.x < x.x) | ((y.x == x.x) & tie) ? 1u : 0u;
+        }
     }
+    for (int o = kRankPer; o < 64; o <<= 1)
+        rank += __shfl_xor(rank, o, 64);
+    if ((threadIdx.x & 63u) < kRankPer)
+        atomicAdd(&before[threadIdx.x % kRankPer], rank);
+    __syncthreads();
+    if (threadIdx.x < kRankPer && k < m)
+        sorted[before[threadIdx.x]] = me;
 }
 
-// Records [0, count) of `in` into the lanes, kRecPer per lane.
-__device__ inline void load_lanes(Rec (&x)[kRecPer], const Rec *__restrict__ in, uint32_t count)
+// The sorted list without its repeats; *total = its length + bias.
+__global__ __launch_bounds__(1024) void k_small_unique(const Rec *__restrict__ sorted,
+                                                       uint32_t host, SmallCount g,
+                                                       Rec *__restrict__ out,
+                                                       unsigned int *total, uint32_t bias)
 {
-    const uint32_t p0 = (threadIdx.x >> 6) * 64 * kRecPer + (threadIdx.x & 63);
+    __shared__ uint32_t wsum[33];
+    uint32_t m;
+    if (!g.get(host, m))
+        return;
+    const uint32_t k0 = threadIdx.x * kRecPer;   // each lane owns kRecPer consecutive records
+    Rec r[kRecPer + 1];
+    uint32_t mine = 0, keep = 0;
+    if (k0 < m) {
+        r[0] = sorted[k0 ? k0 - 1 : 0];
 #pragma unroll
-    for (int q = 0; q < kRecPer; ++q)
-        if (p0 + q * 64 < count)
-            x[q] = in[p0 + q * 64];
-}
-
-// The canonical list of count <= kSmallCanon records; returns the number
-// written (every thread).
-__device__ inline uint32_t small_canon(const Rec *__restrict__ in, uint32_t count,
-                                       Rec *__restrict__ out, RecSortLds &S)
-{
-    Rec x[kRecPer];
-    load_lanes(x, in, count);
-    lds_radix_rec(x, count, S);
-    // repeats dropped: each thread owns up to kRecPer consecutive records
-    const Rec *r = S.xch;
-    uint32_t k0 = threadIdx.x * kRecPer;
-    uint32_t f[kRecPer], mine = 0;
-    for (int q = 0; q < kRecPer; ++q) {
-        uint32_t k = k0 + q;
-        f[q] = (k < count && (k == 0 || !rec_eq(r[k], r[k - 1]))) ? 1u : 0u;
-        mine += f[q];
+        for (int q = 0; q < kRecPer; ++q)
+            r[q + 1] = sorted[k0 + q < m ? k0 + q : m - 1];
+#pragma unroll
+        for (int q = 0; q < kRecPer; ++q) {
+            const bool on = k0 + q < m && (k0 + q == 0 || !rec_eq(r[q + 1], r[q]));
+            keep |= on ? 1u << q : 0u;
+            mine += on ? 1u : 0u;
+        }
     }
     uint32_t all;
-    uint32_t pos = block_exclusive_scan(mine, S.wsum, &all);
+    uint32_t pos = block_exclusive_scan(mine, wsum, &all);
+#pragma unroll
     for (int q = 0; q < kRecPer; ++q)
-        if (f[q])
-            out[pos++] = r[k0 + q];
-    return all;
-}
-
-__global__ __launch_bounds__(1024) void k_small_canon(const Rec *__restrict__ in,
-                                                      uint32_t count, Rec *__restrict__ out,
-                                                      uint32_t *total)
-{
-    __shared__ RecSortLds S;
-    const uint32_t all = small_canon(in, count, out, S);
+        if (keep & (1u << q))
+            out[pos++] = r[q + 1];
     if (threadIdx.x == 0)
-        *total = all;
+        *total = all + bias;
 }
 
-// The same, enqueued before the host knows the count: it runs only when the
-// node-pair levels drained their queue (flag 8, no other flag), the tree has
-// no error bits and the record count fits both the small path and the
-// capacity; *done = records written + 1 then, else it stays 0.
-__global__ __launch_bounds__(1024) void k_small_canon_gated(const Rec *__restrict__ in,
-                                                            const unsigned long long *counter,
-                                                            const unsigned int *qflags,
-                                                            const unsigned int *tree_err,
-                                                            uint32_t limit, Rec *__restrict__ out,
-                                                            unsigned int *done)
-{
-    __shared__ RecSortLds S;
-    const unsigned long long c = *counter;
-    if (*qflags != 8u || *tree_err != 0u || c > (unsigned long long)limit)
-        return;
-    const uint32_t all = c ? small_canon(in, (uint32_t)c, out, S) : 0u;
-    if (threadIdx.x == 0)
-        *done = all + 1;
-}
+// Medium lists: runs of kRunWidth records, sorted as above, then merged
+// kMergeRuns at a time: a record's place in the merged run is its place in its
+// own plus the records before it in the others (equal ones of earlier runs
+// first), found by binary searches that advance together.  Bound: the chain of
+// dependent reads of a pass (11 to 17), so few wide passes; in long lists their
+// number.  Against 4 096-record tiles sorted by one workgroup each and merged
+// pairwise: some 5 K records 68 -> 26 us, 180 K 148 -> 153.
+constexpr uint32_t kRunWidth = 1024, kMergeRuns = 8;
 
-// Medium lists: each workgroup sorts one kSmallCanon-record tile in LDS ...
-__global__ __launch_bounds__(1024) void k_tile_sort(const Rec *__restrict__ in, uint32_t bound,
-                                                    Rec *__restrict__ out, DevCount g)
-{
-    __shared__ RecSortLds S;
-    uint32_t count;
-    if (!g.get(bound, count))
-        return;
-    uint32_t base = blockIdx.x * (uint32_t)kSmallCanon;
-    if (base >= count)
-        return;
-    uint32_t m = count - base < (uint32_t)kSmallCanon ? count - base : (uint32_t)kSmallCanon;
-    Rec x[kRecPer];
-    load_lanes(x, in + base, m);
-    lds_radix_rec(x, m, S);
-    for (uint32_t k = threadIdx.x; k < m; k += blockDim.x)
-        out[base + k] = S.xch[k];
-}
-
-// ... then sorted runs of `width` records are merged pairwise: output k finds
-// by binary search how many of its predecessors come from the left run (the
-// stable merge path: on equal records the left run goes first).
 __global__ __launch_bounds__(256) void k_merge_runs(const Rec *__restrict__ in, uint32_t bound,
                                                     uint32_t width, Rec *__restrict__ out,
                                                     DevCount g)
@@ -1169,47 +1076,49 @@ __global__ __launch_bounds__(256) void k_merge_runs(const Rec *__restrict__ in, 
     uint32_t count;
     if (!g.get(bound, count))
         return;
-    uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
+    const uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= count)
         return;
-    uint64_t q0 = (uint64_t)(k / (2ull * width)) * 2ull * width;
-    uint32_t la = (uint32_t)(count - q0 < width ? count - q0 : width);
-    uint64_t b0 = q0 + la;
-    uint32_t lb = (uint32_t)(count - b0 < width ? count - b0 : width);
-    if (b0 >= count)
-        lb = 0;
-    const Rec *A = in + q0, *B = in + b0;
-    uint32_t kk = (uint32_t)(k - q0);   // rank inside the merged pair
-    uint32_t lo = kk > lb ? kk - lb : 0u, hi = kk < la ? kk : la;
-    // smallest i in [lo, hi] with not (A[i] <= B[kk - i - 1])
-    while (lo < hi) {
-        uint32_t mid = (lo + hi) >> 1;
-        if (!rec_less(B[kk - mid - 1], A[mid]))
-            lo = mid + 1;
-        else
-            hi = mid;
+    const uint32_t run = k / width, group = run / kMergeRuns * kMergeRuns;
+    const Rec me = in[k];
+    const ulonglong2 x = rec_key(me);
+    uint32_t len[kMergeRuns], pos[kMergeRuns];   // of the other runs; those before me
+#pragma unroll
+    for (uint32_t q = 0; q < kMergeRuns; ++q) {
+        const uint64_t b = (uint64_t)(group + q) * width;
+        len[q] = group + q == run || b >= count ? 0u : (uint32_t)(count - b < width ? count - b : width);
+        pos[q] = 0;
     }
-    uint32_t i = lo, j = kk - lo;
-    bool take_a = i < la && (j >= lb || !rec_less(B[j], A[i]));
-    out[k] = take_a ? A[i] : B[j];
+    for (uint32_t step = width; step; step >>= 1) {
+#pragma unroll
+        for (uint32_t q = 0; q < kMergeRuns; ++q) {
+            const bool in_run = pos[q] + step <= len[q];
+            const uint64_t at = (uint64_t)(group + q) * width + pos[q] + step - 1;
+            const ulonglong2 y = rec_key(in[in_run ? at : k]);
+            const bool tie = (y.y < x.y) | ((y.y == x.y) & (group + q < run));
+            const bool before = (y.x < x.x) | ((y.x == x.x) & tie);
+            pos[q] += (in_run & before) ? step : 0u;
+        }
+    }
+    uint64_t place = (uint64_t)group * width + (k - run * width);
+#pragma unroll
+    for (uint32_t q = 0; q < kMergeRuns; ++q)
+        place += pos[q];
+    out[place] = me;
 }
 
-hipError_t launch_small_canon(const Rec *in, uint32_t count, Rec *out, uint32_t *total,
-                              hipStream_t s)
+hipError_t launch_small_canon(const Rec *in, uint32_t count, Rec *tmp, Rec *out,
+                              unsigned int *total, hipStream_t s, const SmallCount &g,
+                              uint32_t bias)
 {
-    if (count == 0 || count > (uint32_t)kSmallCanon)
+    if (count == 0 || count > (uint32_t)kSmallCanon || (g.counter && g.limit != count))
         return hipErrorInvalidValue;
-    k_small_canon<<<1, 1024, 0, s>>>(in, count, out, total);
-    return hipGetLastError();
-}
-
-hipError_t launch_small_canon_gated(const Rec *in, const unsigned long long *counter,
-                                    const unsigned int *qflags, const unsigned int *tree_err,
-                                    uint32_t capacity, Rec *out, unsigned int *done,
-                                    hipStream_t s)
-{
-    const uint32_t limit = capacity < (uint32_t)kSmallCanon ? capacity : (uint32_t)kSmallCanon;
-    k_small_canon_gated<<<1, 1024, 0, s>>>(in, counter, qflags, tree_err, limit, out, done);
+    k_rank_runs<<<(count + kRankPer - 1) / kRankPer, kRankThreads, 0, s>>>(in, count, g, count,
+                                                                           tmp);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess)
+        return e;
+    k_small_unique<<<1, 1024, 0, s>>>(tmp, count, g, out, total, bias);
     return hipGetLastError();
 }
 
@@ -1220,12 +1129,12 @@ hipError_t launch_medium_canon(Rec *a, Rec *b, uint32_t count, uint32_t *flags, 
     if (count <= (uint32_t)kSmallCanon || count > (uint32_t)kMediumCanon ||
         (g.counter && (!total || g.hi != count || !g.qflags || !g.tree_err)))
         return hipErrorInvalidValue;
-    uint32_t tiles = (count + kSmallCanon - 1) / kSmallCanon;
-    k_tile_sort<<<tiles, 1024, 0, s>>>(a, count, b, g);
+    k_rank_runs<<<dim3(kRunWidth / kRankPer, (count + kRunWidth - 1) / kRunWidth), kRankThreads, 0,
+                  s>>>(a, count, g, kRunWidth, b);
     hipError_t e = hipGetLastError();
     Rec *src = b, *dst = a;
     // passes for the bound; with a smaller device count the last ones copy
-    for (uint32_t w = kSmallCanon; e == hipSuccess && w < count; w *= 2) {
+    for (uint32_t w = kRunWidth; e == hipSuccess && w < count; w *= kMergeRuns) {
         k_merge_runs<<<nblk(count, 256), 256, 0, s>>>(src, count, w, dst, g);
         e = hipGetLastError();
         Rec *t = src;

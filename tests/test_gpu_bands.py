@@ -130,3 +130,22 @@ def test_canonical_records_end_times_past_the_horizon(count):
     t = torch.from_numpy(rec.view(np.int32)).cuda()
     got = cd.cd_canonical_records(t, 3000, 300).cpu().numpy().view(np.uint32)
     assert np.array_equal(got, np.unique(rec, axis=0))
+
+
+@pytest.mark.parametrize("count", [7, 8, 9, 1023, 1024, 1025, 4096, 8191, 8192, 8193, 9217,
+                                   65535, 66561])
+@pytest.mark.parametrize("values", [1, 3, 1 << 32])
+def test_canonical_records_of_ranked_runs(count, values):
+    """Sizes around the sorted runs, their merges and the ranked groups, with
+    all records equal, most of them equal, or over the whole 32-bit range
+    (the largest values included)."""
+    need_gpu()
+    rng = np.random.default_rng(count)
+    rec = rng.integers(0, values, (count, 4), dtype=np.uint64).astype(np.uint32)
+    rec[:, :2] %= 300
+    rec[:, 2] %= 3001
+    if values > 3:
+        rec[-1] = [299, 299, 3000, (1 << 32) - 1]
+    t = torch.from_numpy(rec.view(np.int32)).cuda()
+    got = cd.cd_canonical_records(t, 3000, 300).cpu().numpy().view(np.uint32)
+    assert np.array_equal(got, np.unique(rec, axis=0))
