@@ -299,7 +299,7 @@ struct TreeWS {
     void *agglo;            // bottom-up build
     uint32_t *esc;   // escapes of an FP64 tree's nodes, for the refit
     unsigned long long *bounds;
-    void *radix;
+    void *radix, *words;
 };
 size_t layout_tree(void *base, size_t bytes, int64_t N, TreeWS *w)
 {
@@ -317,7 +317,12 @@ size_t layout_tree(void *base, size_t bytes, int64_t N, TreeWS *w)
     w->agglo = c.take_bytes(agglo_ws_bytes((uint32_t)n));
     w->esc = c.take<uint32_t>(2 * n);
     w->bounds = c.take<unsigned long long>(6);
-    w->radix = c.take_bytes(radix_ws_bytes(n));
+    // the word sort's counts: in the place of the slab path's keys, or, of few
+    // boxes, of the other sort's counts
+    const size_t r16 = radix_ws_bytes(n), r8 = radix_words_ws_bytes(n);
+    const bool fits = r8 <= n * sizeof(uint64_t);
+    w->radix = c.take_bytes(fits || r16 > r8 ? r16 : r8);
+    w->words = fits ? (void *)w->keys : w->radix;
     return c.off;
 }
 
@@ -929,22 +934,20 @@ int cd_build_tree(const cd_boxes *boxes, int precision, uint32_t slab_ticks, cd_
         void *res = nullptr;
         {
             Stage st("sort", s);
-            DigitPlan plan;
-            memset(&plan, 0, sizeof plan);
             if (packed) {   // code bits, then slab bits, above the box index
-                for (int sh = 0; sh < cb + sb; sh += 8)
-                    plan.shift[plan.npass++] = (uint8_t)(ib + sh);
+                uint64_t *words = nullptr;
+                CD_HIP(radix_sort_words((uint64_t *)tw.kva, (uint64_t *)tw.kvb, (uint32_t)N,
+                                        (uint32_t)ib, (uint32_t)(cb + sb), tw.words, &words, s));
+                res = words;
             } else {        // code (low word), then slab (high word) of the key
+                DigitPlan plan;
+                memset(&plan, 0, sizeof plan);
                 for (int sh = 0; sh < (int)kKeyCodeBits; sh += 8)
                     plan.shift[plan.npass++] = (uint8_t)sh;
                 for (int sh = 0; sh < sb; sh += 8)
                     plan.shift[plan.npass++] = (uint8_t)(32 + sh);
+                CD_HIP(radix_sort16(SORT_KV, tw.kva, tw.kvb, (size_t)N, plan, tw.radix, &res, s));
             }
-            if (packed)
-                CD_HIP(radix_sort8(tw.kva, tw.kvb, (size_t)N, plan, tw.radix, &res, s));
-            else
-                CD_HIP(radix_sort16(SORT_KV, tw.kva, tw.kvb, (size_t)N, plan, tw.radix, &res,
-                                    s));
         }
         src.kv = packed ? nullptr : (const KV *)res;
         src.packed = packed ? (const uint64_t *)res : nullptr;

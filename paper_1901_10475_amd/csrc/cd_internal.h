@@ -124,16 +124,21 @@ __device__ inline uint32_t wave_inclusive_scan(uint32_t v)
     return v;
 }
 
-// Lanes (among `active`) whose 8-bit digit equals this lane's digit.
+// Lanes (among `active`) whose digit of BITS bits equals this lane's: per bit,
+// those whose bit is the same, by the bit spread over a word (four instructions
+// a bit).
+template <int BITS = 8>
 __device__ inline uint64_t match_digit(uint32_t d, uint64_t active)
 {
-    uint64_t peers = active;
+    uint32_t lo = (uint32_t)active, hi = (uint32_t)(active >> 32);
 #pragma unroll
-    for (int bit = 0; bit < 8; ++bit) {
-        uint64_t b = __ballot((d >> bit) & 1u);
-        peers &= ((d >> bit) & 1u) ? b : ~b;
+    for (int bit = 0; bit < BITS; ++bit) {
+        const int mine = (int)(d << (31 - bit)) >> 31;   // 0 or ~0
+        const uint64_t b = __ballot(mine < 0);
+        lo &= ~((uint32_t)b ^ (uint32_t)mine);
+        hi &= ~((uint32_t)(b >> 32) ^ (uint32_t)mine);
     }
-    return peers;
+    return (uint64_t)hi << 32 | lo;
 }
 
 __device__ inline uint64_t lanemask_lt()
@@ -383,9 +388,11 @@ struct DigitPlan {
 };
 hipError_t radix_sort16(SortKind kind, void *a, void *b, size_t count, const DigitPlan &plan,
                         void *ws, void **result, hipStream_t s);
-// The same over 8-byte items (one 64-bit word each; plan.field ignored).
-hipError_t radix_sort8(void *a, void *b, size_t count, const DigitPlan &plan, void *ws,
-                       void **result, hipStream_t s);
+// Stable LSD sort of 64-bit words by their bits [low, low + bits); the result
+// ends in *result (a or b).  ws: radix_words_ws_bytes(count).
+size_t radix_words_ws_bytes(size_t count);
+hipError_t radix_sort_words(uint64_t *a, uint64_t *b, uint32_t count, uint32_t low, uint32_t bits,
+                            void *ws, uint64_t **result, hipStream_t s);
 // One workgroup per slab: compute the Morton codes of the slab's boxes, sort
 // (code, box index) inside LDS and write 64-bit keys (slab << 32 | code) and
 // box indices in sorted order.  err bit 1: a box's t0 is outside its slab.

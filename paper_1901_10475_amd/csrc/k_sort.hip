@@ -1,11 +1,11 @@
 // k_sort.hip -- fills, device-wide exclusive scan, stable LSD radix sorts.
 //
-// Two radix sorts live here:
-//   * radix_sort16 / radix_sort8: device-wide, stable, over 16-byte items
-//     (key/value pairs or pair records) or 8-byte ones (a key and its box
-//     index packed in one word), 8-bit digits, one histogram + scan + scatter
-//     per digit.  They sort tree keys when boxes are not grouped in slabs and
-//     put pair records in canonical order.
+// Radix sorts:
+//   * radix_sort16 / radix_sort_words: device-wide, stable, over 16-byte items
+//     (key/value pairs or pair records) in 8-bit digits, or 8-byte ones (a key
+//     and its box index packed in one word) in 9-bit digits, one histogram +
+//     scan + scatter per digit.  They sort tree keys when boxes are not grouped
+//     in slabs and put pair records in canonical order.
 //   * k_slab_build: one 1024-thread workgroup per time slab; keys stay in
 //     registers and move through LDS between digit passes, so a slab of up to
 //     kSegCap boxes is sorted with one read and one write of global memory.
@@ -128,7 +128,7 @@ hipError_t scan_exclusive_u32(const uint32_t *in, uint32_t *out, size_t count, v
     return hipGetLastError();
 }
 
-// ---- device-wide LSD radix sort of 16- and 8-byte items -------------------------------
+// ---- device-wide LSD radix sort of 16-byte items ------------------------------------------
 
 constexpr int kRadThreads = 256;
 constexpr int kRadItems = 16;
@@ -151,15 +151,6 @@ struct DigitRec {
         return (v >> shift) & 0xFFu;
     }
 };
-struct DigitU64 {
-    uint32_t shift;
-    __device__ uint32_t operator()(const uint2 &it) const
-    {
-        uint64_t v = ((uint64_t)it.y << 32) | it.x;
-        return (uint32_t)(v >> shift) & 0xFFu;
-    }
-};
-
 // Digit counts of one tile.  Lanes count into one of 16 copies of the
 // histogram (by lane mod 16, rows of 257 words so that the copies of one
 // digit sit in different banks): a tile whose items share a digit (a slab
@@ -301,30 +292,267 @@ hipError_t radix_sort16(SortKind kind, void *a, void *b, size_t count, const Dig
     return hipSuccess;
 }
 
-hipError_t radix_sort8(void *a, void *b, size_t count, const DigitPlan &plan, void *ws,
-                       void **result, hipStream_t s)
+// ---- device-wide LSD radix sort of 64-bit words ------------------------------------------
+//
+// Digits of 9 or 10 bits, so that the 37 bits left above a 27-bit box index
+// take four passes.  Per pass: k_words_up counts each tile's digits into a row,
+// k_words_rows turns every kWordsChunk rows into prefixes and their sum,
+// k_words_chunks the sums into prefixes over the chunks and digit totals, and
+// k_words_down ranks a tile's words, stages them in LDS in digit order and
+// writes each digit's run in consecutive lanes (16 words on average: whole
+// lines, where the 16-byte sort's direct scatter writes single words).
+// Bound: HBM, 24 bytes a word and pass, and in the scatter the ranking (some 40
+// instructions a word).  37 bits of 79.7 M words: counts 3.9 TB/s, scatter 4.1
+// (9 bits) and 3.0 (10), 2.06 ms in all; the 16-byte sort's form with 8-byte
+// items, 8-bit digits and 4 096-word tiles took 2.65 (five passes, counts 3.4,
+// scatter 4.1 TB/s, 36 us of scans a pass).
+constexpr int kWordsThreads = 512, kWordsWaves = kWordsThreads / 64, kWordsChunk = 64;
+template <int BITS>
+struct Words {
+    static constexpr int kBins = 1 << BITS;
+    // two workgroups' LDS on a CU
+    static constexpr int kItems = BITS == 9 ? 16 : 14;
+    static constexpr int kTile = kWordsThreads * kItems;
+    static constexpr int kPer = kBins / kWordsThreads;   // digits per lane
+    static constexpr int kCopies = BITS == 9 ? 8 : 4;    // of the counters
+};
+
+// Digit counts of one tile (Words<BITS>::kCopies histograms by lane, rows of
+// kBins + 1 words so that the copies of one digit sit in different banks).
+template <int BITS>
+__global__ __launch_bounds__(kWordsThreads) void k_words_up(const uint64_t *__restrict__ in,
+                                                            uint32_t count, uint32_t shift,
+                                                            uint32_t mask,
+                                                            uint32_t *__restrict__ rows)
 {
-    *result = a;
-    if (count <= 1 || plan.npass == 0)
-        return hipSuccess;
-    uint32_t nb = (uint32_t)((count + kRadTile - 1) / kRadTile);
-    size_t h = (size_t)nb * 256;
-    uint32_t *hist = (uint32_t *)ws;
-    void *sws = (char *)ws + align_up(h * sizeof(uint32_t), 256);
-    uint2 *src = (uint2 *)a, *dst = (uint2 *)b;
-    for (int p = 0; p < plan.npass; ++p) {
-        const DigitU64 dg{plan.shift[p]};
-        k_radix_upsweep<<<nb, kRadThreads, 0, s>>>(src, count, dg, hist, nb);
-        hipError_t e = hipGetLastError();
-        if (e == hipSuccess)
-            e = scan_exclusive_u32(hist, hist, h, sws, s);
-        if (e == hipSuccess) {
-            k_radix_downsweep<<<nb, kRadThreads, 0, s>>>(src, dst, count, dg, hist, nb);
-            e = hipGetLastError();
+    using W = Words<BITS>;
+    constexpr int kRow = W::kBins + 1;
+    __shared__ uint32_t h[W::kCopies * kRow];
+    // word pairs (their order does not matter here), every load in flight before
+    // the first count; the place of word k of this lane is
+    // base + (k / 2 kWordsThreads + threadIdx.x) 2 + k % 2
+    const uint32_t base = blockIdx.x * (uint32_t)W::kTile + 2 * threadIdx.x;
+    const uint32_t pairs = count / 2;
+    uint64_t v[W::kItems];
+#pragma unroll
+    for (int k = 0; k < W::kItems; k += 2) {
+        const uint32_t p = base / 2 + k / 2 * kWordsThreads;
+        const ulonglong2 x = reinterpret_cast<const ulonglong2 *>(in)[p < pairs ? p : 0];
+        v[k] = p < pairs ? x.x : in[count - 1];   // the last word of an odd count
+        v[k + 1] = x.y;
+    }
+    for (int k = threadIdx.x; k < W::kCopies * kRow; k += kWordsThreads)
+        h[k] = 0;
+    __syncthreads();
+    uint32_t *const mine = h + (threadIdx.x % W::kCopies) * kRow;
+#pragma unroll
+    for (int k = 0; k < W::kItems; ++k)
+        if (base + k / 2 * 2 * kWordsThreads + k % 2 < count)
+            atomicAdd(&mine[(uint32_t)(v[k] >> shift) & mask], 1u);
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < W::kPer; ++q) {
+        const int d = q * kWordsThreads + threadIdx.x;
+        uint32_t sum = 0;
+#pragma unroll
+        for (int c = 0; c < W::kCopies; ++c)
+            sum += h[c * kRow + d];
+        rows[(size_t)blockIdx.x * W::kBins + d] = sum;
+    }
+}
+
+// Rows [c kWordsChunk, ...) of one chunk: each count becomes the sum of those of
+// the chunk's earlier rows, the chunk's total goes to sums[c].
+template <int BITS>
+__global__ __launch_bounds__(256) void k_words_rows(uint32_t *__restrict__ rows, uint32_t tiles,
+                                                    uint32_t *__restrict__ sums)
+{
+    constexpr int kBins = Words<BITS>::kBins, kBatch = 16;
+    const uint32_t d = blockIdx.y * 256 + threadIdx.x, r0 = blockIdx.x * kWordsChunk;
+    const uint32_t n = tiles - r0 < (uint32_t)kWordsChunk ? tiles - r0 : (uint32_t)kWordsChunk;
+    uint32_t run = 0;
+    for (uint32_t k = 0; k < n; k += kBatch) {
+        uint32_t v[kBatch];
+#pragma unroll
+        for (uint32_t q = 0; q < kBatch; ++q)
+            v[q] = k + q < n ? rows[(size_t)(r0 + k + q) * kBins + d] : 0u;
+#pragma unroll
+        for (uint32_t q = 0; q < kBatch; ++q) {
+            if (k + q < n)
+                rows[(size_t)(r0 + k + q) * kBins + d] = run;
+            run += v[q];
         }
+    }
+    sums[(size_t)blockIdx.x * kBins + d] = run;
+}
+
+// One wave per digit: its sums over the chunks become prefixes, the total goes
+// to the row after the last chunk's.
+template <int BITS>
+__global__ __launch_bounds__(256) void k_words_chunks(uint32_t *__restrict__ sums, uint32_t chunks)
+{
+    constexpr int kBins = Words<BITS>::kBins;
+    const uint32_t d = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    uint32_t run = 0;
+    for (uint32_t c0 = 0; c0 < chunks; c0 += 64) {
+        const uint32_t c = c0 + lane;
+        const uint32_t v = c < chunks ? sums[(size_t)c * kBins + d] : 0u;
+        const uint32_t inc = wave_inclusive_scan(v);
+        if (c < chunks)
+            sums[(size_t)c * kBins + d] = run + inc - v;
+        run += (uint32_t)__builtin_amdgcn_readlane(inc, 63);
+    }
+    if (lane == 0)
+        sums[(size_t)chunks * kBins + d] = run;
+}
+
+template <int BITS>
+__global__ __launch_bounds__(kWordsThreads) void k_words_down(
+    const uint64_t *__restrict__ in, uint64_t *__restrict__ out, uint32_t count, uint32_t shift,
+    uint32_t mask, const uint32_t *__restrict__ rows, const uint32_t *__restrict__ sums,
+    uint32_t chunks)
+{
+    using W = Words<BITS>;
+    __shared__ uint64_t stage[W::kTile];
+    __shared__ uint16_t cnt[kWordsWaves][W::kBins + 2];   // per wave and digit
+    __shared__ uint32_t to[W::kBins];                     // place of staged word 0 by digit
+    __shared__ uint32_t wsum[33];
+    const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const uint32_t base = blockIdx.x * (uint32_t)W::kTile;
+    const uint32_t m = count - base < (uint32_t)W::kTile ? count - base : (uint32_t)W::kTile;
+    const uint32_t k0 = w * 64 * W::kItems + lane;
+    uint64_t item[W::kItems];
+    uint32_t rank[W::kItems];
+#pragma unroll
+    for (int j = 0; j < W::kItems; ++j) {   // every load in flight before the ranking
+        const uint32_t k = k0 + j * 64;
+        item[j] = in[base + (k < m ? k : m - 1)];
+    }
+    const uint32_t d0 = threadIdx.x * W::kPer;   // this lane's digits
+    uint32_t place[W::kPer], all[W::kPer];
+#pragma unroll
+    for (int q = 0; q < W::kPer; ++q) {
+        place[q] = rows[(size_t)blockIdx.x * W::kBins + d0 + q];
+        if (chunks > 1)
+            place[q] += sums[(size_t)(blockIdx.x / kWordsChunk) * W::kBins + d0 + q];
+        all[q] = sums[(chunks > 1 ? (size_t)chunks * W::kBins : 0) + d0 + q];
+    }
+    for (uint32_t k = threadIdx.x; k < (uint32_t)(kWordsWaves * (W::kBins + 2) / 2);
+         k += kWordsThreads)
+        reinterpret_cast<uint32_t *>(&cnt[0][0])[k] = 0;
+    __syncthreads();
+    const uint64_t lt = lanemask_lt();
+#pragma unroll
+    for (int j = 0; j < W::kItems; ++j) {
+        const bool valid = k0 + j * 64 < m;
+        const uint32_t d = (uint32_t)(item[j] >> shift) & mask;
+        const uint64_t peers = match_digit<BITS>(d, __ballot(valid));
+        const uint32_t c = cnt[w][d], mine = (uint32_t)__popcll(peers & lt);
+        if (valid && mine == 0)
+            cnt[w][d] = (uint16_t)(c + (uint32_t)__popcll(peers));
+        rank[j] = c + mine;
+    }
+    __syncthreads();
+    {   // per digit: where its words start in the tile and in the output
+        uint32_t n[W::kPer], words = 0, before = 0;
+#pragma unroll
+        for (int q = 0; q < W::kPer; ++q) {
+            n[q] = 0;
+            for (int ww = 0; ww < kWordsWaves; ++ww)
+                n[q] += cnt[ww][d0 + q];
+            words += n[q];
+            before += all[q];
+        }
+        uint32_t total;
+        uint32_t start = block_exclusive_scan(words, wsum, &total);
+        uint32_t first = block_exclusive_scan(before, wsum, &total);
+#pragma unroll
+        for (int q = 0; q < W::kPer; ++q) {
+            to[d0 + q] = first + place[q] - start;
+            first += all[q];
+            uint32_t run = start;
+            for (int ww = 0; ww < kWordsWaves; ++ww) {
+                const uint32_t t = cnt[ww][d0 + q];
+                cnt[ww][d0 + q] = (uint16_t)run;
+                run += t;
+            }
+            start += n[q];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < W::kItems; ++j)
+        if (k0 + j * 64 < m)
+            stage[cnt[w][(uint32_t)(item[j] >> shift) & mask] + rank[j]] = item[j];
+    __syncthreads();
+    for (uint32_t k = threadIdx.x; k < m; k += kWordsThreads) {
+        const uint64_t v = stage[k];
+        const uint32_t at = to[(uint32_t)(v >> shift) & mask] + k;
+        if (at < count)
+            out[at] = v;
+    }
+}
+
+namespace {
+// Rows of the narrowest tiles with the most bins, their chunks' sums, the totals.
+size_t words_tiles(size_t count) { return (count + Words<10>::kTile - 1) / Words<10>::kTile; }
+size_t words_chunks(size_t tiles) { return (tiles + kWordsChunk - 1) / kWordsChunk; }
+}  // namespace
+
+size_t radix_words_ws_bytes(size_t count)
+{
+    const size_t tiles = words_tiles(count);
+    const size_t chunks = words_chunks(tiles);   // (one chunk's sums are the totals)
+    return (tiles + chunks + (chunks > 1 ? 1 : 0)) * Words<10>::kBins * sizeof(uint32_t);
+}
+
+template <int BITS>
+static hipError_t words_pass(const uint64_t *src, uint64_t *dst, uint32_t count, uint32_t shift,
+                             uint32_t bits, uint32_t *rows, hipStream_t s)
+{
+    using W = Words<BITS>;
+    const uint32_t tiles = nblk(count, W::kTile), chunks = (uint32_t)words_chunks(tiles);
+    const uint32_t mask = (1u << bits) - 1;
+    uint32_t *const sums = rows + (size_t)tiles * W::kBins;
+    k_words_up<BITS><<<tiles, kWordsThreads, 0, s>>>(src, count, shift, mask, rows);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess)
+        return e;
+    k_words_rows<BITS><<<dim3(chunks, W::kBins / 256), 256, 0, s>>>(rows, tiles, sums);
+    e = hipGetLastError();
+    if (e != hipSuccess)
+        return e;
+    if (chunks > 1) {
+        k_words_chunks<BITS><<<W::kBins / 4, 256, 0, s>>>(sums, chunks);
+        e = hipGetLastError();
         if (e != hipSuccess)
             return e;
-        uint2 *t = src;
+    }
+    k_words_down<BITS><<<tiles, kWordsThreads, 0, s>>>(src, dst, count, shift, mask, rows, sums,
+                                                       chunks);
+    return hipGetLastError();
+}
+
+hipError_t radix_sort_words(uint64_t *a, uint64_t *b, uint32_t count, uint32_t low, uint32_t bits,
+                            void *ws, uint64_t **result, hipStream_t s)
+{
+    *result = a;
+    if (count <= 1 || bits == 0)
+        return hipSuccess;
+    if (low + bits > 64)
+        return hipErrorInvalidValue;
+    // as few passes as digits of 9 bits and one of 10 allow
+    const uint32_t passes = bits <= 10 ? 1u : (bits - 1 + 8) / 9;
+    uint64_t *src = a, *dst = b;
+    for (uint32_t p = 0; p < passes; ++p) {
+        const uint32_t left = passes - p, take = (bits + left - 1) / left;
+        hipError_t e = take > 9 ? words_pass<10>(src, dst, count, low, take, (uint32_t *)ws, s)
+                                : words_pass<9>(src, dst, count, low, take, (uint32_t *)ws, s);
+        if (e != hipSuccess)
+            return e;
+        low += take;
+        bits -= take;
+        uint64_t *t = src;
         src = dst;
         dst = t;
     }

@@ -405,3 +405,39 @@ def test_radix_tree_of_callers_codes(n, K, prec, in_tree):
         assert np.all(delta[child[inner]] > delta[inner])
     leaf_obj = t["link"][N - 1:]
     assert np.array_equal(leaf_obj, bp.boxes.obj[:N].cpu().numpy().view(np.uint32))
+
+
+@pytest.mark.parametrize("T", [1, 5, 100000])
+@pytest.mark.parametrize("N", [2, 7167, 7168, 7169, 8191, 8192, 8193, 458752, 458753, 524289])
+def test_key_sort_is_stable(N, T):
+    """The packed key sort at its tiles' and chunks' edges, over 32 to 47 key
+    bits (all digit widths): boxes on a few points, so that most keys are
+    equal.  Leaves come slab by slab, the boxes of a point together within a
+    slab and in input order."""
+    need_gpu()
+    say("key sort, N", N, "T", T)
+    rng = np.random.default_rng(N + T)
+    pts = rng.uniform(-7000, 7000, (13, 3))
+    which = rng.integers(0, 13, N)
+    t0 = rng.integers(0, T, N)
+    b = cd.Boxes.from_arrays(pts[which], pts[which] + 1.0, t0, t0 + 1, np.arange(N),
+                             horizon_ticks=T, obj_count=N)
+    tree = cd.Tree(N, cd.CD_FP64)
+    ws = cd._bytes(cd.lib().cd_build_tree_ws(N), "cuda")
+    cd.cd_build_tree(b, cd.CD_FP64, tree, ws, 1)
+    torch.cuda.synchronize()
+    raw = tree.mem.cpu().numpy().view(np.uint8)
+    assert raw[:4].view(np.uint32)[0] == 0
+    leaf = raw[256 + (N - 1) * 64:256 + (2 * N - 1) * 64].reshape(N, 64)[:, 48:64]
+    order = leaf.copy().view(np.uint32)[:, 2].astype(np.int64)
+    assert np.array_equal(np.sort(order), np.arange(N))
+    slab, point = t0[order], which[order]
+    assert np.all(np.diff(slab) >= 0)
+    group = slab * 13 + point
+    starts = np.flatnonzero(np.r_[True, np.diff(group) != 0])
+    # points of one code may alternate only by index; else each group is one run
+    cell = np.floor((pts - pts.min(0)) / (np.ptp(pts, axis=0) + 1.0) * 1024)
+    if len(np.unique(cell, axis=0)) == 13:
+        assert len(starts) == len(np.unique(group))
+        same = np.diff(group) == 0
+        assert np.all(np.diff(order)[same] > 0)
