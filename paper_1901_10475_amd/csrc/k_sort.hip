@@ -563,29 +563,34 @@ hipError_t radix_sort_words(uint64_t *a, uint64_t *b, uint32_t count, uint32_t l
 // ---- per-slab LDS radix sort ---------------------------------------------------------
 //
 // Block = kSegThreads (16 waves).  Wave w holds the keys with local index
-// w * 64 * kSegItems + j * 64 + lane (item j) in registers.  Per 8-bit digit:
-// rank inside the wave per item, scan the (digit, wave) counters, scatter the
-// keys and then the values through one LDS exchange buffer, read back.
+// w * 64 * ITEMS + j * 64 + lane (item j) in registers.  Per 8-bit digit:
+// rank inside the wave per item, scan the (digit, wave) counters, scatter keys
+// and values as pairs through one LDS exchange buffer, read back.
 
 constexpr int kSegWaves = kSegThreads / 64;
+static_assert(kSegCap <= 65536, "a local index in 16 bits");
 
-// Sorts the m <= kSegCap keys of one workgroup by 32-bit key, stably, in four
-// 8-bit digit passes; item j of lane `lane` of wave w is local index
-// w * 64 * kSegItems + j * 64 + lane, before and after.  val travels with
-// key.  xch: kSegCap words of LDS; cnt: kSegWaves * 257; wsum: 64.
-__device__ inline void lds_sort32(uint32_t (&key)[kSegItems], uint32_t (&val)[kSegItems],
-                                  uint32_t m, uint32_t *xch, uint32_t *cnt, uint32_t *wsum)
+// Sorts the m <= kSegThreads * ITEMS keys of one workgroup by 32-bit key,
+// stably, in four 8-bit digit passes; item j of lane `lane` of wave w is local
+// index w * 64 * ITEMS + j * 64 + lane, before and after.  val (below 2^16)
+// travels with key; during a pass its upper half holds the rank, which spares a
+// register an item.  xch: kSegThreads * ITEMS pairs of LDS; cnt: kSegWaves * 257;
+// wsum: 64.
+template <int ITEMS>
+__device__ inline void lds_sort32(uint32_t (&key)[ITEMS], uint32_t (&val)[ITEMS], uint32_t m,
+                                  uint2 *xch, uint32_t *cnt, uint32_t *wsum)
 {
     int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    uint32_t li0 = (uint32_t)w * 64 * kSegItems + lane;
+    uint32_t li0 = (uint32_t)w * 64 * ITEMS + lane;
     uint64_t lt = lanemask_lt();
+#pragma unroll 1
     for (int shift = 0; shift < 32; shift += 8) {
         for (int k = threadIdx.x; k < kSegWaves * 257; k += kSegThreads)
             cnt[k] = 0;
         __syncthreads();
-        uint32_t rk[kSegItems];  // rank inside (digit, wave), then final position
+        // rank inside (digit, wave)
 #pragma unroll
-        for (int j = 0; j < kSegItems; ++j) {
+        for (int j = 0; j < ITEMS; ++j) {
             uint32_t li = li0 + j * 64;
             bool valid = li < m;
             uint32_t d = (key[j] >> shift) & 0xFFu;
@@ -594,7 +599,7 @@ __device__ inline void lds_sort32(uint32_t (&key)[kSegItems], uint32_t (&val)[kS
             uint32_t mine = (uint32_t)__popcll(peers & lt);
             if (valid && mine == 0)
                 cnt[w * 257 + d] = c + (uint32_t)__popcll(peers);
-            rk[j] = c + mine;
+            val[j] |= (c + mine) << 16;
         }
         __syncthreads();
         {   // exclusive scan of the 4096 counters in (digit, wave) order
@@ -615,32 +620,21 @@ __device__ inline void lds_sort32(uint32_t (&key)[kSegItems], uint32_t (&val)[kS
             }
         }
         __syncthreads();
+        int again = shift;   // opaque: the digits are formed anew, not kept (and spilled)
+        asm volatile("" : "+s"(again));
 #pragma unroll
-        for (int j = 0; j < kSegItems; ++j) {
-            uint32_t d = (key[j] >> shift) & 0xFFu;
-            rk[j] += cnt[w * 257 + d];
-        }
-        // keys, then values, through the exchange buffer
-#pragma unroll
-        for (int j = 0; j < kSegItems; ++j)
-            if (li0 + j * 64 < m && rk[j] < (uint32_t)kSegCap)
-                xch[rk[j]] = key[j];
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < kSegItems; ++j)
+        for (int j = 0; j < ITEMS; ++j)
             if (li0 + j * 64 < m)
-                key[j] = xch[li0 + j * 64];
+                xch[cnt[w * 257 + ((key[j] >> again) & 0xFFu)] + (val[j] >> 16)] =
+                    make_uint2(key[j], val[j] & 0xFFFFu);
         __syncthreads();
 #pragma unroll
-        for (int j = 0; j < kSegItems; ++j)
-            if (li0 + j * 64 < m && rk[j] < (uint32_t)kSegCap)
-                xch[rk[j]] = val[j];
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < kSegItems; ++j)
-            if (li0 + j * 64 < m)
-                val[j] = xch[li0 + j * 64];
-        __syncthreads();
+        for (int j = 0; j < ITEMS; ++j)
+            if (li0 + j * 64 < m) {
+                const uint2 x = xch[li0 + j * 64];
+                key[j] = x.x;
+                val[j] = x.y;
+            }
     }
 }
 
@@ -650,7 +644,7 @@ __global__ __launch_bounds__(kSegThreads) void k_slab_build(
     const unsigned long long *bounds, uint32_t *__restrict__ codes_out, void *tree,
     unsigned int *err)
 {
-    __shared__ uint32_t xch[kSegCap];
+    __shared__ uint2 pairs[kSegCap];
     // counters of (digit, wave), stored wave-major with a 257-word row (see
     // k_radix_downsweep): index w * 257 + d
     __shared__ uint32_t cnt[kSegWaves * 257];
@@ -692,12 +686,14 @@ __global__ __launch_bounds__(kSegThreads) void k_slab_build(
     }
     if (bad)
         atomicOr(err, 1u);
-    lds_sort32(key, val, m, xch, cnt, wsum);
+    lds_sort32(key, val, m, pairs, cnt, wsum);
+    __syncthreads();
     // Leaf records.  Reading boxes by sorted position would gather 4-8 byte
     // words from all over the slab; instead each box is read in source order
     // (coalesced) and its whole record is written to its sorted slot.  LDS
     // holds the sorted codes (for the skip links) and the inverse permutation.
-    __shared__ uint32_t vsrc[kSegCap];  // source box -> sorted position
+    uint32_t *const xch = reinterpret_cast<uint32_t *>(pairs);
+    uint32_t *const vsrc = xch + kSegCap;   // source box -> sorted position
 #pragma unroll
     for (int j = 0; j < kSegItems; ++j) {
         uint32_t p = li0 + j * 64;
@@ -751,12 +747,20 @@ __global__ __launch_bounds__(kSegThreads) void k_slab_build(
 // the block (entry k at (b stride + k) es words) sorted in LDS by code,
 // stable, each with its block-local index; written to the same entries of
 // scode / sobj.  With one run (S = n) that is the block's whole order.
+//
+// ITEMS: keys per lane, chosen to just hold a run (the ranking, 32 instructions
+// a key and digit, is done for every place).  Bound: the four digit passes of a
+// workgroup, from 5 keys a lane on alone on its CU.  Against 17 keys a lane for
+// every size, keys and values exchanged apart: 8 blocks of 1 000 53 -> 9.5 us,
+// 150 of 4 999 62 -> 19; 450 blocks of 16 848 121 -> 100 (two rounds of
+// workgroups), where the ranks are kept in 16 bits so that no register spills.
+template <int ITEMS>
 __global__ __launch_bounds__(kSegThreads) void k_block_sort(const uint32_t *ucode, uint32_t n,
                                                             uint32_t S, uint64_t stride,
                                                             uint32_t es, uint32_t *scode,
                                                             uint32_t *sobj)
 {
-    __shared__ uint32_t xch[kSegCap];
+    __shared__ uint2 xch[kSegThreads * ITEMS];
     __shared__ uint32_t cnt[kSegWaves * 257];
     __shared__ uint32_t wsum[64];
     int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -765,23 +769,41 @@ __global__ __launch_bounds__(kSegThreads) void k_block_sort(const uint32_t *ucod
         return;   // (the whole workgroup)
     const uint32_t m = n - r0 < S ? n - r0 : S;
     uint64_t base = (uint64_t)blockIdx.x * stride + r0;
-    uint32_t key[kSegItems], val[kSegItems];
-    uint32_t li0 = (uint32_t)w * 64 * kSegItems + lane;
+    uint32_t key[ITEMS], val[ITEMS];
+    uint32_t li0 = (uint32_t)w * 64 * ITEMS + lane;
 #pragma unroll
-    for (int j = 0; j < kSegItems; ++j) {
+    for (int j = 0; j < ITEMS; ++j) {
         uint32_t li = li0 + j * 64;
         key[j] = li < m ? ucode[(base + li) * es] : 0xFFFFFFFFu;
-        val[j] = r0 + li;
+        val[j] = li;
     }
     lds_sort32(key, val, m, xch, cnt, wsum);
 #pragma unroll
-    for (int j = 0; j < kSegItems; ++j) {
+    for (int j = 0; j < ITEMS; ++j) {
         uint32_t r = li0 + j * 64;
         if (r < m) {
             scode[(base + r) * es] = key[j];
-            sobj[(base + r) * es] = val[j];
+            sobj[(base + r) * es] = r0 + val[j];
         }
     }
+}
+
+static hipError_t block_sort_runs(const uint32_t *ucode, uint32_t n, uint32_t S, uint32_t R,
+                                  uint32_t nblocks, uint64_t stride, uint32_t es,
+                                  uint32_t *scode, uint32_t *sobj, hipStream_t s)
+{
+    auto run = [&](auto kernel) {
+        kernel<<<dim3(nblocks, R), kSegThreads, 0, s>>>(ucode, n, S, stride, es, scode, sobj);
+        return hipGetLastError();
+    };
+    const uint32_t items = (S + kSegThreads - 1) / kSegThreads;
+    return items <= 1   ? run(k_block_sort<1>)
+           : items <= 2 ? run(k_block_sort<2>)
+           : items <= 3 ? run(k_block_sort<3>)
+           : items <= 5 ? run(k_block_sort<5>)
+           : items <= 8 ? run(k_block_sort<8>)
+           : items <= 12 ? run(k_block_sort<12>)
+                         : run(k_block_sort<kSegItems>);
 }
 
 // The R sorted runs of each block merged: entry e of run r goes to position
@@ -829,13 +851,9 @@ hipError_t launch_block_sort(const uint32_t *ucode, uint32_t n, uint32_t nblocks
     if (R > (uint32_t)kBlockRuns || (R > 1 && (!rcode || !robj)))
         return hipErrorInvalidValue;
     const uint32_t S = (n + R - 1) / R;
-    if (R == 1) {
-        k_block_sort<<<dim3(nblocks, 1), kSegThreads, 0, s>>>(ucode, n, S, stride, es, scode,
-                                                              sobj);
-        return hipGetLastError();
-    }
-    k_block_sort<<<dim3(nblocks, R), kSegThreads, 0, s>>>(ucode, n, S, stride, es, rcode, robj);
-    hipError_t e = hipGetLastError();
+    if (R == 1)
+        return block_sort_runs(ucode, n, S, 1, nblocks, stride, es, scode, sobj, s);
+    hipError_t e = block_sort_runs(ucode, n, S, R, nblocks, stride, es, rcode, robj, s);
     if (e != hipSuccess)
         return e;
     k_block_merge<<<dim3((n + 255) / 256, nblocks), 256, 0, s>>>(rcode, robj, n, S, R, stride, es,

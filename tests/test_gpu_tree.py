@@ -441,3 +441,26 @@ def test_key_sort_is_stable(N, T):
         assert len(starts) == len(np.unique(group))
         same = np.diff(group) == 0
         assert np.all(np.diff(order)[same] > 0)
+
+
+@pytest.mark.parametrize("n", [1024, 1025, 2048, 2049, 3072, 3073, 5120, 5121, 8192, 8193, 12288,
+                               12289, 17408])
+def test_block_sort_sizes(n):
+    """The block sort at the edges of its keys per lane: every slab in
+    (code, object) order, each object once, the codes those of the objects in
+    the object layout's boxes' block."""
+    need_gpu()
+    say("block sort, n", n)
+    K = 9
+    c = _uniform(n, K, 2, seed=n + 3, in_tree=True, build=False)
+    cd.cd_build_boxes(c.el_soa, None, c.params, c.boxes, c.ws_boxes)
+    assert c.in_tree and c.boxes.desc.layout == cd.CD_LAYOUT_SORTED
+    obj = c.boxes.obj.cpu().numpy().view(np.uint32).reshape(K, n)
+    code = c.boxes.code.cpu().numpy().view(np.uint32).reshape(K, n)
+    key = (code.astype(np.int64) << 32) | obj.astype(np.int64)
+    assert np.all(np.diff(key, axis=1) > 0)
+    assert np.all(np.sort(obj, axis=1) == np.arange(n)[None, :])
+    lo, hi, t0, t1, ob = c.boxes.to_host()
+    a = _uniform(n, K, 2, seed=n + 3, layout=cd.CD_LAYOUT_OBJECT, in_tree=False)
+    inv = np.argsort(obj, axis=1) + (np.arange(K) * n)[:, None]
+    assert np.array_equal(a.boxes.lo[:, :n * K].cpu().numpy().T, lo[inv.ravel()])
