@@ -835,7 +835,19 @@ int cd_build_tree(const cd_boxes *boxes, int precision, uint32_t slab_ticks, cd_
     hipStream_t s = (hipStream_t)stream;
     unsigned int *err = (unsigned int *)tree->mem;
     void *nodes = (char *)tree->mem + kTreeHeader;
-    CD_HIP(launch_fill_u32(err, 0u, kTreeHeader / 4, s));
+    // slabs of at most kSegCap boxes in object order are built top-down, every
+    // other box set bottom-up; the latter's FP64 leaf skip links go to the side
+    // array
+    const bool seg = boxes->slab_size > 0 && boxes->slab_size <= kSegCap &&
+                     boxes->slab_ticks == w && N % boxes->slab_size == 0;
+    const bool in_place = boxes->records != nullptr;
+    // boxes sorted within their slabs by their codes (cd_build_boxes with
+    // CD_LAYOUT_SORTED) as arrays: box j is leaf j, no key sort
+    const bool presorted = seg && boxes->layout == CD_LAYOUT_SORTED && boxes->code &&
+                           boxes->code_valid;
+    const bool top_down = seg && !in_place && !presorted;
+    CD_HIP(launch_tree_header((TreeHeader *)tree->mem,
+                              N > 0 && precision == CD_FP64 && !top_down, s));
     tree->count = N;
     tree->precision = precision;
     tree->slab_ticks = w;
@@ -847,18 +859,12 @@ int cd_build_tree(const cd_boxes *boxes, int precision, uint32_t slab_ticks, cd_
     layout_tree(ws, ws_bytes, N, &tw);
     BoxView bv = view_of(boxes);
     uint32_t max_slab = horizon / w;
-    bool seg = boxes->slab_size > 0 && boxes->slab_size <= kSegCap && boxes->slab_ticks == w &&
-               N % boxes->slab_size == 0;
     uint2 *kids = (uint2 *)((char *)tree->mem + tree_kids_offset((uint64_t)N, precision));
     SeedSink sink;
     sink.items = (uint2 *)((char *)tree->mem + tree_seeds_offset((uint64_t)N, precision));
     sink.cap = (uint32_t)seed_cap((uint64_t)N);
     sink.hdr = (TreeHeader *)tree->mem;
-    const bool in_place = boxes->records != nullptr;
-    // boxes sorted within their slabs by their codes (cd_build_boxes with
-    // CD_LAYOUT_SORTED) as arrays: box j is leaf j, no key sort
-    const bool presorted = seg && boxes->layout == CD_LAYOUT_SORTED && bv.code;
-    if (seg && !in_place && !presorted) {
+    if (top_down) {
         // object-order slabs: each slab sorted in one workgroup's LDS with its
         // leaf records written in sorted order, then the top-down Karras pass
         // and the refit.  FP32 trees keep their link records in the tree
@@ -894,10 +900,8 @@ int cd_build_tree(const cd_boxes *boxes, int precision, uint32_t slab_ticks, cd_
     // every other box set: hierarchy, inner boxes and skip links in one
     // bottom-up pass; an FP64 tree's leaf skip links go to the side array
     uint32_t *side = nullptr;
-    if (precision == CD_FP64) {
+    if (precision == CD_FP64)
         side = (uint32_t *)((char *)tree->mem + tree_leaf_esc_offset((uint64_t)N, precision));
-        CD_HIP(launch_fill_u32(&((TreeHeader *)tree->mem)->leaf_esc_side, 1u, 1, s));
-    }
     if (in_place) {
         // the leaf records are in place (the records' code words keep the
         // codes); keys from the packed codes
@@ -1068,10 +1072,14 @@ int cd_query_pairs(const cd_tree *tree, cd_pair *out, int64_t capacity, int64_t 
                     n_in = w.qcount + lev + 1;
                     in_cap = sub_cap;
                 }
-                CD_HIP(launch_query_status(w.counter, err, w.qcount, (uint32_t)lev,
-                                           w.ctl + kCtlStatus, s));
+                // the list, if the levels drained and the count fits; the small
+                // one's last kernel writes the status too
+                const uint32_t limit = (uint32_t)(capacity < kSmallCanon ? capacity : kSmallCanon);
+                const bool small = try_canon && !plan && limit > 0;
+                if (!small)
+                    CD_HIP(launch_query_status(w.counter, err, w.qcount, (uint32_t)lev,
+                                               w.ctl + kCtlStatus, s));
                 if (try_canon) {
-                    // the list, if the levels drained and the count fits
                     delete trav;
                     trav = nullptr;
                     Stage c("canon", s);
@@ -1079,14 +1087,16 @@ int cd_query_pairs(const cd_tree *tree, cd_pair *out, int64_t capacity, int64_t 
                         const DevCount g{w.counter, w.qflags, err, (uint32_t)kSmallCanon, plan};
                         CD_HIP(launch_medium_canon(w.raw, w.alt, plan, w.flags, w.pos, w.scan,
                                                    (Rec *)out, s, g, w.ctl + kCtlCanon, 1u));
-                    } else {
-                        const uint32_t limit = (uint32_t)(capacity < kSmallCanon ? capacity
-                                                                                 : kSmallCanon);
-                        if (limit) {
-                            const SmallCount g{w.counter, w.qflags, err, limit};
-                            CD_HIP(launch_small_canon(w.raw, limit, w.alt, (Rec *)out,
-                                                      w.ctl + kCtlCanon, s, g, 1u));
-                        }
+                    } else if (small) {
+                        const SmallCount g{w.counter, w.qflags, err, limit};
+                        QueryReport r{};
+                        r.counter = w.counter;
+                        r.tree_err = err;
+                        r.qcount = w.qcount;
+                        r.levels = (uint32_t)lev;
+                        r.status = w.ctl + kCtlStatus;
+                        CD_HIP(launch_small_canon(w.raw, limit, w.alt, (Rec *)out,
+                                                  w.ctl + kCtlCanon, s, g, 1u, r));
                     }
                     try_canon = false;
                 }
@@ -1241,7 +1251,13 @@ int cd_query_pairs_async(const cd_tree *tree, cd_pair *out, int64_t capacity,
             CD_HIP(launch_pad_records(w.raw, w.counter, cap, s));
         if (!padded) {
             const SmallCount g{w.counter, nullptr, nullptr, cap};
-            CD_HIP(launch_small_canon(w.raw, cap, w.alt, (Rec *)out, w.pos + cap, s, g));
+            QueryReport r{};
+            r.counter = w.counter;
+            r.tree_err = err;
+            r.cap = cap;
+            r.count_out = count_dev;
+            r.status_out = status_dev;
+            CD_HIP(launch_small_canon(w.raw, cap, w.alt, (Rec *)out, w.pos + cap, s, g, 0u, r));
         } else if (cap <= (uint32_t)kMediumCanon) {
             CD_HIP(launch_medium_canon(w.raw, w.alt, cap, w.flags, w.pos, w.scan, (Rec *)out,
                                        s));
@@ -1251,8 +1267,9 @@ int cd_query_pairs_async(const cd_tree *tree, cd_pair *out, int64_t capacity,
             CD_HIP(radix_sort16(SORT_REC, w.raw, w.alt, cap, plan, w.radix, &res, s));
             CD_HIP(launch_unique((const Rec *)res, cap, w.flags, w.pos, w.scan, (Rec *)out, s));
         }
-        CD_HIP(launch_query_finish(w.counter, err, w.pos + cap, cap, padded, count_dev,
-                                   status_dev, s));
+        if (padded)
+            CD_HIP(launch_query_finish(w.counter, err, w.pos + cap, cap, count_dev, status_dev,
+                                       s));
     }
     return debug_sync((hipStream_t)stream, "cd_query_pairs_async", nullptr, status_dev);
 }

@@ -455,6 +455,7 @@ struct TreeHeader {
     uint32_t pad[60];
 };
 static_assert(sizeof(TreeHeader) == 256, "TreeHeader layout");
+hipError_t launch_tree_header(TreeHeader *hdr, bool leaf_esc_side, hipStream_t s);
 inline size_t seed_cap(uint64_t N) { return (size_t)(N / 4 + 4096); }
 // Tree buffer layout: header | nodes (FP64: 64-byte records; FP32: 32-byte
 // boxes, then 8-byte links) | kids[N - 1] (both children of each inner node)
@@ -661,7 +662,7 @@ hipError_t launch_query_decide(const unsigned int *last_count, uint32_t lists,
 hipError_t launch_pad_records(Rec *raw, const unsigned long long *counter, uint32_t cap,
                               hipStream_t s);
 hipError_t launch_query_finish(const unsigned long long *counter, const unsigned int *tree_err,
-                               const uint32_t *uniq, uint32_t cap, bool padded,
+                               const uint32_t *uniq, uint32_t cap,
                                unsigned long long *count_out, unsigned int *status_out,
                                hipStream_t s);
 // bulk interval refinement (items {record, first instant, last instant, 0})
@@ -714,12 +715,25 @@ struct SmallCount {
         return true;
     }
 };
+// What a query's last kernel also reports (each part if its pointer is set):
+// to the host, as launch_query_status; to the device, as launch_query_finish of
+// a list that was not padded.
+struct QueryReport {
+    const unsigned long long *counter;
+    const unsigned int *tree_err;
+    const unsigned int *qcount;   // status: the queue counts, launches made
+    uint32_t levels;
+    unsigned int *status;
+    uint32_t cap;
+    unsigned long long *count_out;
+    unsigned int *status_out;
+};
 // The canonical list of 1 .. kSmallCanon records (count, or g.limit == count of
 // them at most): sorted into tmp (count places), *total = records written to
 // out + bias.
 hipError_t launch_small_canon(const Rec *in, uint32_t count, Rec *tmp, Rec *out,
                               unsigned int *total, hipStream_t s, const SmallCount &g = {},
-                              uint32_t bias = 0);
+                              uint32_t bias = 0, const QueryReport &report = {});
 // kSmallCanon < count <= kMediumCanon: short runs sorted, merged eight at a
 // time, then repeats removed (launch_unique; total at pos[count]).  a holds the
 // records and is overwritten; b is scratch of count records.  Up to 2^18

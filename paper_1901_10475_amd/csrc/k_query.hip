@@ -863,50 +863,64 @@ __global__ void k_pad_records(Rec *raw, const unsigned long long *counter, uint3
 // Result words: count (records written, or records found when they exceed the
 // capacity) and status bits (1 capacity exceeded, 2 tree inconsistent).
 // padded: the list was formed over all cap slots, the unused ones one filler.
-__global__ void k_query_finish(const unsigned long long *counter, const unsigned int *tree_err,
-                               const uint32_t *uniq, uint32_t cap, int padded,
-                               unsigned long long *count_out, unsigned int *status_out)
+__device__ inline void report_finish(unsigned long long c, unsigned int tree_err, uint32_t uniq,
+                                     uint32_t cap, bool padded, unsigned long long *count_out,
+                                     unsigned int *status_out)
 {
-    unsigned long long c = *counter;
     unsigned int st = 0;
     if (c > cap)
         st |= 1u;
-    if (*tree_err)
+    if (tree_err)
         st |= 2u;
     unsigned long long n = 0;
     if (c > cap)
         n = c;
     else if (c > 0)
-        n = (unsigned long long)*uniq - (padded && c < cap ? 1ull : 0ull);
+        n = (unsigned long long)uniq - (padded && c < cap ? 1ull : 0ull);
     *count_out = n;
     *status_out = st;
 }
 
-// Side by side, for one read: the record count, the tree's error word and the
-// last of the queues 1 .. levels that held pairs (0: none did).
-__global__ __launch_bounds__(512) void k_query_status(const unsigned long long *counter,
-                                                      const unsigned int *tree_err,
-                                                      const unsigned int *qcount, uint32_t levels,
-                                                      unsigned int *out)
+__global__ void k_query_finish(const unsigned long long *counter, const unsigned int *tree_err,
+                               const uint32_t *uniq, uint32_t cap,
+                               unsigned long long *count_out, unsigned int *status_out)
 {
-    __shared__ unsigned int last;
+    report_finish(*counter, *tree_err, *uniq, cap, true, count_out, status_out);
+}
+
+// Side by side, for one read: the record count, the tree's error word and the
+// last of the queues 1 .. levels that held pairs (0: none did).  At least
+// `levels` lanes of one workgroup, all of them; last: a word of LDS.
+__device__ inline void report_status(const unsigned long long *counter,
+                                     const unsigned int *tree_err, const unsigned int *qcount,
+                                     uint32_t levels, unsigned int *out, unsigned int *last)
+{
     if (threadIdx.x == 0)
-        last = 0;
+        *last = 0;
     __syncthreads();
     const uint32_t l = threadIdx.x + 1;
     unsigned int any = 0;
     for (uint32_t q = 0; q < kExpandSubs && l <= levels; ++q)
         any |= qcount[q * kExpandSubStride + l];
     if (any)
-        atomicMax(&last, l);
+        atomicMax(last, l);
     __syncthreads();
     if (threadIdx.x == 0) {
         const unsigned long long c = *counter;
         out[0] = (unsigned int)c;
         out[1] = (unsigned int)(c >> 32);
         out[2] = *tree_err;
-        out[3] = last;
+        out[3] = *last;
     }
+}
+
+__global__ __launch_bounds__(512) void k_query_status(const unsigned long long *counter,
+                                                      const unsigned int *tree_err,
+                                                      const unsigned int *qcount, uint32_t levels,
+                                                      unsigned int *out)
+{
+    __shared__ unsigned int last;
+    report_status(counter, tree_err, qcount, levels, out, &last);
 }
 
 hipError_t launch_query_status(const unsigned long long *counter, const unsigned int *tree_err,
@@ -944,12 +958,11 @@ hipError_t launch_pad_records(Rec *raw, const unsigned long long *counter, uint3
 }
 
 hipError_t launch_query_finish(const unsigned long long *counter, const unsigned int *tree_err,
-                               const uint32_t *uniq, uint32_t cap, bool padded,
+                               const uint32_t *uniq, uint32_t cap,
                                unsigned long long *count_out, unsigned int *status_out,
                                hipStream_t s)
 {
-    k_query_finish<<<1, 1, 0, s>>>(counter, tree_err, uniq, cap, padded ? 1 : 0, count_out,
-                                   status_out);
+    k_query_finish<<<1, 1, 0, s>>>(counter, tree_err, uniq, cap, count_out, status_out);
     return hipGetLastError();
 }
 
@@ -1025,13 +1038,19 @@ __global__ __launch_bounds__(kRankThreads) void k_rank_runs(const Rec *__restric
         sorted[before[threadIdx.x]] = me;
 }
 
-// The sorted list without its repeats; *total = its length + bias.
+// The sorted list without its repeats; *total = its length + bias.  Being the
+// query's last kernel it also makes its report (a launch of its own is 4.5 us).
 __global__ __launch_bounds__(1024) void k_small_unique(const Rec *__restrict__ sorted,
                                                        uint32_t host, SmallCount g,
                                                        Rec *__restrict__ out,
-                                                       unsigned int *total, uint32_t bias)
+                                                       unsigned int *total, uint32_t bias,
+                                                       QueryReport report)
 {
     __shared__ uint32_t wsum[33];
+    __shared__ unsigned int last;
+    if (report.status)
+        report_status(report.counter, report.tree_err, report.qcount, report.levels,
+                      report.status, &last);
     uint32_t m;
     if (!g.get(host, m))
         return;
@@ -1056,8 +1075,12 @@ __global__ __launch_bounds__(1024) void k_small_unique(const Rec *__restrict__ s
     for (int q = 0; q < kRecPer; ++q)
         if (keep & (1u << q))
             out[pos++] = r[q + 1];
-    if (threadIdx.x == 0)
+    if (threadIdx.x == 0) {
         *total = all + bias;
+        if (report.count_out)
+            report_finish(*report.counter, *report.tree_err, all, report.cap, false,
+                          report.count_out, report.status_out);
+    }
 }
 
 // Medium lists: runs of kRunWidth records, sorted as above, then merged
@@ -1109,7 +1132,7 @@ __global__ __launch_bounds__(256) void k_merge_runs(const Rec *__restrict__ in, 
 
 hipError_t launch_small_canon(const Rec *in, uint32_t count, Rec *tmp, Rec *out,
                               unsigned int *total, hipStream_t s, const SmallCount &g,
-                              uint32_t bias)
+                              uint32_t bias, const QueryReport &report)
 {
     if (count == 0 || count > (uint32_t)kSmallCanon || (g.counter && g.limit != count))
         return hipErrorInvalidValue;
@@ -1118,7 +1141,7 @@ hipError_t launch_small_canon(const Rec *in, uint32_t count, Rec *tmp, Rec *out,
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return e;
-    k_small_unique<<<1, 1024, 0, s>>>(tmp, count, g, out, total, bias);
+    k_small_unique<<<1, 1024, 0, s>>>(tmp, count, g, out, total, bias, report);
     return hipGetLastError();
 }
 

@@ -13,6 +13,19 @@ namespace cd {
 
 static inline unsigned nblk(uint64_t n, unsigned t) { return (unsigned)((n + t - 1) / t); }
 
+// The empty header of a tree to be built.
+__global__ void k_tree_header(TreeHeader *hdr, uint32_t side)
+{
+    uint32_t *const w = reinterpret_cast<uint32_t *>(hdr);
+    w[threadIdx.x] = w + threadIdx.x == &hdr->leaf_esc_side ? side : 0u;
+}
+
+hipError_t launch_tree_header(TreeHeader *hdr, bool leaf_esc_side, hipStream_t s)
+{
+    k_tree_header<<<1, sizeof(TreeHeader) / 4, 0, s>>>(hdr, leaf_esc_side ? 1u : 0u);
+    return hipGetLastError();
+}
+
 // ---- scene bounds of the box centres -------------------------------------------------
 
 // The frame only shapes the tree (codes outside it are clamped), so a strided
@@ -69,7 +82,7 @@ hipError_t launch_bounds(const BoxView &b, int precision, uint32_t N, unsigned l
         return e;
     uint32_t stride = N > (1u << 18) ? N >> 18 : 1u;
     unsigned g = nblk((N + stride - 1) / stride, 256);
-    g = g > 1024 ? 1024 : g;
+    g = g > 128 ? 128 : g;   // (each makes six atomics on one line)
     if (precision == CD_FP64)
         k_bounds<CD_FP64><<<g, 256, 0, s>>>(b, N, stride, bounds);
     else
