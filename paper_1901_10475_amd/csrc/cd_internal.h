@@ -378,21 +378,35 @@ size_t scan_ws_bytes(size_t count);
 hipError_t scan_exclusive_u32(const uint32_t *in, uint32_t *out, size_t count, void *ws,
                               hipStream_t s);
 size_t radix_ws_bytes(size_t count);
-// Stable LSD sort of 16-byte items by the digits given by `fields`; the result
-// ends in *result (one of a, b).
-enum SortKind { SORT_KV = 0, SORT_REC = 1 };
+// Stable LSD sort of (key, index) items by the 8-bit digits at the plan's shifts;
+// the result ends in *result (one of a, b).
 struct DigitPlan {
     int npass;
-    uint8_t field[16];  // KV: ignored; Rec: 0..3 = i, j, tlo, thi
     uint8_t shift[16];
 };
-hipError_t radix_sort16(SortKind kind, void *a, void *b, size_t count, const DigitPlan &plan,
-                        void *ws, void **result, hipStream_t s);
-// Stable LSD sort of 64-bit words by their bits [low, low + bits); the result
-// ends in *result (a or b).  ws: radix_words_ws_bytes(count).
-size_t radix_words_ws_bytes(size_t count);
+hipError_t radix_sort16(void *a, void *b, size_t count, const DigitPlan &plan, void *ws,
+                        void **result, hipStream_t s);
+// Stable LSD sorts in 9-bit digits, ws: radix_digits_ws_bytes(count).  64-bit
+// words by their bits [low, low + bits); the result ends in *result (a or b).
+size_t radix_digits_ws_bytes(size_t count);
 hipError_t radix_sort_words(uint64_t *a, uint64_t *b, uint32_t count, uint32_t low, uint32_t bits,
                             void *ws, uint64_t **result, hipStream_t s);
+// (key, index) items by the key's low `bits` bits (the same result).
+hipError_t radix_sort_keyed(KV *a, KV *b, uint32_t count, uint32_t bits, void *ws,
+                            const KV **result, hipStream_t s);
+// Records in (i, j, t_lo, t_hi) order, from `in` (kept unless it is b) over a
+// and b; *result is one of the three.  Widths: bits of each field; dur: of
+// t_hi - t_lo, never negative, or with as_end of t_hi itself.
+struct RecWidths {
+    uint32_t dur, tlo, j, i;
+    bool as_end;
+};
+hipError_t radix_sort_records(const Rec *in, Rec *a, Rec *b, uint32_t count,
+                              const RecWidths &w, void *ws, const Rec **result, hipStream_t s);
+// part[kRecParts][kRecFields]: ORs of i, j, t_lo, t_hi - t_lo and of t_hi < t_lo
+// over the records of each of kRecParts workgroups.
+constexpr int kRecParts = 512, kRecFields = 5;
+hipError_t launch_rec_widths(const Rec *in, uint32_t count, uint32_t *part, hipStream_t s);
 // One workgroup per slab: compute the Morton codes of the slab's boxes, sort
 // (code, box index) inside LDS and write 64-bit keys (slab << 32 | code) and
 // box indices in sorted order.  err bit 1: a box's t0 is outside its slab.

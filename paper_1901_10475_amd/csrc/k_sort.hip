@@ -1,11 +1,13 @@
 // k_sort.hip -- fills, device-wide exclusive scan, stable LSD radix sorts.
 //
 // Radix sorts:
-//   * radix_sort16 / radix_sort_words: device-wide, stable, over 16-byte items
-//     (key/value pairs or pair records) in 8-bit digits, or 8-byte ones (a key
-//     and its box index packed in one word) in 9-bit digits, one histogram +
-//     scan + scatter per digit.  They sort tree keys when boxes are not grouped
-//     in slabs and put pair records in canonical order.
+//   * radix_sort_words / _keyed / _records: device-wide, stable, over 8-byte
+//     items (a key and its box index packed in one word), (key, index) pairs or
+//     pair records in 9-bit digits, one histogram + scan + scatter per digit.
+//     They sort tree keys when boxes are not grouped in slabs and put pair
+//     records in canonical order.
+//   * radix_sort16: the same in 8-bit digits and less scratch, for the small
+//     (key, index) lists of the band graph.
 //   * k_slab_build: one 1024-thread workgroup per time slab; keys stay in
 //     registers and move through LDS between digit passes, so a slab of up to
 //     kSegCap boxes is sorted with one read and one write of global memory.
@@ -143,14 +145,6 @@ struct DigitKV {
         return (uint32_t)(key >> shift) & 0xFFu;
     }
 };
-struct DigitRec {
-    uint32_t field, shift;
-    __device__ uint32_t operator()(const uint4 &it) const
-    {
-        uint32_t v = field == 0 ? it.x : field == 1 ? it.y : field == 2 ? it.z : it.w;
-        return (v >> shift) & 0xFFu;
-    }
-};
 // Digit counts of one tile.  Lanes count into one of 16 copies of the
 // histogram (by lane mod 16, rows of 257 words so that the copies of one
 // digit sit in different banks): a tile whose items share a digit (a slab
@@ -250,7 +244,7 @@ size_t radix_ws_bytes(size_t count)
     return align_up(h * sizeof(uint32_t), 256) + scan_ws_bytes(h);
 }
 
-hipError_t radix_sort16(SortKind kind, void *a, void *b, size_t count, const DigitPlan &plan,
+hipError_t radix_sort16(void *a, void *b, size_t count, const DigitPlan &plan,
                         void *ws, void **result, hipStream_t s)
 {
     *result = a;
@@ -262,25 +256,14 @@ hipError_t radix_sort16(SortKind kind, void *a, void *b, size_t count, const Dig
     void *sws = (char *)ws + align_up(h * sizeof(uint32_t), 256);
     uint4 *src = (uint4 *)a, *dst = (uint4 *)b;
     for (int p = 0; p < plan.npass; ++p) {
-        if (kind == SORT_KV) {
-            DigitKV dg{plan.shift[p]};
-            k_radix_upsweep<<<nb, kRadThreads, 0, s>>>(src, count, dg, hist, nb);
-        } else {
-            DigitRec dg{plan.field[p], plan.shift[p]};
-            k_radix_upsweep<<<nb, kRadThreads, 0, s>>>(src, count, dg, hist, nb);
-        }
+        const DigitKV dg{plan.shift[p]};
+        k_radix_upsweep<<<nb, kRadThreads, 0, s>>>(src, count, dg, hist, nb);
         hipError_t e = hipGetLastError();
         if (e == hipSuccess)
             e = scan_exclusive_u32(hist, hist, h, sws, s);
         if (e != hipSuccess)
             return e;
-        if (kind == SORT_KV) {
-            DigitKV dg{plan.shift[p]};
-            k_radix_downsweep<<<nb, kRadThreads, 0, s>>>(src, dst, count, dg, hist, nb);
-        } else {
-            DigitRec dg{plan.field[p], plan.shift[p]};
-            k_radix_downsweep<<<nb, kRadThreads, 0, s>>>(src, dst, count, dg, hist, nb);
-        }
+        k_radix_downsweep<<<nb, kRadThreads, 0, s>>>(src, dst, count, dg, hist, nb);
         e = hipGetLastError();
         if (e != hipSuccess)
             return e;
@@ -292,67 +275,91 @@ hipError_t radix_sort16(SortKind kind, void *a, void *b, size_t count, const Dig
     return hipSuccess;
 }
 
-// ---- device-wide LSD radix sort of 64-bit words ------------------------------------------
+// ---- device-wide LSD radix sort of words, keyed items and records ------------------------
 //
-// Digits of 9 or 10 bits, so that the 37 bits left above a 27-bit box index
-// take four passes.  Per pass: k_words_up counts each tile's digits into a row,
-// k_words_rows turns every kWordsChunk rows into prefixes and their sum,
-// k_words_chunks the sums into prefixes over the chunks and digit totals, and
-// k_words_down ranks a tile's words, stages them in LDS in digit order and
-// writes each digit's run in consecutive lanes (16 words on average: whole
-// lines, where the 16-byte sort's direct scatter writes single words).
-// Bound: HBM, 24 bytes a word and pass, and in the scatter the ranking (some 40
-// instructions a word).  37 bits of 79.7 M words: counts 3.9 TB/s, scatter 4.1
+// Items of 8 or 16 bytes, digits of 9 or 10 bits, so that the 37 bits left above
+// a 27-bit box index take four passes.  Per pass: k_digits_up counts each tile's
+// digits into a row, k_digits_rows turns every kDigitChunk rows into prefixes
+// and their sum, k_digits_chunks the sums into prefixes over the chunks and
+// digit totals, and k_digits_down ranks a tile's items, stages them in LDS in
+// digit order and writes each digit's run in consecutive lanes (128 bytes on
+// average).
+// Bound: HBM, three times the item's size a pass, and in the scatter the ranking
+// (some 40 instructions an item).  37 bits of 79.7 M words: counts 3.9 TB/s, scatter 4.1
 // (9 bits) and 3.0 (10), 2.06 ms in all; the 16-byte sort's form with 8-byte
 // items, 8-bit digits and 4 096-word tiles took 2.65 (five passes, counts 3.4,
 // scatter 4.1 TB/s, 36 us of scans a pass).
-constexpr int kWordsThreads = 512, kWordsWaves = kWordsThreads / 64, kWordsChunk = 64;
-template <int BITS>
-struct Words {
+constexpr int kDigitThreads = 512, kDigitWaves = kDigitThreads / 64, kDigitChunk = 64;
+template <int BITS, class Item>
+struct Digits {
     static constexpr int kBins = 1 << BITS;
     // two workgroups' LDS on a CU
-    static constexpr int kItems = BITS == 9 ? 16 : 14;
-    static constexpr int kTile = kWordsThreads * kItems;
-    static constexpr int kPer = kBins / kWordsThreads;   // digits per lane
+    static constexpr int kItems = (BITS == 9 ? 128 : 112) / (int)sizeof(Item);
+    static constexpr int kTile = kDigitThreads * kItems;
+    static constexpr int kPer = kBins / kDigitThreads;   // digits per lane
     static constexpr int kCopies = BITS == 9 ? 8 : 4;    // of the counters
 };
 
-// Digit counts of one tile (Words<BITS>::kCopies histograms by lane, rows of
+// Digits of `mask`'s width.  A word's bits from `shift` on.
+struct DigitWord {
+    uint32_t shift, mask;
+    __device__ uint32_t operator()(uint64_t v) const { return (uint32_t)(v >> shift) & mask; }
+};
+// A (64-bit key, index) item's key bits from `shift` on.
+struct DigitKey {
+    uint32_t shift, mask;
+    __device__ uint32_t operator()(const uint4 &v) const
+    {
+        return (uint32_t)(((uint64_t)v.y << 32 | v.x) >> shift) & mask;
+    }
+};
+// A record as one number, from the lowest field: t_hi (as the duration t_hi -
+// t_lo, which keeps the order and takes fewer bits, or itself), t_lo, j, i, in
+// `dur`, low - dur, j and whatever bits (t_lo and j cut to theirs: the filler of
+// unused slots has every bit set); its bits from `shift` on.
+struct DigitRec {
+    uint32_t dur, low, j, tlo_mask, j_mask, as_end, shift, mask;
+    __device__ uint32_t operator()(const uint4 &v) const
+    {
+        const uint64_t t = (uint64_t)(v.z & tlo_mask) << dur | (as_end ? v.w : v.w - v.z);
+        const uint64_t ids = (uint64_t)v.x << j | (v.y & j_mask);
+        // a digit that straddles the two words takes its upper bits from ids
+        const uint64_t at = shift >= low ? ids >> (shift - low)
+                            : shift + 10 > low ? t >> shift | ids << (low - shift)
+                                               : t >> shift;
+        return (uint32_t)at & mask;
+    }
+};
+
+// Digit counts of one tile (kCopies histograms by lane, rows of
 // kBins + 1 words so that the copies of one digit sit in different banks).
-template <int BITS>
-__global__ __launch_bounds__(kWordsThreads) void k_words_up(const uint64_t *__restrict__ in,
-                                                            uint32_t count, uint32_t shift,
-                                                            uint32_t mask,
-                                                            uint32_t *__restrict__ rows)
+template <int BITS, class Item, class Digit>
+__global__ __launch_bounds__(kDigitThreads) void k_digits_up(const Item *__restrict__ in,
+                                                             uint32_t count, Digit digit,
+                                                             uint32_t *__restrict__ rows)
 {
-    using W = Words<BITS>;
+    using W = Digits<BITS, Item>;
     constexpr int kRow = W::kBins + 1;
     __shared__ uint32_t h[W::kCopies * kRow];
-    // word pairs (their order does not matter here), every load in flight before
-    // the first count; the place of word k of this lane is
-    // base + (k / 2 kWordsThreads + threadIdx.x) 2 + k % 2
-    const uint32_t base = blockIdx.x * (uint32_t)W::kTile + 2 * threadIdx.x;
-    const uint32_t pairs = count / 2;
-    uint64_t v[W::kItems];
+    const uint32_t base = blockIdx.x * (uint32_t)W::kTile + threadIdx.x;
+    Item v[W::kItems];
 #pragma unroll
-    for (int k = 0; k < W::kItems; k += 2) {
-        const uint32_t p = base / 2 + k / 2 * kWordsThreads;
-        const ulonglong2 x = reinterpret_cast<const ulonglong2 *>(in)[p < pairs ? p : 0];
-        v[k] = p < pairs ? x.x : in[count - 1];   // the last word of an odd count
-        v[k + 1] = x.y;
+    for (int k = 0; k < W::kItems; ++k) {   // every load in flight before the first count
+        const uint32_t g = base + k * kDigitThreads;
+        v[k] = in[g < count ? g : count - 1];
     }
-    for (int k = threadIdx.x; k < W::kCopies * kRow; k += kWordsThreads)
+    for (int k = threadIdx.x; k < W::kCopies * kRow; k += kDigitThreads)
         h[k] = 0;
     __syncthreads();
     uint32_t *const mine = h + (threadIdx.x % W::kCopies) * kRow;
 #pragma unroll
     for (int k = 0; k < W::kItems; ++k)
-        if (base + k / 2 * 2 * kWordsThreads + k % 2 < count)
-            atomicAdd(&mine[(uint32_t)(v[k] >> shift) & mask], 1u);
+        if (base + k * kDigitThreads < count)
+            atomicAdd(&mine[digit(v[k])], 1u);
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < W::kPer; ++q) {
-        const int d = q * kWordsThreads + threadIdx.x;
+        const int d = q * kDigitThreads + threadIdx.x;
         uint32_t sum = 0;
 #pragma unroll
         for (int c = 0; c < W::kCopies; ++c)
@@ -361,15 +368,15 @@ __global__ __launch_bounds__(kWordsThreads) void k_words_up(const uint64_t *__re
     }
 }
 
-// Rows [c kWordsChunk, ...) of one chunk: each count becomes the sum of those of
+// Rows [c kDigitChunk, ...) of one chunk: each count becomes the sum of those of
 // the chunk's earlier rows, the chunk's total goes to sums[c].
 template <int BITS>
-__global__ __launch_bounds__(256) void k_words_rows(uint32_t *__restrict__ rows, uint32_t tiles,
+__global__ __launch_bounds__(256) void k_digits_rows(uint32_t *__restrict__ rows, uint32_t tiles,
                                                     uint32_t *__restrict__ sums)
 {
-    constexpr int kBins = Words<BITS>::kBins, kBatch = 16;
-    const uint32_t d = blockIdx.y * 256 + threadIdx.x, r0 = blockIdx.x * kWordsChunk;
-    const uint32_t n = tiles - r0 < (uint32_t)kWordsChunk ? tiles - r0 : (uint32_t)kWordsChunk;
+    constexpr int kBins = 1 << BITS, kBatch = 16;
+    const uint32_t d = blockIdx.y * 256 + threadIdx.x, r0 = blockIdx.x * kDigitChunk;
+    const uint32_t n = tiles - r0 < (uint32_t)kDigitChunk ? tiles - r0 : (uint32_t)kDigitChunk;
     uint32_t run = 0;
     for (uint32_t k = 0; k < n; k += kBatch) {
         uint32_t v[kBatch];
@@ -389,9 +396,9 @@ __global__ __launch_bounds__(256) void k_words_rows(uint32_t *__restrict__ rows,
 // One wave per digit: its sums over the chunks become prefixes, the total goes
 // to the row after the last chunk's.
 template <int BITS>
-__global__ __launch_bounds__(256) void k_words_chunks(uint32_t *__restrict__ sums, uint32_t chunks)
+__global__ __launch_bounds__(256) void k_digits_chunks(uint32_t *__restrict__ sums, uint32_t chunks)
 {
-    constexpr int kBins = Words<BITS>::kBins;
+    constexpr int kBins = 1 << BITS;
     const uint32_t d = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     uint32_t run = 0;
     for (uint32_t c0 = 0; c0 < chunks; c0 += 64) {
@@ -406,22 +413,21 @@ __global__ __launch_bounds__(256) void k_words_chunks(uint32_t *__restrict__ sum
         sums[(size_t)chunks * kBins + d] = run;
 }
 
-template <int BITS>
-__global__ __launch_bounds__(kWordsThreads) void k_words_down(
-    const uint64_t *__restrict__ in, uint64_t *__restrict__ out, uint32_t count, uint32_t shift,
-    uint32_t mask, const uint32_t *__restrict__ rows, const uint32_t *__restrict__ sums,
-    uint32_t chunks)
+template <int BITS, class Item, class Digit>
+__global__ __launch_bounds__(kDigitThreads) void k_digits_down(
+    const Item *__restrict__ in, Item *__restrict__ out, uint32_t count, Digit digit,
+    const uint32_t *__restrict__ rows, const uint32_t *__restrict__ sums, uint32_t chunks)
 {
-    using W = Words<BITS>;
-    __shared__ uint64_t stage[W::kTile];
-    __shared__ uint16_t cnt[kWordsWaves][W::kBins + 2];   // per wave and digit
-    __shared__ uint32_t to[W::kBins];                     // place of staged word 0 by digit
+    using W = Digits<BITS, Item>;
+    __shared__ Item stage[W::kTile];
+    __shared__ uint16_t cnt[kDigitWaves][W::kBins + 2];   // per wave and digit
+    __shared__ uint32_t to[W::kBins];                     // place of staged item 0 by digit
     __shared__ uint32_t wsum[33];
     const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const uint32_t base = blockIdx.x * (uint32_t)W::kTile;
     const uint32_t m = count - base < (uint32_t)W::kTile ? count - base : (uint32_t)W::kTile;
     const uint32_t k0 = w * 64 * W::kItems + lane;
-    uint64_t item[W::kItems];
+    Item item[W::kItems];
     uint32_t rank[W::kItems];
 #pragma unroll
     for (int j = 0; j < W::kItems; ++j) {   // every load in flight before the ranking
@@ -434,18 +440,18 @@ __global__ __launch_bounds__(kWordsThreads) void k_words_down(
     for (int q = 0; q < W::kPer; ++q) {
         place[q] = rows[(size_t)blockIdx.x * W::kBins + d0 + q];
         if (chunks > 1)
-            place[q] += sums[(size_t)(blockIdx.x / kWordsChunk) * W::kBins + d0 + q];
+            place[q] += sums[(size_t)(blockIdx.x / kDigitChunk) * W::kBins + d0 + q];
         all[q] = sums[(chunks > 1 ? (size_t)chunks * W::kBins : 0) + d0 + q];
     }
-    for (uint32_t k = threadIdx.x; k < (uint32_t)(kWordsWaves * (W::kBins + 2) / 2);
-         k += kWordsThreads)
+    for (uint32_t k = threadIdx.x; k < (uint32_t)(kDigitWaves * (W::kBins + 2) / 2);
+         k += kDigitThreads)
         reinterpret_cast<uint32_t *>(&cnt[0][0])[k] = 0;
     __syncthreads();
     const uint64_t lt = lanemask_lt();
 #pragma unroll
     for (int j = 0; j < W::kItems; ++j) {
         const bool valid = k0 + j * 64 < m;
-        const uint32_t d = (uint32_t)(item[j] >> shift) & mask;
+        const uint32_t d = digit(item[j]);
         const uint64_t peers = match_digit<BITS>(d, __ballot(valid));
         const uint32_t c = cnt[w][d], mine = (uint32_t)__popcll(peers & lt);
         if (valid && mine == 0)
@@ -458,7 +464,7 @@ __global__ __launch_bounds__(kWordsThreads) void k_words_down(
 #pragma unroll
         for (int q = 0; q < W::kPer; ++q) {
             n[q] = 0;
-            for (int ww = 0; ww < kWordsWaves; ++ww)
+            for (int ww = 0; ww < kDigitWaves; ++ww)
                 n[q] += cnt[ww][d0 + q];
             words += n[q];
             before += all[q];
@@ -471,7 +477,7 @@ __global__ __launch_bounds__(kWordsThreads) void k_words_down(
             to[d0 + q] = first + place[q] - start;
             first += all[q];
             uint32_t run = start;
-            for (int ww = 0; ww < kWordsWaves; ++ww) {
+            for (int ww = 0; ww < kDigitWaves; ++ww) {
                 const uint32_t t = cnt[ww][d0 + q];
                 cnt[ww][d0 + q] = (uint16_t)run;
                 run += t;
@@ -483,53 +489,56 @@ __global__ __launch_bounds__(kWordsThreads) void k_words_down(
 #pragma unroll
     for (int j = 0; j < W::kItems; ++j)
         if (k0 + j * 64 < m)
-            stage[cnt[w][(uint32_t)(item[j] >> shift) & mask] + rank[j]] = item[j];
+            stage[cnt[w][digit(item[j])] + rank[j]] = item[j];
     __syncthreads();
-    for (uint32_t k = threadIdx.x; k < m; k += kWordsThreads) {
-        const uint64_t v = stage[k];
-        const uint32_t at = to[(uint32_t)(v >> shift) & mask] + k;
+    for (uint32_t k = threadIdx.x; k < m; k += kDigitThreads) {
+        const Item v = stage[k];
+        const uint32_t at = to[digit(v)] + k;
         if (at < count)
             out[at] = v;
     }
 }
 
 namespace {
-// Rows of the narrowest tiles with the most bins, their chunks' sums, the totals.
-size_t words_tiles(size_t count) { return (count + Words<10>::kTile - 1) / Words<10>::kTile; }
-size_t words_chunks(size_t tiles) { return (tiles + kWordsChunk - 1) / kWordsChunk; }
+uint32_t digit_chunks(uint32_t tiles) { return (tiles + kDigitChunk - 1) / kDigitChunk; }
+// Rows, chunk sums and totals of one pass (one chunk's sums are the totals).
+template <int BITS, class Item>
+size_t digit_bytes(size_t count)
+{
+    const uint32_t tiles = nblk(count, Digits<BITS, Item>::kTile), chunks = digit_chunks(tiles);
+    return ((size_t)tiles + chunks + (chunks > 1 ? 1 : 0)) * (4u << BITS);
+}
 }  // namespace
 
-size_t radix_words_ws_bytes(size_t count)
+size_t radix_digits_ws_bytes(size_t count)
 {
-    const size_t tiles = words_tiles(count);
-    const size_t chunks = words_chunks(tiles);   // (one chunk's sums are the totals)
-    return (tiles + chunks + (chunks > 1 ? 1 : 0)) * Words<10>::kBins * sizeof(uint32_t);
+    const size_t a = digit_bytes<10, uint64_t>(count), b = digit_bytes<9, uint4>(count);
+    return a > b ? a : b;
 }
 
-template <int BITS>
-static hipError_t words_pass(const uint64_t *src, uint64_t *dst, uint32_t count, uint32_t shift,
-                             uint32_t bits, uint32_t *rows, hipStream_t s)
+template <int BITS, class Item, class Digit>
+static hipError_t digit_pass(const Item *src, Item *dst, uint32_t count, const Digit &digit,
+                             uint32_t *rows, hipStream_t s)
 {
-    using W = Words<BITS>;
-    const uint32_t tiles = nblk(count, W::kTile), chunks = (uint32_t)words_chunks(tiles);
-    const uint32_t mask = (1u << bits) - 1;
+    using W = Digits<BITS, Item>;
+    const uint32_t tiles = nblk(count, W::kTile), chunks = digit_chunks(tiles);
     uint32_t *const sums = rows + (size_t)tiles * W::kBins;
-    k_words_up<BITS><<<tiles, kWordsThreads, 0, s>>>(src, count, shift, mask, rows);
+    k_digits_up<BITS><<<tiles, kDigitThreads, 0, s>>>(src, count, digit, rows);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return e;
-    k_words_rows<BITS><<<dim3(chunks, W::kBins / 256), 256, 0, s>>>(rows, tiles, sums);
+    k_digits_rows<BITS><<<dim3(chunks, W::kBins / 256), 256, 0, s>>>(rows, tiles, sums);
     e = hipGetLastError();
     if (e != hipSuccess)
         return e;
     if (chunks > 1) {
-        k_words_chunks<BITS><<<W::kBins / 4, 256, 0, s>>>(sums, chunks);
+        k_digits_chunks<BITS><<<W::kBins / 4, 256, 0, s>>>(sums, chunks);
         e = hipGetLastError();
         if (e != hipSuccess)
             return e;
     }
-    k_words_down<BITS><<<tiles, kWordsThreads, 0, s>>>(src, dst, count, shift, mask, rows, sums,
-                                                       chunks);
+    k_digits_down<BITS><<<tiles, kDigitThreads, 0, s>>>(src, dst, count, digit, rows, sums,
+                                                        chunks);
     return hipGetLastError();
 }
 
@@ -546,8 +555,9 @@ hipError_t radix_sort_words(uint64_t *a, uint64_t *b, uint32_t count, uint32_t l
     uint64_t *src = a, *dst = b;
     for (uint32_t p = 0; p < passes; ++p) {
         const uint32_t left = passes - p, take = (bits + left - 1) / left;
-        hipError_t e = take > 9 ? words_pass<10>(src, dst, count, low, take, (uint32_t *)ws, s)
-                                : words_pass<9>(src, dst, count, low, take, (uint32_t *)ws, s);
+        const DigitWord d{low, (1u << take) - 1};
+        hipError_t e = take > 9 ? digit_pass<10>(src, dst, count, d, (uint32_t *)ws, s)
+                                : digit_pass<9>(src, dst, count, d, (uint32_t *)ws, s);
         if (e != hipSuccess)
             return e;
         low += take;
@@ -558,6 +568,94 @@ hipError_t radix_sort_words(uint64_t *a, uint64_t *b, uint32_t count, uint32_t l
     }
     *result = src;
     return hipSuccess;
+}
+
+// Passes of 9-bit digits over `bits` bits of 16-byte items, from `in` (kept) to
+// a, b, a, ...
+template <class Make>
+static hipError_t sort_items16(const void *in, void *a, void *b, uint32_t count, uint32_t bits,
+                               void *ws, const void **result, hipStream_t s, Make &&make)
+{
+    *result = in;
+    if (count <= 1)
+        return hipSuccess;
+    const uint4 *src = (const uint4 *)in;
+    uint4 *dst = (uint4 *)a, *next = (uint4 *)b;
+    for (uint32_t low = 0; low < bits;) {
+        const uint32_t left = (bits - low + 8) / 9, take = (bits - low + left - 1) / left;
+        hipError_t e = digit_pass<9>(src, dst, count, make(low, (1u << take) - 1),
+                                     (uint32_t *)ws, s);
+        if (e != hipSuccess)
+            return e;
+        low += take;
+        src = dst;
+        uint4 *t = dst;
+        dst = next;
+        next = t;
+    }
+    *result = src;
+    return hipSuccess;
+}
+
+hipError_t radix_sort_keyed(KV *a, KV *b, uint32_t count, uint32_t bits, void *ws,
+                            const KV **result, hipStream_t s)
+{
+    const void *res = nullptr;
+    hipError_t e = sort_items16(a, b, a, count, bits, ws, &res, s, [](uint32_t low, uint32_t mask) {
+        return DigitKey{low, mask};
+    });
+    *result = (const KV *)res;
+    return e;
+}
+
+hipError_t radix_sort_records(const Rec *in, Rec *a, Rec *b, uint32_t count,
+                              const RecWidths &w, void *ws, const Rec **result, hipStream_t s)
+{
+    if (w.dur > 32 || w.tlo > 32 || w.j > 32 || w.i > 32)
+        return hipErrorInvalidValue;
+    const void *res = nullptr;
+    hipError_t e = sort_items16(
+        in, a, b, count, w.dur + w.tlo + w.j + w.i, ws, &res, s,
+        [&](uint32_t low, uint32_t mask) {
+            return DigitRec{w.dur, w.dur + w.tlo, w.j, (uint32_t)((1ull << w.tlo) - 1),
+                            (uint32_t)((1ull << w.j) - 1), w.as_end ? 1u : 0u, low, mask};
+        });
+    *result = (const Rec *)res;
+    return e;
+}
+
+// Per workgroup, the OR of every field of its records: i, j, t_lo, the duration
+// t_hi - t_lo, and 1 if one is negative.
+__global__ __launch_bounds__(256) void k_rec_widths(const Rec *__restrict__ in, uint32_t count,
+                                                    uint32_t *__restrict__ part)
+{
+    __shared__ uint32_t red[4][kRecFields];
+    uint32_t v[kRecFields] = {0, 0, 0, 0, 0};
+    for (uint64_t k = (uint64_t)blockIdx.x * 256 + threadIdx.x; k < count;
+         k += (uint64_t)gridDim.x * 256) {
+        const Rec r = in[k];
+        v[0] |= r.i;
+        v[1] |= r.j;
+        v[2] |= r.tlo;
+        v[3] |= r.thi - r.tlo;
+        v[4] |= r.thi < r.tlo ? 1u : 0u;
+    }
+    for (int f = 0; f < kRecFields; ++f) {
+        for (int o = 32; o >= 1; o >>= 1)
+            v[f] |= __shfl_xor(v[f], o, 64);
+        if ((threadIdx.x & 63) == 0)
+            red[threadIdx.x >> 6][f] = v[f];
+    }
+    __syncthreads();
+    if (threadIdx.x < (uint32_t)kRecFields)
+        part[blockIdx.x * kRecFields + threadIdx.x] = red[0][threadIdx.x] | red[1][threadIdx.x] |
+                                                      red[2][threadIdx.x] | red[3][threadIdx.x];
+}
+
+hipError_t launch_rec_widths(const Rec *in, uint32_t count, uint32_t *part, hipStream_t s)
+{
+    k_rec_widths<<<kRecParts, 256, 0, s>>>(in, count, part);
+    return hipGetLastError();
 }
 
 // ---- per-slab LDS radix sort ---------------------------------------------------------

@@ -149,3 +149,30 @@ def test_canonical_records_of_ranked_runs(count, values):
     t = torch.from_numpy(rec.view(np.int32)).cuda()
     got = cd.cd_canonical_records(t, 3000, 300).cpu().numpy().view(np.uint32)
     assert np.array_equal(got, np.unique(rec, axis=0))
+
+
+@pytest.mark.parametrize("count", [262145, 266241, 300001])
+@pytest.mark.parametrize("kind", ["zero", "one_field", "negative", "wide", "straddle"])
+def test_canonical_records_by_the_bits_they_use(count, kind):
+    """The many-record sort over the widths found in the records: none at all,
+    only one field, end times before t_lo (the field itself is sorted, not the
+    duration), all 32 bits of every field but the ids' 17, and widths whose
+    9-bit digits straddle two fields."""
+    need_gpu()
+    rng = np.random.default_rng(count)
+    rec = np.zeros((count, 4), np.uint64)
+    if kind == "one_field":
+        rec[:, 1] = rng.integers(0, 1 << 17, count)
+    elif kind == "negative":
+        rec[:] = rng.integers(0, 300, (count, 4))
+    elif kind == "wide":
+        rec[:, :2] = rng.integers(0, 1 << 17, (count, 2))
+        rec[:, 2:] = rng.integers(0, 1 << 32, (count, 2), dtype=np.uint64)
+    elif kind == "straddle":
+        rec[:, :2] = rng.integers(0, 37, (count, 2))
+        rec[:, 2] = rng.integers(0, 1 << 21, count)
+        rec[:, 3] = rec[:, 2] + rng.integers(0, 9, count).astype(np.uint64)
+    rec = rec.astype(np.uint32)
+    t = torch.from_numpy(rec.view(np.int32)).cuda()
+    got = cd.cd_canonical_records(t, (1 << 32) - 2, 1 << 17).cpu().numpy().view(np.uint32)
+    assert np.array_equal(got, np.unique(rec, axis=0))
