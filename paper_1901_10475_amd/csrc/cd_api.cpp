@@ -1729,14 +1729,15 @@ int cd_canonical_records(const cd_pair *in, int64_t count, uint32_t horizon_tick
 // ---- learned per-object step ---------------------------------------------------------
 
 struct MlpWS {
-    float *act, *part;
+    float *part;
 };
 size_t layout_mlp(void *base, size_t bytes, int64_t B, MlpWS *w)
 {
     Carve c(base, bytes);
-    uint64_t nblk = ((uint64_t)B + kMlpOuterSamples - 1) / kMlpOuterSamples;
-    w->act = c.take<float>((size_t)258 * (size_t)B);
-    w->part = c.take<float>((size_t)nblk * (kMlpParams + 1));
+    // the partial gradients, in a workspace of the size callers have always been
+    // asked for: 258 floats a sample and a partial for every 128 samples
+    w->part = (float *)c.take_bytes(align_up((size_t)258 * (size_t)B * sizeof(float), 256) +
+                                    ((size_t)B + 127) / 128 * (kMlpParams + 1) * sizeof(float));
     return c.off;
 }
 
@@ -1806,7 +1807,7 @@ int cd_mlp_grad(const float *w, const float *x, const float *target, int64_t bat
         return fail(CD_E_WORKSPACE, "mlp workspace too small");
     MlpWS m;
     layout_mlp(ws, ws_bytes, batch, &m);
-    CD_HIP(launch_mlp_grad(w, x, target, (uint32_t)batch, m.act, m.part, grad_out, loss_out,
+    CD_HIP(launch_mlp_grad(w, x, target, (uint32_t)batch, m.part, grad_out, loss_out,
                            (hipStream_t)stream));
     return debug_sync((hipStream_t)stream, "cd_mlp_grad");
 }

@@ -303,8 +303,6 @@ constexpr int kMlpB2 = kMlpW2 + kMlpHid * kMlpHid;
 constexpr int kMlpW3 = kMlpB2 + kMlpHid;
 constexpr int kMlpB3 = kMlpW3 + kMlpHid;
 constexpr int kMlpParams = kMlpB3 + 1;   // 4609
-constexpr int kMlpOuterThreads = 256;
-constexpr int kMlpOuterSamples = 128;    // samples per outer-product block
 
 // ---- launchers (each returns the launch status) -----------------------------
 
@@ -355,9 +353,10 @@ hipError_t launch_dt_mlp(const cd_elements &el, const uint16_t *w, double mu, do
                          hipStream_t s);
 hipError_t launch_mlp_forward(const float *w, const float *x, uint32_t B, float *y,
                               hipStream_t s);
-// act: [4 * 64 + 1][B] (h1, dz1, h2, dz2, dy), part: [blocks][kMlpParams + 1]
+// part: [mlp_grad_blocks(B)][kMlpParams + 1]
+uint32_t mlp_grad_blocks(uint32_t B);
 hipError_t launch_mlp_grad(const float *w, const float *x, const float *target, uint32_t B,
-                           float *act, float *part, float *grad, float *loss, hipStream_t s);
+                           float *part, float *grad, float *loss, hipStream_t s);
 hipError_t launch_mlp_adam(float *w, float *m, float *v, const float *g, int64_t step,
                            float lr, float beta1, float beta2, float eps, uint16_t *w_bf16,
                            hipStream_t s);

@@ -14,10 +14,9 @@
 // Inference runs one object per lane: BF16 weights staged in LDS (read as
 // wave-uniform broadcasts), BF16 inputs and hidden activations packed two to a
 // register, FP32 accumulation through v_dot2c_f32_bf16.  Training keeps FP32
-// master weights: one kernel runs the forward and backward pass per sample and
-// writes the activations and their gradients feature-major; a second forms the
-// per-parameter outer-product sums over a block of samples in LDS; a third adds
-// the block partials in a fixed order, so gradients are deterministic.
+// master weights: one kernel runs the forward and backward pass and sums the
+// gradients of its samples, on the FP32 matrix instructions; a second adds the
+// partial gradients in a fixed order, so gradients are deterministic.
 #include "cd_internal.h"
 
 namespace cd {
@@ -225,164 +224,216 @@ __global__ __launch_bounds__(256) void k_mlp_forward(const float *__restrict__ w
     y[b] = out;
 }
 
-// Rows of the activation array (each B long).
-constexpr int kActH1 = 0, kActDZ1 = 64, kActH2 = 128, kActDZ2 = 192, kActDY = 256,
-              kActSQ = 257, kActRows = 258;
+// Gradients: forward and backward pass and the per-parameter sums in one kernel,
+// 64 samples (a tile) at a time, activations and their gradients in LDS.  The
+// three 64 x 64 x 64 products of a tile -- z2 = h1 W2^T, dh1 = dz2 W2 and
+// gW2 = dz2^T h1 -- run on the FP32 matrix instructions (32 x 32 x 2, one
+// quadrant a wave; gW2 accumulates in registers over the workgroup's tiles), the
+// small sums on the lanes.  Rows of 65 words: lanes along a row and along a
+// column both meet different banks.
+// Bound: latency; a workgroup alone takes 12 us for a tile, 2.6 of them matrix
+// instructions, so up to three share a CU.  33 696 samples: 24 us, and 4 for the
+// sum of the partials (264 workgroups of two tiles 27); a kernel that kept 258
+// rows of activations in memory and another for their outer products by scalar
+// FMA took 145, the serial sum of 264 partials 63.  Error of the gradient against
+// 64 bits there 5.8e-8, before 1.7e-7.
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-// Per sample: forward, loss term (y - t)^2 / B and the backward pass to the
-// pre-activation gradients dz1, dz2 and dy.
-__global__ __launch_bounds__(256) void k_mlp_backprop(const float *__restrict__ w,
-                                                      const float *__restrict__ x,
-                                                      const float *__restrict__ target,
-                                                      uint32_t B, float *__restrict__ act)
+constexpr int kGradTile = 64, kGradRow = 65, kGradThreads = 256, kGradWaves = kGradThreads / 64,
+              kGradSpan = kGradTile / kGradWaves;   // samples (or terms) of a wave
+// Workgroups, and so partial gradients, at most (three on a CU), with equal
+// numbers of tiles.
+uint32_t mlp_grad_blocks(uint32_t B)
 {
-    __shared__ MlpF32 s;
-    load_mlp_f32(s, w);
-    uint32_t b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= B)
-        return;
-    float xv[kMlpIn], h1[kMlpHid];
-    for (int c = 0; c < kMlpIn; ++c)
-        xv[c] = x[(uint64_t)b * kMlpIn + c];
-    mlp_layer1(s, xv, h1);
-    float y = s.b3;
-#pragma unroll 1
-    for (int r = 0; r < kMlpHid; ++r)
-        y = fmaf(s.w3[r], fmaxf(mlp_row2(s, r, h1), 0.0f), y);
-    float res = y - target[b];
-    float dy = 2.0f * res / (float)B;
-    act[(uint64_t)kActDY * B + b] = dy;
-    act[(uint64_t)kActSQ * B + b] = res * res / (float)B;
-    // second pass: recompute each h2 row (cheaper than holding 64 more
-    // registers), then accumulate dh1 = W2^T dz2
-    float dh1[kMlpHid];
-#pragma unroll
-    for (int k = 0; k < kMlpHid; ++k)
-        dh1[k] = 0.0f;
-#pragma unroll 1
-    for (int r = 0; r < kMlpHid; ++r) {
-        float h2 = fmaxf(mlp_row2(s, r, h1), 0.0f);
-        float dz2 = h2 > 0.0f ? dy * s.w3[r] : 0.0f;
-        act[(uint64_t)(kActH2 + r) * B + b] = h2;
-        act[(uint64_t)(kActDZ2 + r) * B + b] = dz2;
-#pragma unroll
-        for (int q = 0; q < kMlpHid / 4; ++q) {
-            float4 wv = s.W2[r][q];
-            dh1[4 * q + 0] = fmaf(dz2, wv.x, dh1[4 * q + 0]);
-            dh1[4 * q + 1] = fmaf(dz2, wv.y, dh1[4 * q + 1]);
-            dh1[4 * q + 2] = fmaf(dz2, wv.z, dh1[4 * q + 2]);
-            dh1[4 * q + 3] = fmaf(dz2, wv.w, dh1[4 * q + 3]);
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < kMlpHid; ++k) {
-        act[(uint64_t)(kActH1 + k) * B + b] = h1[k];
-        act[(uint64_t)(kActDZ1 + k) * B + b] = h1[k] > 0.0f ? dh1[k] : 0.0f;
-    }
+    constexpr uint32_t kMost = 768;
+    const uint32_t tiles = (uint32_t)(((uint64_t)B + kGradTile - 1) / kGradTile),
+                   each = (tiles + kMost - 1) / kMost;
+    return tiles ? (tiles + each - 1) / each : 0u;
 }
 
-// Block partial of every gradient entry (and of the loss, entry kMlpParams):
-// sum over the block's samples of u[s] * v[s] for the entry's two rows.
-constexpr int kOuterStage = 32;
-constexpr int kOuterStride = kOuterStage + 1;   // row stride in LDS: no bank conflicts
-// LDS rows: act rows 0..257, then x (5 rows), then a row of ones
-constexpr int kOuterRowX = kActRows, kOuterRowOne = kActRows + kMlpIn,
-              kOuterRows = kActRows + kMlpIn + 1;
-constexpr int kOuterSlots = (kMlpParams + 1 + kMlpOuterThreads - 1) / kMlpOuterThreads;
-
-__device__ inline void outer_rows(int p, int &u, int &v)
+// acc += A B for one wave's 32 x 32 quadrant and 64 terms: a(m, k) and b(k, n)
+// are read for m, n = lane % 32 and k = 2 step + lane / 32; acc[4 i + j] is row
+// 8 i + 4 (lane / 32) + j, column lane % 32.
+template <class A, class B>
+__device__ inline f32x16 quadrant(f32x16 acc, A &&a, B &&b)
 {
-    if (p < kMlpB1) {   // W1[r][c] = sum dz1[r] x[c]
-        u = kActDZ1 + p / kMlpIn;
-        v = kOuterRowX + p % kMlpIn;
-    } else if (p < kMlpW2) {
-        u = kActDZ1 + (p - kMlpB1);
-        v = kOuterRowOne;
-    } else if (p < kMlpB2) {   // W2[r][c] = sum dz2[r] h1[c]
-        int q = p - kMlpW2;
-        u = kActDZ2 + q / kMlpHid;
-        v = kActH1 + q % kMlpHid;
-    } else if (p < kMlpW3) {
-        u = kActDZ2 + (p - kMlpB2);
-        v = kOuterRowOne;
-    } else if (p < kMlpB3) {   // w3[c] = sum dy h2[c]
-        u = kActDY;
-        v = kActH2 + (p - kMlpW3);
-    } else if (p == kMlpB3) {
-        u = kActDY;
-        v = kOuterRowOne;
-    } else {   // loss
-        u = kActSQ;
-        v = kOuterRowOne;
-    }
-}
-
-__global__ __launch_bounds__(kMlpOuterThreads) void k_mlp_outer(const float *__restrict__ act,
-                                                                const float *__restrict__ x,
-                                                                uint32_t B,
-                                                                float *__restrict__ part)
-{
-    __shared__ float st[kOuterRows * kOuterStride];
-    int uo[kOuterSlots], vo[kOuterSlots];
-    float acc[kOuterSlots];
-#pragma unroll
-    for (int j = 0; j < kOuterSlots; ++j) {
-        int p = threadIdx.x + j * kMlpOuterThreads;
-        int u = kOuterRowOne, v = kOuterRowOne;
-        if (p <= kMlpParams)
-            outer_rows(p, u, v);
-        uo[j] = u * kOuterStride;
-        vo[j] = v * kOuterStride;
-        acc[j] = 0.0f;
-    }
-    uint64_t b0 = (uint64_t)blockIdx.x * kMlpOuterSamples;
-    uint64_t b1 = b0 + kMlpOuterSamples < B ? b0 + kMlpOuterSamples : B;
-    for (uint64_t s0 = b0; s0 < b1; s0 += kOuterStage) {
-        __syncthreads();
-        for (int t = threadIdx.x; t < kOuterRows * kOuterStage; t += kMlpOuterThreads) {
-            int row = t / kOuterStage, c = t % kOuterStage;
-            uint64_t b = s0 + c;
-            float val = 0.0f;
-            if (b < b1) {
-                if (row < kActRows)
-                    val = act[(uint64_t)row * B + b];
-                else if (row < kOuterRowOne)
-                    val = x[b * kMlpIn + (row - kOuterRowX)];
-                else
-                    val = 1.0f;
-            }
-            st[row * kOuterStride + c] = val;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < kOuterSlots; ++j) {
-            const float *u = st + uo[j];
-            const float *v = st + vo[j];
-            float a = acc[j];
 #pragma unroll 8
-            for (int c = 0; c < kOuterStage; ++c)
-                a = fmaf(u[c], v[c], a);
-            acc[j] = a;
+    for (int step = 0; step < 32; ++step)
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a(step), b(step), acc, 0, 0, 0);
+    return acc;
+}
+
+__global__ __launch_bounds__(kGradThreads)
+__attribute__((amdgpu_waves_per_eu(3))) void k_mlp_grad(const float *__restrict__ w,
+                                                           const float *__restrict__ x,
+                                                           const float *__restrict__ target,
+                                                           uint32_t B, float *__restrict__ part)
+{
+    // h2: relu(z2), then dz2, then dz1
+    __shared__ float h1[kGradTile * kGradRow], h2[kGradTile * kGradRow],
+        w2[kMlpHid * kGradRow];
+    __shared__ float xs[kGradTile][kMlpIn], sw3[kMlpHid], ypart[kGradWaves][kGradTile],
+        dys[kGradTile];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int col = lane & 31, half = lane >> 5, qm = (wv >> 1) * 32, qn = (wv & 1) * 32;
+    float w1[kMlpIn];
+    for (int k = threadIdx.x; k < kMlpHid * kMlpHid; k += kGradThreads)
+        w2[k / kMlpHid * kGradRow + k % kMlpHid] = w[kMlpW2 + k];
+#pragma unroll
+    for (int c = 0; c < kMlpIn; ++c)
+        w1[c] = w[kMlpW1 + lane * kMlpIn + c];
+    const float b1 = w[kMlpB1 + lane], b2 = w[kMlpB2 + qn + col], w3 = w[kMlpW3 + lane],
+                b3 = w[kMlpB3];
+    if (wv == 0)
+        sw3[lane] = w3;
+    f32x16 g2 = {};
+    float gb1 = 0.0f, gb2 = 0.0f, gw3 = 0.0f, gb3 = 0.0f, loss = 0.0f, gw1[kMlpIn] = {};
+    const uint32_t tiles = (uint32_t)(((uint64_t)B + kGradTile - 1) / kGradTile);
+    for (uint32_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        const uint32_t s0 = tile * kGradTile, n = B - s0 < kGradTile ? B - s0 : kGradTile;
+        const int first = wv * kGradSpan;   // this wave's samples where lanes are units
+        __syncthreads();   // the last tile's LDS has been read
+        for (int k = threadIdx.x; k < kGradTile * kMlpIn; k += kGradThreads)
+            xs[k / kMlpIn][k % kMlpIn] =
+                (uint32_t)(k / kMlpIn) < n ? x[(uint64_t)s0 * kMlpIn + k] : 0.0f;
+        const float want = target[s0 + ((uint32_t)lane < n ? lane : n - 1)];
+        __syncthreads();
+#pragma unroll 4
+        for (int q = 0; q < kGradSpan; ++q) {
+            float acc = b1;
+#pragma unroll
+            for (int c = 0; c < kMlpIn; ++c)
+                acc = fmaf(w1[c], xs[first + q][c], acc);
+            // samples past the batch: no activation, no gradient
+            h1[(first + q) * kGradRow + lane] = (uint32_t)(first + q) < n ? fmaxf(acc, 0.0f) : 0.0f;
+        }
+        __syncthreads();
+        {
+            f32x16 z;
+#pragma unroll
+            for (int k = 0; k < 16; ++k)
+                z[k] = b2;
+            z = quadrant(
+                z, [&](int k) { return h1[(qm + col) * kGradRow + 2 * k + half]; },
+                [&](int k) { return w2[(qn + col) * kGradRow + 2 * k + half]; });
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                const int s = qm + 8 * (k / 4) + 4 * half + k % 4;
+                h2[s * kGradRow + qn + col] = (uint32_t)s < n ? fmaxf(z[k], 0.0f) : 0.0f;
+            }
+        }
+        __syncthreads();
+        {   // y, lanes along the samples, each wave a quarter of the units
+            float y = 0.0f;
+#pragma unroll
+            for (int q = 0; q < kGradSpan; ++q)
+                y = fmaf(sw3[first + q], h2[lane * kGradRow + first + q], y);
+            ypart[wv][lane] = y;
+        }
+        __syncthreads();
+        {
+            float y = b3;
+#pragma unroll
+            for (int q = 0; q < kGradWaves; ++q)
+                y += ypart[q][lane];
+            const float res = (uint32_t)lane < n ? y - want : 0.0f, dy = 2.0f * res / (float)B;
+            gb3 += dy;
+            loss += res * res / (float)B;
+            if (wv == 0)
+                dys[lane] = dy;
+        }
+        __syncthreads();
+#pragma unroll 4
+        for (int q = 0; q < kGradSpan; ++q) {
+            float &at = h2[(first + q) * kGradRow + lane];
+            const float h = at, dy = dys[first + q], dz = h > 0.0f ? dy * w3 : 0.0f;
+            gw3 = fmaf(dy, h, gw3);
+            gb2 += dz;
+            at = dz;
+        }
+        __syncthreads();
+        f32x16 dh = {};
+        dh = quadrant(
+            dh, [&](int k) { return h2[(qm + col) * kGradRow + 2 * k + half]; },
+            [&](int k) { return w2[(2 * k + half) * kGradRow + qn + col]; });
+        g2 = quadrant(
+            g2, [&](int k) { return h2[(2 * k + half) * kGradRow + qm + col]; },
+            [&](int k) { return h1[(2 * k + half) * kGradRow + qn + col]; });
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const int at = (qm + 8 * (k / 4) + 4 * half + k % 4) * kGradRow + qn + col;
+            h2[at] = h1[at] > 0.0f ? dh[k] : 0.0f;
+        }
+        __syncthreads();
+#pragma unroll 4
+        for (int q = 0; q < kGradSpan; ++q) {
+            const float dz = h2[(first + q) * kGradRow + lane];
+            gb1 += dz;
+#pragma unroll
+            for (int c = 0; c < kMlpIn; ++c)
+                gw1[c] = fmaf(dz, xs[first + q][c], gw1[c]);
         }
     }
+    // the workgroup's partial gradient
+    float *const out = part + (uint64_t)blockIdx.x * (kMlpParams + 1);
 #pragma unroll
-    for (int j = 0; j < kOuterSlots; ++j) {
-        int p = threadIdx.x + j * kMlpOuterThreads;
-        if (p <= kMlpParams)
-            part[(uint64_t)blockIdx.x * (kMlpParams + 1) + p] = acc[j];
+    for (int k = 0; k < 16; ++k)
+        out[kMlpW2 + (qm + 8 * (k / 4) + 4 * half + k % 4) * kMlpHid + qn + col] = g2[k];
+    constexpr int kSmall = 3 + kMlpIn;   // per unit: gb1, gb2, gw3, gW1
+    __syncthreads();
+    {
+        float *const red = h1 + (wv * kSmall) * 64 + lane;
+        red[0] = gb1;
+        red[64] = gb2;
+        red[128] = gw3;
+#pragma unroll
+        for (int c = 0; c < kMlpIn; ++c)
+            red[(3 + c) * 64] = gw1[c];
+    }
+    __syncthreads();
+    for (int k = threadIdx.x; k < kSmall * 64; k += kGradThreads) {
+        float sum = 0.0f;
+        for (int q = 0; q < kGradWaves; ++q)
+            sum += h1[q * kSmall * 64 + k];
+        const int f = k / 64, u = k % 64;
+        out[f == 0 ? kMlpB1 + u : f == 1 ? kMlpB2 + u : f == 2 ? kMlpW3 + u
+                                                               : kMlpW1 + u * kMlpIn + f - 3] = sum;
+    }
+    for (int o = 32; o >= 1; o >>= 1) {
+        gb3 += __shfl_xor(gb3, o, 64);
+        loss += __shfl_xor(loss, o, 64);
+    }
+    if (threadIdx.x == 0) {
+        out[kMlpB3] = gb3;
+        out[kMlpParams] = loss;
     }
 }
 
-// Gradient entry p = sum of the block partials in block order.
-__global__ void k_mlp_reduce(const float *__restrict__ part, uint32_t nblk,
-                             float *__restrict__ grad, float *__restrict__ loss)
+// Gradient entry = sum of the partials, kReduceSlices strided sums of them added
+// in order (the same every time).
+constexpr int kReduceSlices = 16;
+
+__global__ __launch_bounds__(64 * kReduceSlices) void k_mlp_reduce(const float *__restrict__ part,
+                                                                   uint32_t nblk,
+                                                                   float *__restrict__ grad,
+                                                                   float *__restrict__ loss)
 {
-    int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p > kMlpParams)
-        return;
+    __shared__ float red[kReduceSlices][64];
+    const int lane = threadIdx.x & 63, slice = threadIdx.x >> 6, p = blockIdx.x * 64 + lane;
     float sum = 0.0f;
-    for (uint32_t k = 0; k < nblk; ++k)
-        sum += part[(uint64_t)k * (kMlpParams + 1) + p];
+    if (p <= kMlpParams) {
+#pragma unroll 8
+        for (uint32_t k = slice; k < nblk; k += kReduceSlices)
+            sum += part[(uint64_t)k * (kMlpParams + 1) + p];
+    }
+    red[slice][lane] = sum;
+    __syncthreads();
+    if (slice != 0 || p > kMlpParams)
+        return;
+#pragma unroll
+    for (int q = 1; q < kReduceSlices; ++q)
+        sum += red[q][lane];
     if (p < kMlpParams)
         grad[p] = sum;
     else if (loss)
@@ -453,12 +504,15 @@ hipError_t launch_mlp_forward(const float *w, const float *x, uint32_t B, float 
 }
 
 hipError_t launch_mlp_grad(const float *w, const float *x, const float *target, uint32_t B,
-                           float *act, float *part, float *grad, float *loss, hipStream_t s)
+                           float *part, float *grad, float *loss, hipStream_t s)
 {
-    unsigned nblk = blocks_for(B, kMlpOuterSamples);
-    k_mlp_backprop<<<blocks_for(B, 256), 256, 0, s>>>(w, x, target, B, act);
-    k_mlp_outer<<<nblk, kMlpOuterThreads, 0, s>>>(act, x, B, part);
-    k_mlp_reduce<<<blocks_for(kMlpParams + 1, 256), 256, 0, s>>>(part, nblk, grad, loss);
+    const uint32_t nblk = mlp_grad_blocks(B);
+    k_mlp_grad<<<nblk, kGradThreads, 0, s>>>(w, x, target, B, part);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess)
+        return e;
+    k_mlp_reduce<<<blocks_for(kMlpParams + 1, 64), 64 * kReduceSlices, 0, s>>>(part, nblk, grad,
+                                                                               loss);
     return hipGetLastError();
 }
 

@@ -275,3 +275,23 @@ def test_trained_network_gains_over_speed_bound_step():
     # the learned steps (with their training-tuned scalar) against the
     # training-tuned uniform rescaling: no gain, at most a small loss
     assert rows["learned tuned"]["cost"] <= 1.05 * fair["cost"]
+
+
+@pytest.mark.parametrize("B", [63, 64, 65, 128, 768 * 64, 768 * 64 + 1])
+def test_gradient_at_tile_edges(B):
+    """Sample counts around the 64-sample tile and around one tile for every
+    workgroup: the gradient and the loss to 1e-5 of the 64-bit reference, as
+    the other sizes."""
+    need_gpu()
+    say("mlp grad B", B)
+    theta = _theta(B)
+    rng = np.random.default_rng(B + 1)
+    X = rng.uniform(0, 1.2, (B, 5)).astype(np.float32)
+    t = rng.normal(0, 1, B).astype(np.float32)
+    w = torch.from_numpy(theta.astype(np.float32)).cuda()
+    g, loss = ld.cd_mlp_grad(w, torch.from_numpy(X).cuda(), torch.from_numpy(t).cuda())
+    X64, t64 = X.astype(np.float64), t.astype(np.float64)
+    gr = ref.grad(theta, X64, t64)
+    assert np.linalg.norm(g.cpu().numpy() - gr) <= 1e-5 * np.linalg.norm(gr)
+    lr = ref.loss(theta, X64, t64)
+    assert abs(loss.item() - lr) <= 1e-5 * lr
