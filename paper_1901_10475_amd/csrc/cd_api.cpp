@@ -934,9 +934,22 @@ int cd_build_tree(const cd_boxes *boxes, int precision, uint32_t slab_ticks, cd_
         // keep its top bits (at least kMinPackedCodeBits of 30)
         const int sb = bits_for(max_slab), ib = N > 1 ? bits_for((uint64_t)N - 1) : 1;
         const int room = 64 - sb - ib;
-        const int cb = room < (int)kKeyCodeBits ? room : (int)kKeyCodeBits;
+        int cb = room < (int)kKeyCodeBits ? room : (int)kKeyCodeBits;
         const bool packed = cb >= (int)kMinPackedCodeBits;
-        {
+        // the sort takes 9 bits a pass, so a key one bit past that (37 with the
+        // default slabs) gives up the code's last bit: at 88 M boxes a digit of
+        // 10 bits takes 617 us to scatter, one of 9 414, and the tree of 29
+        // code bits is traversed in the same 2.89 ms (at 79.7 M boxes 430 and
+        // 311 us, traversal 1.07 and 1.13 ms)
+        if (packed && (cb + sb) % 9 == 1)
+            --cb;
+        // words of boxes that carry codes are formed by the sort's first pass
+        // (at 88 M boxes 558 us for it, where a kernel for the keys and a pass
+        // over them take 274 + 600); codes formed from the boxes, which costs
+        // more than a read, are formed once
+        const bool formed = packed && bv.code && N > 1;
+        const KeySource keys{bv.code, bv.t0, err, w, max_slab, (uint32_t)ib, (uint32_t)cb};
+        if (!formed) {
             Stage st("keys", s);
             if (!bv.code)
                 CD_HIP(launch_bounds(bv, boxes->precision, (uint32_t)N, tw.bounds, s));
@@ -951,7 +964,8 @@ int cd_build_tree(const cd_boxes *boxes, int precision, uint32_t slab_ticks, cd_
             if (packed) {   // code bits, then slab bits, above the box index
                 uint64_t *words = nullptr;
                 CD_HIP(radix_sort_words((uint64_t *)tw.kva, (uint64_t *)tw.kvb, (uint32_t)N,
-                                        (uint32_t)ib, (uint32_t)(cb + sb), tw.words, &words, s));
+                                        (uint32_t)ib, (uint32_t)(cb + sb), formed ? &keys : nullptr,
+                                        tw.words, &words, s));
                 res = words;
             } else {        // code (low word), then slab (high word) of the key
                 const KV *items = nullptr;

@@ -385,11 +385,36 @@ struct DigitPlan {
 };
 hipError_t radix_sort16(void *a, void *b, size_t count, const DigitPlan &plan, void *ws,
                         void **result, hipStream_t s);
+// The tree's packed key words of boxes that carry codes: slab << (cb + ib) |
+// code' << ib | box index (N <= 2^ib), slab = t0 / slab_ticks (at most max_slab,
+// else err bit 1), code' the top cb bits of the code's low kKeyCodeBits.
+constexpr uint32_t kKeyCodeBits = 30, kMinPackedCodeBits = 24;
+struct KeySource {
+    const uint32_t *code, *t0;
+    unsigned int *err;
+    uint32_t slab_ticks, max_slab, ib, cb;
+};
+__host__ __device__ inline uint64_t key_code(const KeySource &k, uint32_t code)
+{
+    return (uint64_t)((code & ((1u << kKeyCodeBits) - 1)) >> (kKeyCodeBits - k.cb)) << k.ib;
+}
+__host__ __device__ inline uint64_t key_word(const KeySource &k, uint32_t code, uint32_t t0,
+                                             uint32_t index, bool *bad)
+{
+    uint32_t slab = t0 / k.slab_ticks;
+    if (slab > k.max_slab) {
+        *bad = true;
+        slab = k.max_slab;
+    }
+    return (uint64_t)slab << (k.cb + k.ib) | key_code(k, code) | index;
+}
 // Stable LSD sorts in 9-bit digits, ws: radix_digits_ws_bytes(count).  64-bit
 // words by their bits [low, low + bits); the result ends in *result (a or b).
+// keys: the first pass forms the words (low = ib, count > 1) instead of reading
+// them from a.
 size_t radix_digits_ws_bytes(size_t count);
 hipError_t radix_sort_words(uint64_t *a, uint64_t *b, uint32_t count, uint32_t low, uint32_t bits,
-                            void *ws, uint64_t **result, hipStream_t s);
+                            const KeySource *keys, void *ws, uint64_t **result, hipStream_t s);
 // (key, index) items by the key's low `bits` bits (the same result).
 hipError_t radix_sort_keyed(KV *a, KV *b, uint32_t count, uint32_t bits, void *ws,
                             const KV **result, hipStream_t s);
@@ -433,11 +458,9 @@ hipError_t launch_bounds(const BoxView &b, int precision, uint32_t N,
                          unsigned long long *bounds /*[6]: min xyz, max xyz*/, hipStream_t s);
 // The device-wide key sort's keys: slab << 32 | the code's low kKeyCodeBits
 // bits (Morton codes have 30).  kv: (key, box index) items; packed (with kv
-// == nullptr): one word per box, slab << (cb + ib) | code' << ib | box index
-// (N <= 2^ib), code' the code's top cb bits (cb <= kKeyCodeBits: large box
-// sets give up the lowest code bits, which only shape the tree, to keep
+// == nullptr): one word per box as KeySource has it (cb <= kKeyCodeBits: large
+// box sets give up the lowest code bits, which only shape the tree, to keep
 // 8-byte sort items).
-constexpr uint32_t kKeyCodeBits = 30, kMinPackedCodeBits = 24;
 hipError_t launch_keys(const BoxView &b, int precision, uint32_t N, uint32_t slab_ticks,
                        uint32_t max_slab, uint32_t slab_size,
                        const unsigned long long *bounds, uint32_t *morton, KV *kv,

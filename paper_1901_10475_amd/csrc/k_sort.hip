@@ -277,27 +277,65 @@ hipError_t radix_sort16(void *a, void *b, size_t count, const DigitPlan &plan,
 
 // ---- device-wide LSD radix sort of words, keyed items and records ------------------------
 //
-// Items of 8 or 16 bytes, digits of 9 or 10 bits, so that the 37 bits left above
-// a 27-bit box index take four passes.  Per pass: k_digits_up counts each tile's
-// digits into a row, k_digits_rows turns every kDigitChunk rows into prefixes
-// and their sum, k_digits_chunks the sums into prefixes over the chunks and
-// digit totals, and k_digits_down ranks a tile's items, stages them in LDS in
-// digit order and writes each digit's run in consecutive lanes (128 bytes on
-// average).
+// Items of 8 or 16 bytes, digits of 9 bits, so that 36 key bits take four
+// passes.  Per pass: k_digits_up counts each tile's digits into a row,
+// k_digits_rows turns every kDigitChunk rows into prefixes and their sum,
+// k_digits_chunks the sums into prefixes over the chunks and digit totals, and
+// k_digits_down ranks a tile's items, stages them in LDS in digit order and
+// writes each digit's run in consecutive lanes (128 bytes on average).  The
+// first pass takes its items from a source of its own: the tree's key words are
+// formed from the boxes' codes and tags as they are read, and its counts read
+// the codes alone.
 // Bound: HBM, three times the item's size a pass, and in the scatter the ranking
-// (some 40 instructions an item).  37 bits of 79.7 M words: counts 3.9 TB/s, scatter 4.1
-// (9 bits) and 3.0 (10), 2.06 ms in all; the 16-byte sort's form with 8-byte
-// items, 8-bit digits and 4 096-word tiles took 2.65 (five passes, counts 3.4,
-// scatter 4.1 TB/s, 36 us of scans a pass).
+// (some 40 instructions an item).
+// 36 bits of 79.7 M tree words: counts 3.9 TB/s (the first, of codes alone, 2.8:
+// neighbours are one object's, with equal digits), scatter 4.1, 1.98 ms in all;
+// as 37 bits with a digit of 10 and the words written by a kernel of their own
+// 2.36 (keys 0.28, 10-bit scatter at 3.0 TB/s).  88 M words of 100 000 objects:
+// 2.92 -> 2.42 ms.
 constexpr int kDigitThreads = 512, kDigitWaves = kDigitThreads / 64, kDigitChunk = 64;
-template <int BITS, class Item>
+constexpr int kDigitBits = 9, kDigitBins = 1 << kDigitBits, kDigitCopies = 8;   // of the counters
+static_assert(kDigitBins == kDigitThreads, "a lane per digit");
+template <class Item>
 struct Digits {
-    static constexpr int kBins = 1 << BITS;
     // two workgroups' LDS on a CU
-    static constexpr int kItems = (BITS == 9 ? 128 : 112) / (int)sizeof(Item);
+    static constexpr int kItems = 128 / (int)sizeof(Item);
     static constexpr int kTile = kDigitThreads * kItems;
-    static constexpr int kPer = kBins / kDigitThreads;   // digits per lane
-    static constexpr int kCopies = BITS == 9 ? 8 : 4;    // of the counters
+};
+
+// Where a pass takes its items from.  raw: what is read (for the scatter,
+// low_raw for the counts of the first digit); item: the item.
+template <class T>
+struct ItemArray {
+    using Item = T;
+    using Raw = T;
+    using LowRaw = T;
+    const T *__restrict__ in;
+    __device__ Raw raw(uint32_t g) const { return in[g]; }
+    __device__ Item item(const Raw &v, uint32_t, bool *) const { return v; }
+    __device__ LowRaw low_raw(uint32_t g) const { return in[g]; }
+    __device__ Item low_item(const LowRaw &v) const { return v; }
+    __device__ void report(bool) const {}
+};
+// The tree's key words, formed as launch_keys forms them.
+struct KeyWords {
+    using Item = uint64_t;
+    using Raw = uint2;
+    using LowRaw = uint32_t;
+    KeySource k;
+    __device__ Raw raw(uint32_t g) const { return make_uint2(k.code[g], k.t0[g]); }
+    __device__ Item item(const Raw &v, uint32_t g, bool *bad) const
+    {
+        return key_word(k, v.x, v.y, g, bad);
+    }
+    // the code's bits alone: a first digit never reaches the slab
+    __device__ LowRaw low_raw(uint32_t g) const { return k.code[g]; }
+    __device__ Item low_item(uint32_t c) const { return key_code(k, c); }
+    __device__ void report(bool bad) const
+    {
+        if (bad)
+            atomicOr(k.err, 1u);
+    }
 };
 
 // Digits of `mask`'s width.  A word's bits from `shift` on.
@@ -325,56 +363,51 @@ struct DigitRec {
         const uint64_t ids = (uint64_t)v.x << j | (v.y & j_mask);
         // a digit that straddles the two words takes its upper bits from ids
         const uint64_t at = shift >= low ? ids >> (shift - low)
-                            : shift + 10 > low ? t >> shift | ids << (low - shift)
+                            : shift + kDigitBits > low ? t >> shift | ids << (low - shift)
                                                : t >> shift;
         return (uint32_t)at & mask;
     }
 };
 
 // Digit counts of one tile (kCopies histograms by lane, rows of
-// kBins + 1 words so that the copies of one digit sit in different banks).
-template <int BITS, class Item, class Digit>
-__global__ __launch_bounds__(kDigitThreads) void k_digits_up(const Item *__restrict__ in,
-                                                             uint32_t count, Digit digit,
+// kDigitBins + 1 words so that the copies of one digit sit in different banks).
+template <class Source, class Digit>
+__global__ __launch_bounds__(kDigitThreads) void k_digits_up(Source src, uint32_t count,
+                                                             Digit digit,
                                                              uint32_t *__restrict__ rows)
 {
-    using W = Digits<BITS, Item>;
-    constexpr int kRow = W::kBins + 1;
-    __shared__ uint32_t h[W::kCopies * kRow];
+    using W = Digits<typename Source::Item>;
+    constexpr int kRow = kDigitBins + 1;
+    __shared__ uint32_t h[kDigitCopies * kRow];
     const uint32_t base = blockIdx.x * (uint32_t)W::kTile + threadIdx.x;
-    Item v[W::kItems];
+    typename Source::LowRaw v[W::kItems];
 #pragma unroll
     for (int k = 0; k < W::kItems; ++k) {   // every load in flight before the first count
         const uint32_t g = base + k * kDigitThreads;
-        v[k] = in[g < count ? g : count - 1];
+        v[k] = src.low_raw(g < count ? g : count - 1);
     }
-    for (int k = threadIdx.x; k < W::kCopies * kRow; k += kDigitThreads)
+    for (int k = threadIdx.x; k < kDigitCopies * kRow; k += kDigitThreads)
         h[k] = 0;
     __syncthreads();
-    uint32_t *const mine = h + (threadIdx.x % W::kCopies) * kRow;
+    uint32_t *const mine = h + (threadIdx.x % kDigitCopies) * kRow;
 #pragma unroll
     for (int k = 0; k < W::kItems; ++k)
         if (base + k * kDigitThreads < count)
-            atomicAdd(&mine[digit(v[k])], 1u);
+            atomicAdd(&mine[digit(src.low_item(v[k]))], 1u);
     __syncthreads();
+    uint32_t sum = 0;
 #pragma unroll
-    for (int q = 0; q < W::kPer; ++q) {
-        const int d = q * kDigitThreads + threadIdx.x;
-        uint32_t sum = 0;
-#pragma unroll
-        for (int c = 0; c < W::kCopies; ++c)
-            sum += h[c * kRow + d];
-        rows[(size_t)blockIdx.x * W::kBins + d] = sum;
-    }
+    for (int c = 0; c < kDigitCopies; ++c)
+        sum += h[c * kRow + threadIdx.x];
+    rows[(size_t)blockIdx.x * kDigitBins + threadIdx.x] = sum;
 }
 
 // Rows [c kDigitChunk, ...) of one chunk: each count becomes the sum of those of
 // the chunk's earlier rows, the chunk's total goes to sums[c].
-template <int BITS>
 __global__ __launch_bounds__(256) void k_digits_rows(uint32_t *__restrict__ rows, uint32_t tiles,
                                                     uint32_t *__restrict__ sums)
 {
-    constexpr int kBins = 1 << BITS, kBatch = 16;
+    constexpr int kBins = kDigitBins, kBatch = 16;
     const uint32_t d = blockIdx.y * 256 + threadIdx.x, r0 = blockIdx.x * kDigitChunk;
     const uint32_t n = tiles - r0 < (uint32_t)kDigitChunk ? tiles - r0 : (uint32_t)kDigitChunk;
     uint32_t run = 0;
@@ -395,10 +428,9 @@ __global__ __launch_bounds__(256) void k_digits_rows(uint32_t *__restrict__ rows
 
 // One wave per digit: its sums over the chunks become prefixes, the total goes
 // to the row after the last chunk's.
-template <int BITS>
 __global__ __launch_bounds__(256) void k_digits_chunks(uint32_t *__restrict__ sums, uint32_t chunks)
 {
-    constexpr int kBins = 1 << BITS;
+    constexpr int kBins = kDigitBins;
     const uint32_t d = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     uint32_t run = 0;
     for (uint32_t c0 = 0; c0 < chunks; c0 += 64) {
@@ -413,15 +445,16 @@ __global__ __launch_bounds__(256) void k_digits_chunks(uint32_t *__restrict__ su
         sums[(size_t)chunks * kBins + d] = run;
 }
 
-template <int BITS, class Item, class Digit>
+template <class Source, class Digit>
 __global__ __launch_bounds__(kDigitThreads) void k_digits_down(
-    const Item *__restrict__ in, Item *__restrict__ out, uint32_t count, Digit digit,
+    Source src, typename Source::Item *__restrict__ out, uint32_t count, Digit digit,
     const uint32_t *__restrict__ rows, const uint32_t *__restrict__ sums, uint32_t chunks)
 {
-    using W = Digits<BITS, Item>;
+    using Item = typename Source::Item;
+    using W = Digits<Item>;
     __shared__ Item stage[W::kTile];
-    __shared__ uint16_t cnt[kDigitWaves][W::kBins + 2];   // per wave and digit
-    __shared__ uint32_t to[W::kBins];                     // place of staged item 0 by digit
+    __shared__ uint16_t cnt[kDigitWaves][kDigitBins + 2];   // per wave and digit
+    __shared__ uint32_t to[kDigitBins];                     // place of staged item 0 by digit
     __shared__ uint32_t wsum[33];
     const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const uint32_t base = blockIdx.x * (uint32_t)W::kTile;
@@ -429,21 +462,27 @@ __global__ __launch_bounds__(kDigitThreads) void k_digits_down(
     const uint32_t k0 = w * 64 * W::kItems + lane;
     Item item[W::kItems];
     uint32_t rank[W::kItems];
+    {
+        typename Source::Raw raw[W::kItems];
+        bool bad = false;
 #pragma unroll
-    for (int j = 0; j < W::kItems; ++j) {   // every load in flight before the ranking
-        const uint32_t k = k0 + j * 64;
-        item[j] = in[base + (k < m ? k : m - 1)];
-    }
-    const uint32_t d0 = threadIdx.x * W::kPer;   // this lane's digits
-    uint32_t place[W::kPer], all[W::kPer];
+        for (int j = 0; j < W::kItems; ++j) {   // every load in flight before the ranking
+            const uint32_t k = k0 + j * 64;
+            raw[j] = src.raw(base + (k < m ? k : m - 1));
+        }
 #pragma unroll
-    for (int q = 0; q < W::kPer; ++q) {
-        place[q] = rows[(size_t)blockIdx.x * W::kBins + d0 + q];
-        if (chunks > 1)
-            place[q] += sums[(size_t)(blockIdx.x / kDigitChunk) * W::kBins + d0 + q];
-        all[q] = sums[(chunks > 1 ? (size_t)chunks * W::kBins : 0) + d0 + q];
+        for (int j = 0; j < W::kItems; ++j) {
+            const uint32_t k = k0 + j * 64;
+            item[j] = src.item(raw[j], base + (k < m ? k : m - 1), &bad);
+        }
+        src.report(bad);
     }
-    for (uint32_t k = threadIdx.x; k < (uint32_t)(kDigitWaves * (W::kBins + 2) / 2);
+    const uint32_t d0 = threadIdx.x;   // this lane's digit
+    uint32_t place = rows[(size_t)blockIdx.x * kDigitBins + d0];
+    if (chunks > 1)
+        place += sums[(size_t)(blockIdx.x / kDigitChunk) * kDigitBins + d0];
+    const uint32_t all = sums[(chunks > 1 ? (size_t)chunks * kDigitBins : 0) + d0];
+    for (uint32_t k = threadIdx.x; k < (uint32_t)(kDigitWaves * (kDigitBins + 2) / 2);
          k += kDigitThreads)
         reinterpret_cast<uint32_t *>(&cnt[0][0])[k] = 0;
     __syncthreads();
@@ -452,37 +491,24 @@ __global__ __launch_bounds__(kDigitThreads) void k_digits_down(
     for (int j = 0; j < W::kItems; ++j) {
         const bool valid = k0 + j * 64 < m;
         const uint32_t d = digit(item[j]);
-        const uint64_t peers = match_digit<BITS>(d, __ballot(valid));
+        const uint64_t peers = match_digit<kDigitBits>(d, __ballot(valid));
         const uint32_t c = cnt[w][d], mine = (uint32_t)__popcll(peers & lt);
         if (valid && mine == 0)
             cnt[w][d] = (uint16_t)(c + (uint32_t)__popcll(peers));
         rank[j] = c + mine;
     }
     __syncthreads();
-    {   // per digit: where its words start in the tile and in the output
-        uint32_t n[W::kPer], words = 0, before = 0;
-#pragma unroll
-        for (int q = 0; q < W::kPer; ++q) {
-            n[q] = 0;
-            for (int ww = 0; ww < kDigitWaves; ++ww)
-                n[q] += cnt[ww][d0 + q];
-            words += n[q];
-            before += all[q];
-        }
+    {   // the digit: where its words start in the tile and in the output
+        uint32_t words = 0;
+        for (int ww = 0; ww < kDigitWaves; ++ww)
+            words += cnt[ww][d0];
         uint32_t total;
-        uint32_t start = block_exclusive_scan(words, wsum, &total);
-        uint32_t first = block_exclusive_scan(before, wsum, &total);
-#pragma unroll
-        for (int q = 0; q < W::kPer; ++q) {
-            to[d0 + q] = first + place[q] - start;
-            first += all[q];
-            uint32_t run = start;
-            for (int ww = 0; ww < kDigitWaves; ++ww) {
-                const uint32_t t = cnt[ww][d0 + q];
-                cnt[ww][d0 + q] = (uint16_t)run;
-                run += t;
-            }
-            start += n[q];
+        uint32_t run = block_exclusive_scan(words, wsum, &total);
+        to[d0] = block_exclusive_scan(all, wsum, &total) + place - run;
+        for (int ww = 0; ww < kDigitWaves; ++ww) {
+            const uint32_t t = cnt[ww][d0];
+            cnt[ww][d0] = (uint16_t)run;
+            run += t;
         }
     }
     __syncthreads();
@@ -502,62 +528,62 @@ __global__ __launch_bounds__(kDigitThreads) void k_digits_down(
 namespace {
 uint32_t digit_chunks(uint32_t tiles) { return (tiles + kDigitChunk - 1) / kDigitChunk; }
 // Rows, chunk sums and totals of one pass (one chunk's sums are the totals).
-template <int BITS, class Item>
+template <class Item>
 size_t digit_bytes(size_t count)
 {
-    const uint32_t tiles = nblk(count, Digits<BITS, Item>::kTile), chunks = digit_chunks(tiles);
-    return ((size_t)tiles + chunks + (chunks > 1 ? 1 : 0)) * (4u << BITS);
+    const uint32_t tiles = nblk(count, Digits<Item>::kTile), chunks = digit_chunks(tiles);
+    return ((size_t)tiles + chunks + (chunks > 1 ? 1 : 0)) * (4u << kDigitBits);
 }
 }  // namespace
 
 size_t radix_digits_ws_bytes(size_t count)
 {
-    const size_t a = digit_bytes<10, uint64_t>(count), b = digit_bytes<9, uint4>(count);
-    return a > b ? a : b;
+    return digit_bytes<uint4>(count);   // (more than 8-byte items' half as many tiles)
 }
 
-template <int BITS, class Item, class Digit>
-static hipError_t digit_pass(const Item *src, Item *dst, uint32_t count, const Digit &digit,
-                             uint32_t *rows, hipStream_t s)
+template <class Source, class Digit>
+static hipError_t digit_pass(const Source &src, typename Source::Item *dst, uint32_t count,
+                             const Digit &digit, uint32_t *rows, hipStream_t s)
 {
-    using W = Digits<BITS, Item>;
-    const uint32_t tiles = nblk(count, W::kTile), chunks = digit_chunks(tiles);
-    uint32_t *const sums = rows + (size_t)tiles * W::kBins;
-    k_digits_up<BITS><<<tiles, kDigitThreads, 0, s>>>(src, count, digit, rows);
+    const uint32_t tiles = nblk(count, Digits<typename Source::Item>::kTile);
+    const uint32_t chunks = digit_chunks(tiles);
+    uint32_t *const sums = rows + (size_t)tiles * kDigitBins;
+    k_digits_up<<<tiles, kDigitThreads, 0, s>>>(src, count, digit, rows);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return e;
-    k_digits_rows<BITS><<<dim3(chunks, W::kBins / 256), 256, 0, s>>>(rows, tiles, sums);
+    k_digits_rows<<<dim3(chunks, kDigitBins / 256), 256, 0, s>>>(rows, tiles, sums);
     e = hipGetLastError();
     if (e != hipSuccess)
         return e;
     if (chunks > 1) {
-        k_digits_chunks<BITS><<<W::kBins / 4, 256, 0, s>>>(sums, chunks);
+        k_digits_chunks<<<kDigitBins / 4, 256, 0, s>>>(sums, chunks);
         e = hipGetLastError();
         if (e != hipSuccess)
             return e;
     }
-    k_digits_down<BITS><<<tiles, kDigitThreads, 0, s>>>(src, dst, count, digit, rows, sums,
-                                                        chunks);
+    k_digits_down<<<tiles, kDigitThreads, 0, s>>>(src, dst, count, digit, rows, sums, chunks);
     return hipGetLastError();
 }
 
 hipError_t radix_sort_words(uint64_t *a, uint64_t *b, uint32_t count, uint32_t low, uint32_t bits,
-                            void *ws, uint64_t **result, hipStream_t s)
+                            const KeySource *keys, void *ws, uint64_t **result, hipStream_t s)
 {
     *result = a;
+    if (keys && (count <= 1 || low != keys->ib || keys->cb < (uint32_t)kDigitBits))
+        return hipErrorInvalidValue;
     if (count <= 1 || bits == 0)
         return hipSuccess;
     if (low + bits > 64)
         return hipErrorInvalidValue;
-    // as few passes as digits of 9 bits and one of 10 allow
-    const uint32_t passes = bits <= 10 ? 1u : (bits - 1 + 8) / 9;
     uint64_t *src = a, *dst = b;
-    for (uint32_t p = 0; p < passes; ++p) {
-        const uint32_t left = passes - p, take = (bits + left - 1) / left;
+    for (bool first = true; bits > 0; first = false) {
+        const uint32_t left = (bits + kDigitBits - 1) / kDigitBits;
+        const uint32_t take = (bits + left - 1) / left;
         const DigitWord d{low, (1u << take) - 1};
-        hipError_t e = take > 9 ? digit_pass<10>(src, dst, count, d, (uint32_t *)ws, s)
-                                : digit_pass<9>(src, dst, count, d, (uint32_t *)ws, s);
+        hipError_t e = first && keys
+                           ? digit_pass(KeyWords{*keys}, dst, count, d, (uint32_t *)ws, s)
+                           : digit_pass(ItemArray<uint64_t>{src}, dst, count, d, (uint32_t *)ws, s);
         if (e != hipSuccess)
             return e;
         low += take;
@@ -583,8 +609,8 @@ static hipError_t sort_items16(const void *in, void *a, void *b, uint32_t count,
     uint4 *dst = (uint4 *)a, *next = (uint4 *)b;
     for (uint32_t low = 0; low < bits;) {
         const uint32_t left = (bits - low + 8) / 9, take = (bits - low + left - 1) / left;
-        hipError_t e = digit_pass<9>(src, dst, count, make(low, (1u << take) - 1),
-                                     (uint32_t *)ws, s);
+        hipError_t e = digit_pass(ItemArray<uint4>{src}, dst, count,
+                                  make(low, (1u << take) - 1), (uint32_t *)ws, s);
         if (e != hipSuccess)
             return e;
         low += take;

@@ -443,6 +443,46 @@ def test_key_sort_is_stable(N, T):
         assert np.all(np.diff(order)[same] > 0)
 
 
+@pytest.mark.parametrize("T", [5, 640, 1 << 17])
+@pytest.mark.parametrize("N", [2, 511, 8191, 8192, 8193, 524289])
+def test_key_words_formed_by_the_sort(N, T):
+    """Boxes that carry codes (some with bits above the 30 a key holds), sorted
+    without a kernel for their keys, at the sort's tile and chunk edges and with
+    key bits on and beside a multiple of nine: leaves in the order of slab, code
+    (less the bits the word has no room for) and index; a box past the horizon's
+    last slab is reported, and not before."""
+    need_gpu()
+    say("formed key words, N", N, "T", T)
+    rng = np.random.default_rng(N + T)
+    lo = rng.uniform(-7000, 7000, (N, 3))
+    t0 = rng.integers(0, T + 1, N)
+    code = rng.integers(0, 1 << 32, N).astype(np.uint32)
+    code[rng.integers(0, N, N // 2)] = code[0]             # equal codes keep their order
+    slab_ticks = 10 if T == 640 else 1
+    sb = (T // slab_ticks).bit_length()
+    cb = min(30, 64 - sb - (N - 1).bit_length())
+    assert cb >= 24
+    if (sb + cb) % 9 == 1:
+        cb -= 1
+    b = cd.Boxes.from_arrays(lo, lo + 1.0, t0, t0 + 1, np.arange(N), horizon_ticks=T, obj_count=N)
+    codes = torch.from_numpy(code.view(np.int32)).cuda()
+    b.desc.code, b.desc.code_valid = codes.data_ptr(), 1
+    tree = cd.Tree(N, cd.CD_FP64)
+    ws = cd._bytes(cd.lib().cd_build_tree_ws(N), "cuda")
+    cd.cd_build_tree(b, cd.CD_FP64, tree, ws, slab_ticks)
+    torch.cuda.synchronize()
+    raw = tree.mem.cpu().numpy().view(np.uint8)
+    assert raw[:4].view(np.uint32)[0] == 0
+    leaf = raw[256 + (N - 1) * 64:256 + (2 * N - 1) * 64].reshape(N, 64)[:, 48:64]
+    order = leaf.copy().view(np.uint32)[:, 2].astype(np.int64)
+    top = (code & np.uint32((1 << 30) - 1)) >> np.uint32(30 - cb)
+    assert np.array_equal(order, np.lexsort((np.arange(N), top, t0 // slab_ticks)))
+    b.t0[N - 1] = (T // slab_ticks + 1) * slab_ticks
+    cd.cd_build_tree(b, cd.CD_FP64, tree, ws, slab_ticks)
+    torch.cuda.synchronize()
+    assert tree.mem[:4].cpu().numpy().view(np.uint32)[0] & 1
+
+
 @pytest.mark.parametrize("n", [1024, 1025, 2048, 2049, 3072, 3073, 5120, 5121, 8192, 8193, 12288,
                                12289, 17408])
 def test_block_sort_sizes(n):
