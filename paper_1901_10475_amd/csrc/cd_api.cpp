@@ -403,6 +403,7 @@ size_t layout_query(void *base, size_t bytes, int64_t N, int64_t cap, QueryWS *w
 // then the level flags and a status copy (leaf count low/high, flags, last
 // queue count).
 constexpr int kRefineMaxLevels = 40;      // > log2(2^32 instants) + 2
+constexpr int kRefineFirst = 8;   // launches before the first look at the status
 constexpr int kRefCtlFlags = kRefineMaxLevels + 1;
 constexpr int kRefCtlStatus = kRefineMaxLevels + 4;
 constexpr int kRefCtlWords = kRefCtlStatus + 4;
@@ -1501,30 +1502,44 @@ int cd_refine_records(const cd_elements *el, const cd_params *p, uint32_t delta_
         Stage st("refine", s);
         CD_HIP(launch_object_setup(*el, p->mu, (double)p->start_ticks * p->tick_s, w.oc, w.os,
                                    nullptr, s));
-        CD_HIP(launch_fill_u32(w.ctl, 0u, kRefCtlWords, s));
-        CD_HIP(launch_fill_u32(w.ctl, (uint32_t)count, 1, s));
-        CD_HIP(launch_fill_u64(w.counter, 0ull, 1, s));
-        CD_HIP(launch_refine_seed(pairs, (uint32_t)count, p->start_ticks, T, delta_ticks, w.qa,
-                                  s));
-        for (int lev = 0; lev < levels; ++lev) {
-            const uint4 *in = (lev & 1) ? w.qb : w.qa;
-            uint4 *outq = (lev & 1) ? w.qa : w.qb;
-            // at most count * 2^lev items reach level lev
-            uint64_t most = (uint64_t)count << (lev < 32 ? lev : 32);
-            if (most > w.qcap)
-                most = w.qcap;
-            uint32_t blocks = (uint32_t)((most + 255) / 256);
-            blocks = blocks < 1 ? 1 : (blocks > 2048 ? 2048 : blocks);
-            CD_HIP(launch_refine_level((int)p->box_rule, w.oc, w.os, (uint32_t)el->n, pairs, in,
-                                       w.ctl + lev, w.qcap, outq, w.ctl + lev + 1, w.qcap,
-                                       w.raw, (unsigned long long)capacity, w.counter,
-                                       w.ctl + kRefCtlFlags, delta_ticks, min_steps, p->tick_s,
-                                       0.5 * p->threshold_km, blocks, s));
+        // Launches that take few items several levels down end most runs within
+        // kRefineFirst of them (seven for 235 000 records of up to 16 000
+        // instants, of which 14 launches make a level each), so the rest are
+        // enqueued only when the status says so.  Their queues hold items of different levels, which can be
+        // more than any one level has: a run that overflows so is made again
+        // level by level.
+        for (bool deep = true;; deep = false) {
+            CD_HIP(launch_refine_seed(pairs, (uint32_t)count, p->start_ticks, T, delta_ticks,
+                                      w.qa, w.ctl, kRefCtlWords, w.counter, s));
+            int lev = 0;
+            for (int stop = deep ? kRefineFirst : levels;; stop = levels) {
+                for (stop = stop < levels ? stop : levels; lev < stop; ++lev) {
+                    // a launch makes at most two items of one, or, taking them
+                    // down, 2 * kRefineThreads of one workgroup's
+                    const int grow = (deep ? 9 : 1) * lev;
+                    uint64_t most = (uint64_t)count << (grow < 32 ? grow : 32);
+                    if (most > w.qcap)
+                        most = w.qcap;
+                    uint32_t blocks = (uint32_t)((most + 255) / 256);
+                    blocks = blocks < 1 ? 1 : (blocks > 2048 ? 2048 : blocks);
+                    CD_HIP(launch_refine_level(
+                        (int)p->box_rule, w.oc, w.os, (uint32_t)el->n, pairs,
+                        (lev & 1) ? w.qb : w.qa, w.ctl + lev, w.qcap, (lev & 1) ? w.qa : w.qb,
+                        w.ctl + lev + 1, w.qcap, w.raw, (unsigned long long)capacity, w.counter,
+                        w.ctl + kRefCtlFlags, delta_ticks, min_steps, p->tick_s,
+                        0.5 * p->threshold_km, deep, blocks, s));
+                }
+                CD_HIP(launch_refine_status(w.counter, w.ctl + kRefCtlFlags, w.ctl + lev,
+                                            w.ctl + kRefCtlStatus, s));
+                CD_HIP(hipMemcpyAsync(st4, w.ctl + kRefCtlStatus, sizeof st4,
+                                      hipMemcpyDeviceToHost, s));
+                CD_HIP(hipStreamSynchronize(s));
+                if (lev == levels || (st4[2] & 1u) || st4[3] == 0)
+                    break;
+            }
+            if (!deep || !(st4[2] & 1u))
+                break;
         }
-        CD_HIP(launch_refine_status(w.counter, w.ctl + kRefCtlFlags, w.ctl + levels,
-                                    w.ctl + kRefCtlStatus, s));
-        CD_HIP(hipMemcpyAsync(st4, w.ctl + kRefCtlStatus, sizeof st4, hipMemcpyDeviceToHost, s));
-        CD_HIP(hipStreamSynchronize(s));
     }
     unsigned long long cnt = (unsigned long long)st4[0] | ((unsigned long long)st4[1] << 32);
     if (st4[2] & 1u) {

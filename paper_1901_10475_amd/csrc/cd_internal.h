@@ -701,16 +701,19 @@ hipError_t launch_query_finish(const unsigned long long *counter, const unsigned
                                const uint32_t *uniq, uint32_t cap,
                                unsigned long long *count_out, unsigned int *status_out,
                                hipStream_t s);
-// bulk interval refinement (items {record, first instant, last instant, 0})
+// bulk interval refinement (items {record, first instant, last instant, 0});
+// the seed (count > 0) sets the control words too: ctl[0] = count, the others and
+// *leaf_count 0.  deep: a launch may take items down several levels.
 hipError_t launch_refine_seed(const cd_pair *pairs, uint32_t count, uint32_t start, uint32_t T,
-                              uint32_t delta, uint4 *items, hipStream_t s);
+                              uint32_t delta, uint4 *items, unsigned int *ctl,
+                              uint32_t ctl_words, unsigned long long *leaf_count, hipStream_t s);
 hipError_t launch_refine_level(int rule, const ObjConst *oc, const ObjSinus *os, uint32_t n,
                                const cd_pair *pairs, const uint4 *in, const unsigned int *n_in,
                                uint32_t in_cap, uint4 *outq, unsigned int *n_out,
                                uint32_t out_cap, Rec *leaves, unsigned long long leaf_cap,
                                unsigned long long *leaf_count, unsigned int *flags,
                                uint32_t delta, uint32_t min_steps, double tick_s,
-                               double half_thr, uint32_t blocks, hipStream_t s);
+                               double half_thr, bool deep, uint32_t blocks, hipStream_t s);
 hipError_t launch_refine_status(const unsigned long long *leaf_count, const unsigned int *flags,
                                 const unsigned int *last_count, unsigned int *out, hipStream_t s);
 // altitude bands (potential-collision graph); pad = sqrt(3) thr / 2

@@ -155,3 +155,30 @@ def test_empty_records():
     assert cd.cd_refine_records(el, p, 1, none).shape[0] == 0
     with pytest.raises(cd.CDError):
         cd.cd_refine_records(el, p, 0, none)
+
+
+@pytest.mark.parametrize("count,T,capacity", [(1, 20_000, None),      # one record fills the queue
+                                              (3, 255, None),         # halves just fit the lanes
+                                              (3, 513, None),
+                                              (12, 20_000, 1),        # the queue overflows
+                                              (600_000, 8, None)])    # more items than lanes
+def test_every_instant_of_identical_objects(count, T, capacity):
+    """Objects on one orbit collide at every instant, so every record's leaves
+    are all its instants, in whatever launches its halves are taken."""
+    need_gpu()
+    say("refine identical objects", count, T, capacity)
+    el = np.tile(catalog.leo_mix(np.random.default_rng(95), 1), (5, 1))
+    p = cd.params_struct(1e-3, MU, 1.0, T, 1_000)
+    rng = np.random.default_rng(count)
+    pair = np.array([(i, j) for i in range(5) for j in range(i + 1, 5)], np.uint32)
+    which = rng.integers(0, len(pair), count) if count > 12 else np.arange(count) % len(pair)
+    lo = rng.integers(0, T, count) if count > 12 else np.zeros(count, np.int64)
+    hi = np.minimum(lo + 3, T + 1) if count > 12 else np.full(count, T + 1)
+    rec = np.concatenate([pair[which], np.stack([lo, hi], 1).astype(np.uint32)], 1)
+    got = cd.cd_refine_records(cd.soa(el), p, 1, torch.from_numpy(rec.view(np.int32)).cuda(),
+                               capacity=capacity).cpu().numpy().view(np.uint32)
+    at = [(which * (T + 1) + lo + d)[lo + d < hi] for d in range(int((hi - lo).max()))]
+    key = np.unique(np.concatenate(at))
+    t = (key % (T + 1)).astype(np.uint32)
+    want = np.concatenate([pair[key // (T + 1)], np.stack([t, t + 1], 1)], 1)
+    assert np.array_equal(got, want)
