@@ -443,6 +443,26 @@ def test_key_sort_is_stable(N, T):
         assert np.all(np.diff(order)[same] > 0)
 
 
+@pytest.mark.parametrize("rule", [cd.CD_BOX_SPEED, cd.CD_BOX_INTERVAL_E])
+@pytest.mark.parametrize("prec", [cd.CD_FP64, cd.CD_FP32])
+@pytest.mark.parametrize("n", [15, 16, 17, 63, 64, 65, 127, 129, 144])
+def test_box_rows_on_and_off_lines(n, prec, rule):
+    """An object's boxes do not depend on how many others share its slabs, so
+    the rows of n objects (on whole lines where 16 divides n) are the first n of
+    those of 160, bit for bit."""
+    need_gpu()
+    say("box rows", n, prec, rule)
+    el = catalog.leo_mix(np.random.default_rng(21), 160)
+    rows = []
+    for m in (160, n):
+        p = cd.params_struct(1e-3, catalog.MU_EARTH, 1.0, 18_999, 1_000, box_rule=rule)
+        bp = cd.BroadPhase(m, p, None, prec, prec, layout=cd.CD_LAYOUT_OBJECT, in_tree=False)
+        cd.cd_build_boxes(cd.soa(el[:m]), None, p, bp.boxes, bp.ws_boxes)
+        rows.append([a.reshape((19, m) + a.shape[1:])[:, :n] for a in bp.boxes.to_host()])
+    for a, b in zip(*rows):
+        assert np.array_equal(a, b)
+
+
 @pytest.mark.parametrize("T", [5, 640, 1 << 17])
 @pytest.mark.parametrize("N", [2, 511, 8191, 8192, 8193, 524289])
 def test_key_words_formed_by_the_sort(N, T):
