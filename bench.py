@@ -52,18 +52,18 @@ BOX_RULES = {"speed": 0, "nu": 1, "ecc": 2}
 BOX_SUFFIX = {"speed": "", "nu": "_box_interval_nu", "ecc": "_box_interval_ecc"}
 
 TRAFFIC = {
-    # k_agglo_leaves + 8 item passes with their scans and compactions
-    ("hierarchy", "fp64", "fixed"): {"fetch_kib": 2014019.7 + 57452.5 + 10084.2 + 154.1,
-                                     "write_kib": 4469510.2 + 75683.7 + 13266.6 + 234.9,
+    # k_agglo_leaves + 3 item passes
+    ("hierarchy", "fp64", "fixed"): {"fetch_kib": 2016437.7 + 60688.4 + 2100.9 + 64.4,
+                                     "write_kib": 4499608.6 + 77755.2 + 2585.6 + 67.6,
                                      "sources": {"paper_1901_10475_amd/csrc/k_agglo.hip":
-                                                 "5cd4ac788798fc9103eb37ffd7c0fbe8be30b23c"}},
+                                                 "bd2ac70cbd749c5c1c3770a84b2758036d859790"}},
     # k_block_codes + k_block_sort + k_boxes_uniform (records)
-    ("boxes", "fp64", "fixed"): {"fetch_kib": 3205.6 + 38913.2 + 43762.8,
-                                 "write_kib": 29615.6 + 109775.7 + 4114047.9,
+    ("boxes", "fp64", "fixed"): {"fetch_kib": 3200.5 + 14936.4 + 53865.9,
+                                 "write_kib": 29615.6 + 59494.9 + 4128444.9,
                                  "sources": {"paper_1901_10475_amd/csrc/k_boxes.hip":
-                                             "bf37f93ed5022344fdde388ad03e5b9b7779cc91",
+                                             "00c82ba400381dc3c0afacf1d75bf6eaf6c65bc0",
                                              "paper_1901_10475_amd/csrc/k_sort.hip":
-                                             "fb1eebe7f8229aa0d8e2160512a508b55f851817"}},
+                                             "106074fbac895f37d1a8fce5cac82dc5a28b3e6c"}},
 }
 
 

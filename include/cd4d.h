@@ -26,7 +26,7 @@
  *     needed, which sets how many the next one makes before its
  *     first host check; and, per thread, the last synchronous query's launch
  *     count (cd_last_query_levels) and raw record count (when that fitted the
- *     one-workgroup canonical list, the next query forms its list before the
+ *     small canonical list, the next query forms its list before the
  *     first host check, on the device's count).  None of them changes a
  *     result: records depend only on the arguments of the call.
  *   - Streams are hipStream_t values passed as void* (NULL = default stream).
