@@ -1107,7 +1107,7 @@ int cd_query_pairs(const cd_tree *tree, cd_pair *out, int64_t capacity, int64_t 
                     Stage c("canon", s);
                     if (plan) {
                         const DevCount g{w.counter, w.qflags, err, (uint32_t)kSmallCanon, plan};
-                        CD_HIP(launch_medium_canon(w.raw, w.alt, plan, w.flags, w.pos, w.scan,
+                        CD_HIP(launch_medium_canon(w.raw, w.raw, w.alt, plan, w.flags, w.pos, w.scan,
                                                    (Rec *)out, s, g, w.ctl + kCtlCanon, 1u));
                     } else if (small) {
                         const SmallCount g{w.counter, w.qflags, err, limit};
@@ -1182,7 +1182,7 @@ int cd_query_pairs(const cd_tree *tree, cd_pair *out, int64_t capacity, int64_t 
         if (count <= (uint32_t)kSmallCanon) {
             CD_HIP(launch_small_canon(w.raw, count, w.alt, (Rec *)out, w.pos + count, s));
         } else if (count <= (uint32_t)kMediumCanon) {
-            CD_HIP(launch_medium_canon(w.raw, w.alt, count, w.flags, w.pos, w.scan, (Rec *)out,
+            CD_HIP(launch_medium_canon(w.raw, w.raw, w.alt, count, w.flags, w.pos, w.scan, (Rec *)out,
                                        s));
         } else {
             const Rec *res = nullptr;
@@ -1279,7 +1279,7 @@ int cd_query_pairs_async(const cd_tree *tree, cd_pair *out, int64_t capacity,
             r.status_out = status_dev;
             CD_HIP(launch_small_canon(w.raw, cap, w.alt, (Rec *)out, w.pos + cap, s, g, 0u, r));
         } else if (cap <= (uint32_t)kMediumCanon) {
-            CD_HIP(launch_medium_canon(w.raw, w.alt, cap, w.flags, w.pos, w.scan, (Rec *)out,
+            CD_HIP(launch_medium_canon(w.raw, w.raw, w.alt, cap, w.flags, w.pos, w.scan, (Rec *)out,
                                        s));
         } else {
             const Rec *res = nullptr;
@@ -1560,7 +1560,7 @@ int cd_refine_records(const cd_elements *el, const cd_params *p, uint32_t delta_
         if (nleaf <= (uint32_t)kSmallCanon) {
             CD_HIP(launch_small_canon(w.raw, nleaf, w.alt, (Rec *)out, w.pos + nleaf, s));
         } else if (nleaf <= (uint32_t)kMediumCanon) {
-            CD_HIP(launch_medium_canon(w.raw, w.alt, nleaf, w.flags, w.pos, w.scan, (Rec *)out,
+            CD_HIP(launch_medium_canon(w.raw, w.raw, w.alt, nleaf, w.flags, w.pos, w.scan, (Rec *)out,
                                        s));
         } else {
             const Rec *res = nullptr;
@@ -1741,8 +1741,7 @@ int cd_canonical_records(const cd_pair *in, int64_t count, uint32_t horizon_tick
     if (m <= (uint32_t)kSmallCanon) {
         CD_HIP(launch_small_canon((const Rec *)in, m, w.alt, (Rec *)out, w.pos + m, s));
     } else if (m <= (uint32_t)kMediumCanon) {
-        CD_HIP(hipMemcpyAsync(w.raw, in, (size_t)m * sizeof(Rec), hipMemcpyDeviceToDevice, s));
-        CD_HIP(launch_medium_canon(w.raw, w.alt, m, w.flags, w.pos, w.scan, (Rec *)out, s));
+        CD_HIP(launch_medium_canon((const Rec *)in, w.raw, w.alt, m, w.flags, w.pos, w.scan, (Rec *)out, s));
     } else {
         const Rec *res = nullptr;
         CD_HIP(sort_records((const Rec *)in, w.raw, w.alt, m, w.radix, w.flags, &res, s));

@@ -1088,10 +1088,15 @@ __global__ __launch_bounds__(1024) void k_small_unique(const Rec *__restrict__ s
 // own plus the records before it in the others (equal ones of earlier runs
 // first), found by binary searches that advance together.  Bound: the chain of
 // dependent reads of a pass (11 to 17), so few wide passes; in long lists their
-// number.  Against 4 096-record tiles sorted by one workgroup each and merged
-// pairwise: some 5 K records 68 -> 26 us, 180 K 148 -> 153.
+// number.  A pass that has only two or four runs left is compiled for those:
+// every other run costs each step of the search a read of nothing.
+// Whole calls against 4 096-record tiles sorted by one workgroup each and merged
+// pairwise: 5 000 records 165 -> 113 us, 16 000 170 -> 120, 100 000 195 -> 161,
+// 180 000 215 -> 198, 262 000 222 -> 218 (with eight runs in every pass: 117, 139,
+// 192, 229, 253).
 constexpr uint32_t kRunWidth = 1024, kMergeRuns = 8;
 
+template <uint32_t RUNS>
 __global__ __launch_bounds__(256) void k_merge_runs(const Rec *__restrict__ in, uint32_t bound,
                                                     uint32_t width, Rec *__restrict__ out,
                                                     DevCount g)
@@ -1102,19 +1107,19 @@ __global__ __launch_bounds__(256) void k_merge_runs(const Rec *__restrict__ in, 
     const uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= count)
         return;
-    const uint32_t run = k / width, group = run / kMergeRuns * kMergeRuns;
+    const uint32_t run = k / width, group = run / RUNS * RUNS;
     const Rec me = in[k];
     const ulonglong2 x = rec_key(me);
-    uint32_t len[kMergeRuns], pos[kMergeRuns];   // of the other runs; those before me
+    uint32_t len[RUNS], pos[RUNS];   // of the other runs; those before me
 #pragma unroll
-    for (uint32_t q = 0; q < kMergeRuns; ++q) {
+    for (uint32_t q = 0; q < RUNS; ++q) {
         const uint64_t b = (uint64_t)(group + q) * width;
         len[q] = group + q == run || b >= count ? 0u : (uint32_t)(count - b < width ? count - b : width);
         pos[q] = 0;
     }
     for (uint32_t step = width; step; step >>= 1) {
 #pragma unroll
-        for (uint32_t q = 0; q < kMergeRuns; ++q) {
+        for (uint32_t q = 0; q < RUNS; ++q) {
             const bool in_run = pos[q] + step <= len[q];
             const uint64_t at = (uint64_t)(group + q) * width + pos[q] + step - 1;
             const ulonglong2 y = rec_key(in[in_run ? at : k]);
@@ -1125,7 +1130,7 @@ __global__ __launch_bounds__(256) void k_merge_runs(const Rec *__restrict__ in, 
     }
     uint64_t place = (uint64_t)group * width + (k - run * width);
 #pragma unroll
-    for (uint32_t q = 0; q < kMergeRuns; ++q)
+    for (uint32_t q = 0; q < RUNS; ++q)
         place += pos[q];
     out[place] = me;
 }
@@ -1145,20 +1150,31 @@ hipError_t launch_small_canon(const Rec *in, uint32_t count, Rec *tmp, Rec *out,
     return hipGetLastError();
 }
 
-hipError_t launch_medium_canon(Rec *a, Rec *b, uint32_t count, uint32_t *flags, uint32_t *pos,
+hipError_t launch_medium_canon(const Rec *in, Rec *a, Rec *b, uint32_t count, uint32_t *flags, uint32_t *pos,
                                void *scan_ws, Rec *out, hipStream_t s, const DevCount &g,
                                unsigned int *total, uint32_t bias)
 {
     if (count <= (uint32_t)kSmallCanon || count > (uint32_t)kMediumCanon ||
         (g.counter && (!total || g.hi != count || !g.qflags || !g.tree_err)))
         return hipErrorInvalidValue;
-    k_rank_runs<<<dim3(kRunWidth / kRankPer, (count + kRunWidth - 1) / kRunWidth), kRankThreads, 0,
-                  s>>>(a, count, g, kRunWidth, b);
+    // Ranking a run costs its square: past the 65 536 records that two passes
+    // merge a third one runs anyway and takes twice the runs, so they are half as
+    // long (100 000 records 172 -> 161 us a call, 262 000 228 -> 218; a third pass
+    // for fewer records would cost more than that).
+    const uint32_t width = count > kMergeRuns * kMergeRuns * kRunWidth ? kRunWidth / 2 : kRunWidth;
+    k_rank_runs<<<dim3(width / kRankPer, nblk(count, width)), kRankThreads, 0, s>>>(in, count, g,
+                                                                                  width, b);
     hipError_t e = hipGetLastError();
     Rec *src = b, *dst = a;
     // passes for the bound; with a smaller device count the last ones copy
-    for (uint32_t w = kRunWidth; e == hipSuccess && w < count; w *= kMergeRuns) {
-        k_merge_runs<<<nblk(count, 256), 256, 0, s>>>(src, count, w, dst, g);
+    for (uint32_t w = width; e == hipSuccess && w < count; w *= kMergeRuns) {
+        const uint32_t left = nblk(count, w), blocks = nblk(count, 256);
+        if (left <= 2)
+            k_merge_runs<2><<<blocks, 256, 0, s>>>(src, count, w, dst, g);
+        else if (left <= 4)
+            k_merge_runs<4><<<blocks, 256, 0, s>>>(src, count, w, dst, g);
+        else
+            k_merge_runs<kMergeRuns><<<blocks, 256, 0, s>>>(src, count, w, dst, g);
         e = hipGetLastError();
         Rec *t = src;
         src = dst;

@@ -176,3 +176,19 @@ def test_canonical_records_by_the_bits_they_use(count, kind):
     t = torch.from_numpy(rec.view(np.int32)).cuda()
     got = cd.cd_canonical_records(t, (1 << 32) - 2, 1 << 17).cpu().numpy().view(np.uint32)
     assert np.array_equal(got, np.unique(rec, axis=0))
+
+
+@pytest.mark.parametrize("count", [4097, 8192, 8193, 16384, 16385, 32768, 32769, 65537, 131073,
+                                   200_001, 262_144])
+def test_canonical_records_by_merged_runs(count):
+    """Lists of every number of runs left to a merge pass (two, four, eight of
+    1 024, 8 192 and 65 536 records), with repeats; the input is kept."""
+    need_gpu()
+    say("canonical records by runs", count)
+    rng = np.random.default_rng(count)
+    rec = np.stack([rng.integers(0, 50, count), rng.integers(50, 4000, count),
+                    rng.integers(0, 9, count), rng.integers(10, 13, count)], 1).astype(np.uint32)
+    pairs = torch.from_numpy(rec.view(np.int32)).cuda()
+    got = cd.cd_canonical_records(pairs, 20, 4000).cpu().numpy().view(np.uint32)
+    assert np.array_equal(got, np.unique(rec, axis=0))
+    assert np.array_equal(pairs.cpu().numpy().view(np.uint32), rec)
