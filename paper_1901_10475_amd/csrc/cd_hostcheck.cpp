@@ -1,9 +1,11 @@
-// cd_hostcheck.cpp -- the LBVH index arithmetic of cd_logic.h run on the CPU.
+// cd_hostcheck.cpp -- the LBVH index arithmetic of cd_logic.h and the Kepler
+// solver of orbit.h run on the CPU.
 //
 // Pre-flight only: the tests use it to check, without a GPU, that the Karras
-// topology is a proper binary tree, that the skip links follow pre-order, and
-// that the stackless walk the traversal kernel performs terminates and finds
-// the same pairs as the oracle.  It is not a fallback for any library call.
+// topology is a proper binary tree, that the skip links follow pre-order, that
+// the stackless walk the traversal kernel performs terminates and finds
+// the same pairs as the oracle, and that every Kepler solve ends at its root.
+// It is not a fallback for any library call.
 #include <stdint.h>
 #include <string.h>
 #include <algorithm>
@@ -11,6 +13,7 @@
 #include <vector>
 
 #include "cd_logic.h"
+#include "orbit.h"
 
 using namespace cd;
 
@@ -72,6 +75,26 @@ int hc_karras32(const uint64_t *keys, int64_t N, uint32_t slab_size, uint32_t *l
         esc_leaf[i] = slab_size ? slab_escape32(V, n, i) : keys_escape32(keys, n, i);
     }
     return 0;
+}
+
+// Solves of the box kernels: (E, sin E, cos E) of Kepler's equation at M[k] from
+// the cold start to cold[3 k ..], and at M[k] + dM[k] from the warm start there
+// to warm[3 k ..].
+void hc_kepler(int64_t n, const double *M, const double *dM, const double *e, double *cold,
+               double *warm)
+{
+    for (int64_t k = 0; k < n; ++k) {
+        double E = kepler_start(M[k], e[k]), sE, cE, q;
+        kepler(M[k], e[k], E, sE, cE, q);
+        cold[3 * k] = E;
+        cold[3 * k + 1] = sE;
+        cold[3 * k + 2] = cE;
+        E = kepler_next(E, sE, q, e[k], dM[k]);
+        kepler(M[k] + dM[k], e[k], E, sE, cE, q);
+        warm[3 * k] = E;
+        warm[3 * k + 1] = sE;
+        warm[3 * k + 2] = cE;
+    }
 }
 
 uint32_t hc_morton30(double x, double y, double z, const double *mn, const double *inv_ext)

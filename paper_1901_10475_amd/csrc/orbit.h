@@ -36,27 +36,48 @@ __device__ inline ObjConst object_const(double a, double e, double inc, double r
     return c;
 }
 
+// The cold start's single precision: the hardware's sine, cosine and reciprocal,
+// since only a guess is formed from them (on the host, where the tests run the
+// solver, the library's).
+__host__ __device__ inline float start_sin(float x)
+{
+#ifdef __HIP_DEVICE_COMPILE__
+    return __sinf(x);
+#else
+    return sinf(x);
+#endif
+}
+__host__ __device__ inline float start_slope(float e, float x)   // dE/dM at x
+{
+#ifdef __HIP_DEVICE_COMPILE__
+    return __builtin_amdgcn_rcpf(1.0f - e * __cosf(x));
+#else
+    return 1.0f / (1.0f - e * cosf(x));
+#endif
+}
+
 // Cold start of Kepler's equation E - e sin E = M: delta = E - M solved by
 // Newton in single precision on the reduced mean anomaly (|delta| <= e), good
 // to about 1e-6, which is all that the double-precision step below needs.
-__device__ inline double kepler_start(double M, double e)
+__host__ __device__ inline double kepler_start(double M, double e)
 {
     const double turn = 6.283185307179586476925286766559;
     const float m = (float)(M - turn * rint(M * 0.15915494309189533577));
     const float ef = (float)e;
-    float x = ef * __sinf(m) * __builtin_amdgcn_rcpf(1.0f - ef * __cosf(m));
+    float x = ef * start_sin(m) * start_slope(ef, m);
     x = fminf(fmaxf(x, -ef), ef);
 #pragma unroll
     for (int it = 0; it < 2; ++it) {
-        x -= (x - ef * __sinf(m + x)) * __builtin_amdgcn_rcpf(1.0f - ef * __cosf(m + x));
+        x -= (x - ef * start_sin(m + x)) * start_slope(ef, m + x);
         x = fminf(fmaxf(x, -ef), ef);
     }
     return M + (double)x;
 }
 
 // Warm start dM past a solved point (E, sin E, q = dE/dM): the second-order
-// Taylor step.
-__device__ inline double kepler_next(double E, double sE, double q, double e, double dM)
+// Taylor step.  Good for short steps only; of long steps of eccentric orbits
+// the solve below drops it.
+__host__ __device__ inline double kepler_next(double E, double sE, double q, double e, double dM)
 {
     const double x = q * dM;
     return E + (x - 0.5 * (e * q) * sE * x * x);
@@ -70,14 +91,23 @@ __device__ inline double kepler_next(double E, double sE, double q, double e, do
 // b = e cos E q d1^2 / 6 (the reversed Taylor series of f); the step is
 // accepted when a bound on the fourth-order term is below 1e-17, and sin and
 // cos at the root come from the addition theorem with |d| <= 1e-3.  Guesses
-// good to 1e-4 (both starts above, e <= 0.9) pass at once.  f is formed from
+// good to 1e-4 pass at once: the cold start up to e = 0.65 (more than eight in
+// ten beyond), the warm one up to dM = 0.05 at e = 0.3 or 0.1 at e = 0.1.  f is formed from
 // E - M, which is exact, so sin and cos are those of the root itself and not
 // of its rounded value: rms error against 80-bit arithmetic 5.4e-17 for M up
 // to 6.3 and 6.8e-17 for M up to 3000, where Newton to a fixed point (2 to 4
 // sincos per solve) has 1.8e-16 and 8.5e-14.
-__device__ inline void kepler(double M, double e, double &E, double &sE, double &cE, double &q)
+//
+// Newton from a guess far from the root may wander without end where 1 - e cos E
+// is small (of a million solves at e = 0.65 and dM = 1.5, 1 700 did not end in
+// 40 turns), so a guess that has not passed in kKeplerGuess turns gives way to
+// the cold start, and every later turn stays within |E - M| <= e, which holds
+// the root: at most 9 turns for e up to 0.999, 38 for 1 - e = 1e-12.
+constexpr int kKeplerGuess = 3, kKeplerTurns = 100;
+__host__ __device__ inline void kepler(double M, double e, double &E, double &sE, double &cE,
+                                       double &q)
 {
-    for (int it = 0; it < 40; ++it) {
+    for (int turn = 1; turn <= kKeplerTurns; ++turn) {
         double s, c;
         sincos(E, &s, &c);
         q = 1.0 / (1.0 - e * c);
@@ -97,6 +127,10 @@ __device__ inline void kepler(double M, double e, double &E, double &sE, double 
             return;
         }
         E -= (ah < 0.25 && ad < 0.25) ? d : d1;
+        if (turn == kKeplerGuess)
+            E = kepler_start(M, e);
+        else if (turn > kKeplerGuess)
+            E = fmin(fmax(E, M - e), M + e);
     }
     sincos(E, &sE, &cE);
 }
