@@ -26,12 +26,15 @@ struct Walker {
     __device__ void at(double t_s, double p[3])
     {
         double m = c.m0 + c.n * t_s;
-        // short step: extrapolate from the last solution
-        E = warm && fabs(m - M) < 0.25 ? kepler_next(E, sE, q, c.e, m - M) : kepler_start(m, c.e);
+        // short step: extrapolate from the last solution (the choice left to the
+        // solve, which holds one cold start instead of two: with two the walk of
+        // two objects spills, 163 -> 186 us for 235 000 records, with one 152)
+        const bool cold = !(warm && fabs(m - M) < 0.25);
+        E = kepler_next(E, sE, q, c.e, m - M);
         warm = true;
         M = m;
         double cE;
-        kepler(m, c.e, E, sE, cE, q);
+        kepler(m, c.e, E, sE, cE, q, cold);
         position(c, sE, cE, p);
     }
 };

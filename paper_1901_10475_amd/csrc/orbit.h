@@ -83,8 +83,9 @@ __host__ __device__ inline double kepler_next(double E, double sE, double q, dou
     return E + (x - 0.5 * (e * q) * sE * x * x);
 }
 
-// Kepler's equation E - e sin E = M from the guess in E; returns E, sin E,
-// cos E and q = dE/dM = 1 / (1 - e cos E) (q near E, for the next guess).
+// Kepler's equation E - e sin E = M from the guess in E (cold: from the cold
+// start, formed in the one place where the restart below forms it); returns E, sin
+// E, cos E and q = dE/dM = 1 / (1 - e cos E) (q near E, for the next guess).
 //
 // One sincos per solve.  With f = E - e sin E - M and d1 = f q the root lies
 // at E - d, d = d1 (1 + a + 2 a^2 - b) + O(d1^4), a = e sin E q d1 / 2,
@@ -105,9 +106,12 @@ __host__ __device__ inline double kepler_next(double E, double sE, double q, dou
 // the root: at most 9 turns for e up to 0.999, 38 for 1 - e = 1e-12.
 constexpr int kKeplerGuess = 3, kKeplerTurns = 100;
 __host__ __device__ inline void kepler(double M, double e, double &E, double &sE, double &cE,
-                                       double &q)
+                                       double &q, bool cold = false)
 {
     for (int turn = 1; turn <= kKeplerTurns; ++turn) {
+        if (cold)
+            E = kepler_start(M, e);
+        cold = turn == kKeplerGuess;
         double s, c;
         sincos(E, &s, &c);
         q = 1.0 / (1.0 - e * c);
@@ -127,9 +131,7 @@ __host__ __device__ inline void kepler(double M, double e, double &E, double &sE
             return;
         }
         E -= (ah < 0.25 && ad < 0.25) ? d : d1;
-        if (turn == kKeplerGuess)
-            E = kepler_start(M, e);
-        else if (turn > kKeplerGuess)
+        if (turn > kKeplerGuess)
             E = fmin(fmax(E, M - e), M + e);
     }
     sincos(E, &sE, &cE);
