@@ -132,9 +132,15 @@ __global__ __launch_bounds__(kRefineThreads) void k_refine_level(
 {
     __shared__ uint4 held[2][kRefineThreads];
     __shared__ uint32_t wsum[64];
-    __shared__ unsigned int qbase;
+    __shared__ unsigned int qbase, stop;
     __shared__ unsigned long long lbase;
-    if (*flags)
+    // a set flag (queue overflow, or an earlier launch found its queue empty) ends
+    // the run; read once a workgroup, because the workgroups that overflow set it
+    // while others start, and a workgroup's waves must leave together
+    if (threadIdx.x == 0)
+        stop = *flags;
+    __syncthreads();
+    if (stop)
         return;
     uint32_t m = *n_in;
     m = m < in_cap ? m : in_cap;

@@ -182,3 +182,25 @@ def test_every_instant_of_identical_objects(count, T, capacity):
     t = (key % (T + 1)).astype(np.uint32)
     want = np.concatenate([pair[key // (T + 1)], np.stack([t, t + 1], 1)], 1)
     assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("count,span", [(250_000, 4), (250_000, 16), (120_000, 33)])
+def test_queue_overflow_while_workgroups_start(count, span):
+    """Launches that take items down several levels over more workgroups than the
+    chip holds at once, of items that all split: the queue overflows while
+    workgroups are still being dealt out, and the run is made again."""
+    need_gpu()
+    say("refine overflow", count, span)
+    T = 1000
+    el = np.tile(catalog.leo_mix(np.random.default_rng(96), 1), (5, 1))
+    p = cd.params_struct(1e-3, MU, 1.0, T, 1_000)
+    rng = np.random.default_rng(count + span)
+    pair = np.array([(i, j) for i in range(5) for j in range(i + 1, 5)], np.uint32)
+    which = rng.integers(0, len(pair), count)
+    lo = rng.integers(0, T - span, count)
+    rec = np.concatenate([pair[which], np.stack([lo, lo + span], 1).astype(np.uint32)], 1)
+    got = cd.cd_refine_records(cd.soa(el), p, 1, torch.from_numpy(rec.view(np.int32)).cuda(),
+                               capacity=1).cpu().numpy().view(np.uint32)
+    key = np.unique(np.concatenate([which * (T + 1) + lo + d for d in range(span)]))
+    t = (key % (T + 1)).astype(np.uint32)
+    assert np.array_equal(got, np.concatenate([pair[key // (T + 1)], np.stack([t, t + 1], 1)], 1))
