@@ -419,7 +419,10 @@ struct RefineWS {
     void *scan, *radix;
     uint32_t qcap;
 };
-// work items per level: the records twice over, the output capacity, or 2^16
+// work items per level: the records twice over, the output capacity, or 2^16; so
+// many less than 2^32 that the place of a workgroup's next strip of them (at most
+// kRefineBlocks kRefineThreads on) does not wrap, which its loop would not end on
+constexpr uint32_t kRefineBlocks = 2048;
 uint32_t refine_queue_cap(int64_t count, int64_t capacity)
 {
     uint64_t q = (uint64_t)(count > 0 ? count : 0) * 2;
@@ -427,7 +430,8 @@ uint32_t refine_queue_cap(int64_t count, int64_t capacity)
         q = (uint64_t)capacity;
     if (q < 65536)
         q = 65536;
-    return (uint32_t)(q < 0xFFFFFFF0ull ? q : 0xFFFFFFF0ull);
+    const uint64_t most = (1ull << 32) - kRefineBlocks * kRefineThreads;
+    return (uint32_t)(q < most ? q : most);
 }
 size_t layout_refine(void *base, size_t bytes, int64_t n, int64_t count, int64_t cap,
                      RefineWS *w)
@@ -1520,8 +1524,8 @@ int cd_refine_records(const cd_elements *el, const cd_params *p, uint32_t delta_
                     uint64_t most = (uint64_t)count << (grow < 32 ? grow : 32);
                     if (most > w.qcap)
                         most = w.qcap;
-                    uint32_t blocks = (uint32_t)((most + 255) / 256);
-                    blocks = blocks < 1 ? 1 : (blocks > 2048 ? 2048 : blocks);
+                    uint32_t blocks = (uint32_t)((most + kRefineThreads - 1) / kRefineThreads);
+                    blocks = blocks < 1 ? 1 : (blocks > kRefineBlocks ? kRefineBlocks : blocks);
                     CD_HIP(launch_refine_level(
                         (int)p->box_rule, w.oc, w.os, (uint32_t)el->n, pairs,
                         (lev & 1) ? w.qb : w.qa, w.ctl + lev, w.qcap, (lev & 1) ? w.qa : w.qb,

@@ -707,6 +707,7 @@ hipError_t launch_query_finish(const unsigned long long *counter, const unsigned
 hipError_t launch_refine_seed(const cd_pair *pairs, uint32_t count, uint32_t start, uint32_t T,
                               uint32_t delta, uint4 *items, unsigned int *ctl,
                               uint32_t ctl_words, unsigned long long *leaf_count, hipStream_t s);
+constexpr int kRefineThreads = 256;   // items a workgroup takes at a time
 hipError_t launch_refine_level(int rule, const ObjConst *oc, const ObjSinus *os, uint32_t n,
                                const cd_pair *pairs, const uint4 *in, const unsigned int *n_in,
                                uint32_t in_cap, uint4 *outq, unsigned int *n_out,

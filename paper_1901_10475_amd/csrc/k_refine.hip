@@ -78,8 +78,6 @@ __device__ inline void solve_end(const ObjConst &c, double t_s, const EndPt &A, 
     position(c, B.sE, B.cE, pb);
 }
 
-constexpr int kRefineThreads = 256;
-
 // True if the two objects' boxes over the item's span meet.
 template <int RULE>
 __device__ inline bool boxes_meet(const ObjConst *__restrict__ oc, const ObjSinus *__restrict__ os,

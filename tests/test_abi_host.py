@@ -197,6 +197,16 @@ def test_refine_argument_errors_before_any_launch():
     assert L.cd_refine_records_ws(100, 10**6, 0) > L.cd_refine_records_ws(100, 10, 0)
 
 
+def test_refine_queue_ends_a_grid_before_2_32():
+    """Two queues of 16-byte items, of at most 2^32 less a grid's 2048 x 256 items
+    (from there on a workgroup's strips would start over and never end)."""
+    import paper_1901_10475_amd as cd
+    L = cd.lib()
+    other = L.cd_refine_records_ws(1, 1, 0) - 2 * 16 * 65536
+    assert L.cd_refine_records_ws(1, 10**8, 0) == 2 * 16 * 2 * 10**8 + other
+    assert L.cd_refine_records_ws(1, 0x7FFFFFFF, 0) == 2 * 16 * (2**32 - 2048 * 256) + other
+
+
 def test_band_argument_errors_before_any_launch():
     import paper_1901_10475_amd as cd
     L = cd.lib()
