@@ -97,6 +97,13 @@ void hc_kepler(int64_t n, const double *M, const double *dM, const double *e, do
     }
 }
 
+// 1 if the hierarchy's check takes time t to be one of slab u.
+int hc_in_slab(uint32_t u, uint32_t ticks, uint32_t t)
+{
+    uint32_t start, width;
+    return slab_times(u, ticks, &start, &width) && t - start < width ? 1 : 0;
+}
+
 uint32_t hc_morton30(double x, double y, double z, const double *mn, const double *inv_ext)
 {
     return morton30(x, y, z, mn, inv_ext);

@@ -293,6 +293,20 @@ struct CodeKeys {
     }
 };
 
+// The times of slab u (t / ticks == u, ticks >= 1) as one 32-bit comparison:
+// t - start < width.  The last slab may reach past the 32 bits; its width stops
+// there, since a time before the slab would wrap into the rest.  False if the
+// whole slab lies past every 32-bit time.
+__host__ __device__ inline bool slab_times(uint32_t u, uint32_t ticks, uint32_t *start,
+                                           uint32_t *width)
+{
+    const uint64_t at = (uint64_t)u * ticks;
+    const uint32_t room = 0u - (uint32_t)at;   // times from start on (0: all of them)
+    *start = (uint32_t)at;
+    *width = room != 0 && room < ticks ? room : ticks;
+    return at <= 0xFFFFFFFFull;
+}
+
 // Bytes of X (each below 128) that are <= y or < y: the top bit of each byte.
 __host__ __device__ inline uint64_t bytes_le(uint64_t X, uint32_t y)
 {

@@ -647,7 +647,7 @@ __device__ __forceinline__ void seeds_taken(AggShared<TP, LEAVES> &S)
 }
 
 // Is a leaf's slab (t0 / ticks) the one of its position?  ONE: the chunk lies
-// in one slab, whose first tick is `start` (beyond: past every 32-bit tick);
+// in one slab, of the times that slab_times gives (beyond: past every 32-bit tick);
 // else slabs of ms leaves, item K of the chunk being leaf base + K (ms == 0: no
 // slabs).
 template <bool ONE>
@@ -908,9 +908,7 @@ __global__ __launch_bounds__(kAggThreads)
         const Chunk<TP, LEAVES> C{S, N, base, m, P.vL, P.vR, P.vN};
         SlabCheck<SHARED> in_slab{slab_ticks, 0u, base, 0u, false};
         if constexpr (SHARED) {
-            const uint64_t at = (uint64_t)u * slab_ticks;
-            in_slab.start = (uint32_t)at;
-            in_slab.beyond = at > 0xFFFFFFFFull;
+            in_slab.beyond = !slab_times(u, slab_ticks, &in_slab.start, &in_slab.ticks);
         } else if constexpr (kCode) {
             in_slab.ms = G.ms;
         }

@@ -524,3 +524,34 @@ def test_block_sort_sizes(n):
     a = _uniform(n, K, 2, seed=n + 3, layout=cd.CD_LAYOUT_OBJECT, in_tree=False)
     inv = np.argsort(obj, axis=1) + (np.arange(K) * n)[:, None]
     assert np.array_equal(a.boxes.lo[:, :n * K].cpu().numpy().T, lo[inv.ravel()])
+
+
+@pytest.mark.parametrize("n,ticks,when", [(512, 0x80000001, 0), (700, 3_000_000_000, 1_000_000_000),
+                                          (1100, 0xFFFFFFF0, 5), (512, 1_000_000, 1)])
+def test_box_before_a_slab_at_the_end_of_the_ticks(n, ticks, when):
+    """A box whose time lies before its slab is reported also where the slab
+    reaches past the 32 bits, and only then."""
+    need_gpu()
+    say("box before its slab", n, ticks, when)
+    K = 0xFFFFFFFE // ticks + 1 if ticks > 1 << 30 else 4
+    t0 = np.repeat(np.arange(K, dtype=np.int64) * ticks, n)
+    rng = np.random.default_rng(n)
+    lo = rng.uniform(-7000, 7000, (K * n, 3))
+    codes = torch.from_numpy(np.tile(np.sort(rng.integers(0, 1 << 30, n)), K).astype(np.int32)).cuda()
+    for bad in (False, True):
+        t = t0.copy()
+        if bad:
+            t[-n // 2] = when
+        b = cd.Boxes.from_arrays(lo, lo + 1.0, t, t + 1, np.tile(np.arange(n), K),
+                                 horizon_ticks=0xFFFFFFFE, obj_count=n, slab_ticks=ticks, slab_size=n)
+        b.desc.code, b.desc.code_valid, b.desc.layout = codes.data_ptr(), 1, cd.CD_LAYOUT_SORTED
+        tree = cd.Tree(K * n, cd.CD_FP64)
+        cd.cd_build_tree(b, cd.CD_FP64, tree, cd._bytes(cd.lib().cd_build_tree_ws(K * n), "cuda"))
+        out = torch.empty((1 << 16, 4), dtype=torch.int32, device="cuda")
+        ws = cd._bytes(cd.lib().cd_query_pairs_ws(K * n, 1 << 16), "cuda")
+        if bad:
+            with pytest.raises(cd.CDError) as ei:
+                cd.cd_query_pairs(tree, out, 1 << 16, ws)
+            assert ei.value.status == cd.CD_E_INVALID
+        else:
+            assert cd.cd_query_pairs(tree, out, 1 << 16, ws)[0] == cd.CD_OK

@@ -297,3 +297,20 @@ def test_bottom_up_build_gives_the_karras_tree(seed, N, bits, slab, chunk):
         assert np.array_equal(right[:N - 1], ref[1][:N - 1])
         assert np.array_equal(esc_in[:N - 1], ref[4][:N - 1])
         assert np.array_equal(esc_leaf, ref[5])
+
+
+@pytest.mark.parametrize("ticks", [1, 2, 1000, 0x10001, 0x7FFFFFFF, 0x80000000, 0x80000001,
+                                   3_000_000_000, 0xFFFFFFFF])
+def test_slab_times_are_those_of_the_division(ticks):
+    """The one-comparison slab check equals t / ticks == u, up to the slab that
+    reaches past the 32 bits and those beyond it."""
+    L = ctypes.CDLL(LIB)
+    L.hc_in_slab.argtypes = [ctypes.c_uint32] * 3
+    last = 0xFFFFFFFF // ticks
+    edge = lambda x: [y for y in (x - 1, x, x + 1) if 0 <= y <= 0xFFFFFFFF]
+    slabs = sorted({u for b in (0, last // 2, last, min(last + 3, 0xFFFFFFFF)) for u in edge(b)})
+    times = sorted({t for b in [0, 0x80000000, 0xFFFFFFFF] + [u * ticks for u in slabs]
+                    + [(u * ticks) & 0xFFFFFFFF for u in slabs] for t in edge(b)})
+    for u in slabs:
+        for t in times:
+            assert L.hc_in_slab(u, ticks, t) == (t // ticks == u), (u, t)
