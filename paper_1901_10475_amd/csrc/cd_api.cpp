@@ -935,19 +935,10 @@ int cd_build_tree(const cd_boxes *boxes, int precision, uint32_t slab_ticks, cd_
         // per-object steps and other unsorted box sets: one key sort, the
         // boxes then read through the sorted items.  When slab, code and box
         // index fit one 64-bit word the sort moves 8-byte items instead of
-        // 16-byte (key, index) pairs; box sets too large for the whole code
-        // keep its top bits (at least kMinPackedCodeBits of 30)
+        // 16-byte (key, index) pairs
         const int sb = bits_for(max_slab), ib = N > 1 ? bits_for((uint64_t)N - 1) : 1;
-        const int room = 64 - sb - ib;
-        int cb = room < (int)kKeyCodeBits ? room : (int)kKeyCodeBits;
-        const bool packed = cb >= (int)kMinPackedCodeBits;
-        // the sort takes 9 bits a pass, so a key one bit past that (37 with the
-        // default slabs) gives up the code's last bit: at 88 M boxes a digit of
-        // 10 bits takes 617 us to scatter, one of 9 414, and the tree of 29
-        // code bits is traversed in the same 2.89 ms (at 79.7 M boxes 430 and
-        // 311 us, traversal 1.07 and 1.13 ms)
-        if (packed && (cb + sb) % 9 == 1)
-            --cb;
+        const int cb = packed_code_bits(sb, ib);
+        const bool packed = cb > 0;
         // words of boxes that carry codes are formed by the sort's first pass
         // (at 88 M boxes 558 us for it, where a kernel for the keys and a pass
         // over them take 274 + 600); codes formed from the boxes, which costs

@@ -104,6 +104,8 @@ int hc_in_slab(uint32_t u, uint32_t ticks, uint32_t t)
     return slab_times(u, ticks, &start, &width) && t - start < width ? 1 : 0;
 }
 
+int hc_packed_code_bits(int sb, int ib) { return packed_code_bits(sb, ib); }
+
 uint32_t hc_morton30(double x, double y, double z, const double *mn, const double *inv_ext)
 {
     return morton30(x, y, z, mn, inv_ext);

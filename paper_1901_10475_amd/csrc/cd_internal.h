@@ -389,6 +389,20 @@ hipError_t radix_sort16(void *a, void *b, size_t count, const DigitPlan &plan, v
 // code' << ib | box index (N <= 2^ib), slab = t0 / slab_ticks (at most max_slab,
 // else err bit 1), code' the top cb bits of the code's low kKeyCodeBits.
 constexpr uint32_t kKeyCodeBits = 30, kMinPackedCodeBits = 24;
+// Code bits of a packed key word beside sb slab and ib index bits, or 0 if words
+// do not do: box sets too large for the whole code keep its top bits, at least
+// kMinPackedCodeBits.  The sort takes 9 bits a pass, so a key one bit past that
+// (37 with the default slabs) gives up the code's last bit if it has one to spare:
+// at 88 M boxes a digit of 10 bits takes 617 us to scatter, one of 9 414, and the
+// tree of 29 code bits is traversed in the same 2.89 ms (at 79.7 M boxes 430 and
+// 311 us, traversal 1.07 and 1.13 ms).
+inline int packed_code_bits(int sb, int ib)
+{
+    const int room = 64 - sb - ib, cb = room < (int)kKeyCodeBits ? room : (int)kKeyCodeBits;
+    if (cb < (int)kMinPackedCodeBits)
+        return 0;
+    return cb > (int)kMinPackedCodeBits && (cb + sb) % 9 == 1 ? cb - 1 : cb;
+}
 struct KeySource {
     const uint32_t *code, *t0;
     unsigned int *err;

@@ -314,3 +314,17 @@ def test_slab_times_are_those_of_the_division(ticks):
     for u in slabs:
         for t in times:
             assert L.hc_in_slab(u, ticks, t) == (t // ticks == u), (u, t)
+
+
+def test_packed_key_words_keep_the_code_bits_promised():
+    """Words hold slab, code and index in 64 bits with 24 to 30 code bits, all
+    that there is room for but at most one."""
+    L = ctypes.CDLL(LIB)
+    L.hc_packed_code_bits.argtypes = [ctypes.c_int] * 2
+    for sb in range(33):
+        for ib in range(1, 31):
+            room, cb = 64 - sb - ib, L.hc_packed_code_bits(sb, ib)
+            if room < 24:
+                assert cb == 0, (sb, ib)
+            else:
+                assert max(24, min(room, 30) - 1) <= cb <= min(room, 30), (sb, ib)
