@@ -274,3 +274,38 @@ def test_node_pair_launches_of_dense_boxes(n, K, km, prec):
                 {"max_levels": 3}, {"max_levels": 40, "expand_blocks": 64, "expand_threads": 64}):
         got, c, s = _async(bp, cap, tun)
         assert s == 0 and np.array_equal(got, ref), tun
+
+
+@pytest.mark.parametrize("prec", [cd.CD_FP64, cd.CD_FP32])
+@pytest.mark.parametrize("n,K,km", [(300, 7, 3000.0), (300, 7, 10_000.0), (1500, 40, 300.0)])
+def test_node_pairs_answer_dense_boxes_themselves(n, K, km, prec):
+    """Dense boxes whose sibling pairs still fit the seed list: no query of them
+    is finished by the per-leaf walk, neither the synchronising one (which then
+    reports its launches) nor, given launches to spare, the device-count one
+    (whose walk steps the counters build counts)."""
+    need_gpu()
+    say("dense boxes by node pairs, n", n, "K", K, "km", km, "precision", prec)
+    rng = np.random.default_rng(n)
+    el = cd.soa(catalog.leo_mix(rng, n))
+    p = cd.params_struct(1.0, catalog.MU_EARTH, km, 2 * K - 1, 2)
+    with cd.counters_build():
+        bp = cd.BroadPhase(n, p, box_precision=prec, tree_precision=prec, capacity=1 << 20)
+        bp.build(el)
+        shapes = (None, {"expand_blocks": 64, "expand_threads": 64},
+                  {"expand_blocks": 64, "expand_threads": 1024})
+        cd.cd_set_tuning({"mode": 1})
+        try:
+            ref = bp.query().cpu().numpy()
+            assert cd.cd_last_query_levels() == 0 and len(ref) > 10_000
+            for tun in shapes:
+                cd.cd_set_tuning(tun)
+                assert np.array_equal(bp.query().cpu().numpy(), ref), tun
+                assert cd.cd_last_query_levels() > 0, tun
+        finally:
+            cd.cd_set_tuning(None)
+        for tun in shapes:
+            cd.cd_counters_reset(None)
+            got, c, s = _async(bp, len(ref), dict(tun or {}, max_levels=40))
+            assert s == 0 and np.array_equal(got, ref), tun
+            work = cd.cd_counters_read()
+            assert work["walk_steps"] == 0 and work["pairs"] > 0, tun

@@ -555,3 +555,39 @@ def test_box_before_a_slab_at_the_end_of_the_ticks(n, ticks, when):
             assert ei.value.status == cd.CD_E_INVALID
         else:
             assert cd.cd_query_pairs(tree, out, 1 << 16, ws)[0] == cd.CD_OK
+
+
+@pytest.mark.parametrize("T", [1, 5, 100000])
+@pytest.mark.parametrize("N", [2, 8191, 8192, 8193, 458753])
+def test_key_sort_orders_distinct_cells(N, T):
+    """The packed key sort of boxes on points of 13 cells of the code's grid:
+    leaves by slab, then by the point's code, then in input order."""
+    need_gpu()
+    say("key sort of distinct cells, N", N, "T", T)
+    rng = np.random.default_rng(3 * N + T)
+    k = np.arange(13)
+    pts = np.stack([k % 4, k // 4 % 4, (7 * k) % 13], 1) * 1000.0   # 85 cells apart at least
+    assert len(np.unique(pts, axis=0)) == 13
+    which = np.r_[k, rng.integers(0, 13, N)][:N] if N > 13 else rng.integers(0, 13, N)
+    t0 = rng.integers(0, T, N)
+    b = cd.Boxes.from_arrays(pts[which], pts[which] + 1.0, t0, t0 + 1, np.arange(N),
+                             horizon_ticks=T, obj_count=N)
+    tree = cd.Tree(N, cd.CD_FP64)
+    cd.cd_build_tree(b, cd.CD_FP64, tree, cd._bytes(cd.lib().cd_build_tree_ws(N), "cuda"), 1)
+    torch.cuda.synchronize()
+    raw = tree.mem.cpu().numpy().view(np.uint8)
+    assert raw[:4].view(np.uint32)[0] == 0
+    leaf = raw[256 + (N - 1) * 64:256 + (2 * N - 1) * 64].reshape(N, 64)[:, 48:64]
+    order = leaf.copy().view(np.uint32)[:, 2].astype(np.int64)
+    assert np.array_equal(np.sort(order), np.arange(N))
+    group = t0[order] * 13 + which[order]
+    run = np.r_[True, np.diff(group) != 0]
+    assert np.all(np.diff(t0[order]) >= 0) and run.sum() == len(np.unique(group))
+    assert np.all(np.diff(order)[~run[1:]] > 0)
+    if N > 13:   # the points stand in one order, the same in every slab
+        first = which[order][run]
+        slab = t0[order][run]
+        full = [s for s in np.unique(slab) if (slab == s).sum() == 13][:50]
+        assert full or T > 1000
+        for s in full:
+            assert np.array_equal(first[slab == s], first[slab == full[0]])
