@@ -328,9 +328,10 @@ int cd_query_pairs(const cd_tree *tree, cd_pair *out, int64_t capacity, int64_t 
  * The node-pair traversal runs for the tuning's max_levels launches (one
  * expands one level of many pairs, several levels of few), each ending at once
  * when the previous queue is empty; if its queue overflows or is not drained by
- * then, the per-leaf walk redoes the traversal, decided on the device.  The canonical sort runs over all
- * `capacity` slots (unused slots hold a filler record that sorts last), so
- * its cost follows the capacity, not the count.  Workspace as for
+ * then, the per-leaf walk redoes the traversal, decided on the device.  Up to a
+ * capacity of 4 096 the canonical list is formed of the records present; above,
+ * its sort runs over all `capacity` slots (unused slots hold a filler record that
+ * sorts last), so its cost follows the capacity, not the count.  Workspace as for
  * cd_query_pairs.  Returns CD_OK once everything is enqueued. */
 int cd_query_pairs_async(const cd_tree *tree, cd_pair *out, int64_t capacity,
                          unsigned long long *count_dev, unsigned int *status_dev, void *ws,
@@ -381,9 +382,13 @@ typedef struct {
 int cd_set_tuning(const cd_tuning *t);
 int cd_get_tuning(cd_tuning *t);
 /* Node-pair launches the calling thread's last cd_query_pairs made until its
- * queue was empty (0 when that query used the per-leaf walk, or none ran):
- * on the same tree, a max_levels with which cd_query_pairs_async needs no
- * walk. */
+ * queue was empty (0 when that query used the per-leaf walk, or none ran): on
+ * the same tree, a max_levels with which cd_query_pairs_async is expected to need
+ * no walk.  How pairs fall to the device's waves, and with it this number, may
+ * differ by a launch or so between runs; the device-count query's last launch
+ * takes what earlier ones left as far as its waves hold it, and the walk finishes
+ * whatever is left then (slower, the same list).  A launch or two to spare cost a
+ * few microseconds each. */
 int cd_last_query_levels(void);
 
 /* ---- executed-work counters (diagnostic build) --------------------------- */

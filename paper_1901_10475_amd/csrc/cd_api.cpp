@@ -185,10 +185,9 @@ std::atomic<int> g_expand_levels{kExpandBatch};
 // drain its queue (0: the per-leaf walk ran, or no query yet).
 thread_local int g_last_levels = 0;
 // Raw record count of the calling thread's last synchronous query: when it
-// fits the one-workgroup canonical list (or the tile-and-merge path, with a
-// quarter to spare), the next query forms that list right after its
-// node-pair levels, before the host reads the count, which saves a round
-// trip to the host.
+// fits the small canonical list (or the one of merged runs, with a quarter to
+// spare), the next query forms that list right after its node-pair launches,
+// before the host reads the count, which saves a round trip to the host.
 thread_local unsigned long long g_last_records = 0;
 
 int check_params(const cd_params *p)
@@ -1064,7 +1063,7 @@ int cd_query_pairs(const cd_tree *tree, cd_pair *out, int64_t capacity, int64_t 
             unsigned int qf = 0;
             bool try_canon = true;
             const unsigned long long last = g_last_records;
-            uint32_t plan = 0;   // bound of a tile-and-merge list formed early
+            uint32_t plan = 0;   // bound of a list of merged runs formed early
             if (last > (unsigned long long)kSmallCanon && last <= (unsigned long long)kMediumCanon) {
                 unsigned long long b = (last + last / 4 + kSmallCanon) / kSmallCanon * kSmallCanon;
                 b = b < (unsigned long long)kMediumCanon ? b : (unsigned long long)kMediumCanon;
@@ -1500,9 +1499,9 @@ int cd_refine_records(const cd_elements *el, const cd_params *p, uint32_t delta_
         // Launches that take few items several levels down end most runs within
         // kRefineFirst of them (seven for 235 000 records of up to 16 000
         // instants, of which 14 launches make a level each), so the rest are
-        // enqueued only when the status says so.  Their queues hold items of different levels, which can be
-        // more than any one level has: a run that overflows so is made again
-        // level by level.
+        // enqueued only when the status says so.  Their queues hold items of
+        // different levels, which can be more than any one level has: a run that
+        // overflows so is made again level by level.
         for (bool deep = true;; deep = false) {
             CD_HIP(launch_refine_seed(pairs, (uint32_t)count, p->start_ticks, T, delta_ticks,
                                       w.qa, w.ctl, kRefCtlWords, w.counter, s));

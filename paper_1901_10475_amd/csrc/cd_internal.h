@@ -791,8 +791,10 @@ hipError_t launch_small_canon(const Rec *in, uint32_t count, Rec *tmp, Rec *out,
 // kSmallCanon < count <= kMediumCanon: short runs sorted, merged eight at a
 // time, then repeats removed (launch_unique; total at pos[count]).  in holds the
 // records (kept, unless it is a); a and b are scratch of count records.  Up to 2^18
-// records three merge passes cost less than the radix path's ten digit passes
-// (three launches each): calls over 262 000 records take 218 us, over 270 000 270.
+// records three merge passes cost less than the radix path, its read of the
+// widths in use and its digit passes (eight of up to four launches each for 100 000
+// objects over 21.6 M ticks): calls over 262 000 records take 218 us, over 270 000
+// 270.
 constexpr int kMediumCanon = 1 << 18;
 // A record count read on the device when the kernels run, for lists
 // enqueued before the host knows it: valid when the node-pair levels drained

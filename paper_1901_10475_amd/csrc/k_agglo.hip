@@ -1164,8 +1164,9 @@ __global__ __launch_bounds__(kAggThreads) void k_agglo_items(
 
 namespace {
 
-// Chunks of pass 1, at most: all but the last are full, or (slabs of
-// kAggSlabMin boxes and more) each holds at least kAggSlabMin leaves.
+// Chunks of pass 1, at most: all but the last are full, or (slabs of ms >=
+// kAggSlabMin boxes) a slab has ceil(ms / 1024) of them, which is at most
+// floor(ms / 512).
 size_t agglo_chunks(uint32_t N) { return N < 2 * kAggSlabMin ? 1 : N / kAggSlabMin; }
 
 // The workspace: pass 1's roots per chunk, the lists of every other pass

@@ -28,7 +28,7 @@ struct Walker {
         double m = c.m0 + c.n * t_s;
         // short step: extrapolate from the last solution (the choice left to the
         // solve, which holds one cold start instead of two: with two the walk of
-        // two objects spills, 163 -> 186 us for 235 000 records, with one 152)
+        // two objects spills, 163 -> 186 us for 231 000 records, with one 152)
         const bool cold = !(warm && fabs(m - M) < 0.25);
         E = kepler_next(E, sE, q, c.e, m - M);
         warm = true;

@@ -20,8 +20,9 @@
 
 namespace cd {
 
-// The control words of a run over count records, and record r's instants: the first grid instant at or after t_lo and the last at
-// or before min(t_hi - 1, T); an empty record gets first > last.
+// The control words of a run over count records, and record r's instants: the
+// first grid instant at or after t_lo and the last at or before min(t_hi - 1, T);
+// an empty record gets first > last.
 __global__ void k_refine_seed(const cd_pair *__restrict__ pairs, uint32_t count, uint32_t start,
                               uint32_t T, uint32_t delta, uint4 *__restrict__ items,
                               unsigned int *__restrict__ ctl, uint32_t ctl_words,

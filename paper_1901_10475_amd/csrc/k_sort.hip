@@ -11,10 +11,10 @@
 //   * k_slab_build: one 1024-thread workgroup per time slab; keys stay in
 //     registers and move through LDS between digit passes, so a slab of up to
 //     kSegCap boxes is sorted with one read and one write of global memory.
-// Both rank digits stably with the same wave-level scheme: the lanes holding
-// equal digits are found with eight ballots, the lowest of them bumps a
-// per-(digit, wave) counter in LDS, and a digit-major scan of those counters
-// turns per-wave ranks into positions.
+// All rank digits stably with the same wave-level scheme: the lanes holding
+// equal digits are found with a ballot for each bit of the digit, the lowest of
+// them bumps a per-(digit, wave) counter in LDS, and a digit-major scan of those
+// counters turns per-wave ranks into positions.
 #include "cd_internal.h"
 
 namespace cd {
