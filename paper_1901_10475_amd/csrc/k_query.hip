@@ -717,7 +717,12 @@ __global__ __launch_bounds__(1024) void k_expand_all(const void *__restrict__ tr
     __shared__ uint32_t wsum[64];
     __shared__ unsigned int qbase, go;
     __shared__ unsigned long long rbase;
-    if (load_dev(flags) & 7u)   // handed over before the launch: the same in every workgroup
+    // handed over before the launch, or while this workgroup was not yet running:
+    // read once, because a workgroup's waves must leave together
+    if (threadIdx.x == 0)
+        go = (load_dev(flags) & 7u) == 0;
+    __syncthreads();
+    if (!go)
         return;
     const uint2 *in = seeds;
     const unsigned int *n_in = nseeds;

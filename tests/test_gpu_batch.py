@@ -309,3 +309,38 @@ def test_node_pairs_answer_dense_boxes_themselves(n, K, km, prec):
             assert s == 0 and np.array_equal(got, ref), tun
             work = cd.cd_counters_read()
             assert work["walk_steps"] == 0 and work["pairs"] > 0, tun
+
+
+@pytest.mark.parametrize("prec", [cd.CD_FP64, cd.CD_FP32])
+@pytest.mark.parametrize("n", [300, 1500])
+def test_queue_overflow_in_every_mode(n, prec):
+    """Bars along x over bars along y: few siblings overlap, every crossing pair
+    does, so the queues overflow in the middle of the levels (n = 1 500) or nearly
+    fill; the per-leaf walk then makes the list, in every mode."""
+    need_gpu()
+    say("crossing bars", n, prec)
+    k = np.arange(n)
+    far = np.full(n, 10.0 * n)
+    lo = np.concatenate([np.column_stack([0 * far, 10.0 * k, 0.0 * k]),
+                         np.column_stack([10.0 * k, 0 * far, 0.0 * k])])
+    hi = np.concatenate([np.column_stack([far, 10.0 * k + 1, 0.0 * k + 1]),
+                         np.column_stack([10.0 * k + 1, far, 0.0 * k + 1])])
+    N = 2 * n
+    b = cd.Boxes.from_arrays(lo, hi, np.zeros(N), np.ones(N), np.arange(N), precision=prec,
+                             horizon_ticks=1, obj_count=N)
+    tree = cd.Tree(N, prec)
+    cd.cd_build_tree(b, prec, tree, cd._bytes(cd.lib().cd_build_tree_ws(N), "cuda"))
+    cap = n * n + 10
+    out = torch.empty((cap, 4), dtype=torch.int32, device="cuda")
+    ws = cd._bytes(cd.lib().cd_query_pairs_ws(N, cap), "cuda")
+    i, j = np.divmod(np.arange(n * n), n)
+    want = np.column_stack([i, n + j, 0 * i, 0 * i + 1])
+    try:
+        for mode in (0, 1, 2):
+            for blocks in (64, 2048):
+                cd.cd_set_tuning({"mode": mode, "expand_blocks": blocks})
+                rc, cnt = cd.cd_query_pairs(tree, out, cap, ws)
+                assert rc == cd.CD_OK and cnt == n * n, (mode, blocks, rc, cnt)
+                assert np.array_equal(out[:cnt].cpu().numpy(), want), (mode, blocks)
+    finally:
+        cd.cd_set_tuning(None)
